@@ -601,7 +601,7 @@ fe_status fe_set_projectors(fe_mesh_t m, int32_t natoms, const double *pos, int3
   release(m, m->nl_atom_off); release(m, m->nl_atom_nodes); release(m, m->nl_atom_proj);
   release(m, m->nl_F64); release(m, m->nl_F32); release(m, m->nl_rows); release(m, m->nl_rowptr);
   release(m, m->nl_colidx); release(m, m->nl_val64); release(m, m->nl_val32); release(m, m->nl_h);
-  release(m, m->nl_chunk_atom); release(m, m->nl_chunk_n0); release(m, m->nl_chunk_order); release(m, m->nl_atom_chunk0); release(m, m->nl_proj_atom);
+  release(m, m->nl_chunks); release(m, m->nl_atom_chunk0); release(m, m->nl_proj_atom);
   release(m, m->nl_b_row0); release(m, m->nl_b_p0); release(m, m->nl_b_proj); release(m, m->nl_b_rows);
   release(m, m->nl_b_rowptr); release(m, m->nl_b_lcol); release(m, m->nl_b_val32);
   release(m, m->nl_b_A64); release(m, m->nl_b_aoff); release(m, m->nl_b_k);
@@ -839,7 +839,7 @@ fe_status fe_set_projectors(fe_mesh_t m, int32_t natoms, const double *pos, int3
   // that chunks of different atoms covering one region run close in time and
   // the X rows they share are read again from the caches instead of HBM.
   // (The partials keep their per-atom order, so the sums are unchanged.)
-  std::vector<int> chunk_order(chunk_atom.size());
+  std::vector<int> chunks;   // per chunk in this order: partial slot, first support entry, entries, projectors of its atom
   {
     std::vector<std::pair<int, int>> key(chunk_atom.size());
     for (size_t c = 0; c < chunk_atom.size(); ++c) {
@@ -848,7 +848,10 @@ fe_status fe_set_projectors(fe_mesh_t m, int32_t natoms, const double *pos, int3
       key[c] = {atom_nodes[mid], (int)c};
     }
     std::sort(key.begin(), key.end());
-    for (size_t c = 0; c < key.size(); ++c) chunk_order[c] = key[c].second;
+    for (const auto &kc : key) {
+      const int c = kc.second, a = chunk_atom[c], n0 = chunk_n0[c];
+      chunks.insert(chunks.end(), {c, n0, std::min(NL_CHUNK, atom_off[a + 1] - n0), proj_off[a + 1] - proj_off[a]});
+    }
   }
   // Brick partition of the rows for the LDS-staged update: rows grouped by
   // 8^3-node bricks of the node grid, a brick split into its eight 4^3
@@ -962,9 +965,7 @@ fe_status fe_set_projectors(fe_mesh_t m, int32_t natoms, const double *pos, int3
   m->nl_nbrick = (int)b_row0.size() - 1;
   m->nl_bmaxp = bmaxp;
   if ((st = upload(m, &m->nl_h, hv))) return st;
-  if ((st = upload(m, &m->nl_chunk_atom, chunk_atom))) return st;
-  if ((st = upload(m, &m->nl_chunk_n0, chunk_n0))) return st;
-  if ((st = upload(m, &m->nl_chunk_order, chunk_order))) return st;
+  if ((st = upload(m, &m->nl_chunks, chunks))) return st;
   if ((st = upload(m, &m->nl_atom_chunk0, atom_chunk0))) return st;
   if ((st = upload(m, &m->nl_proj_atom, proj_atom))) return st;
   m->nl_nchunks = (int)chunk_atom.size();

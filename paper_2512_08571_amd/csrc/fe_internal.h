@@ -201,9 +201,8 @@ struct Mesh {
   int64_t nl_nsup = 0;
   int nl_maxproj = 0;
   int nl_nchunks = 0;
-  int *nl_chunk_atom = nullptr;         // atom of each node chunk
-  int *nl_chunk_n0 = nullptr;           // first support-list entry of each chunk
-  int *nl_chunk_order = nullptr;        // execution order of the chunks (by position)
+  int *nl_chunks = nullptr;             // [nchunks][4] node chunks in execution order (by position): partial
+                                        // slot, first support-list entry, entries, projectors of the atom
   int *nl_atom_chunk0 = nullptr;        // [natoms+1] chunk offsets
   int *nl_proj_atom = nullptr;          // atom of each projector
   std::vector<int> h_atom_off, h_atom_proj;

@@ -6,8 +6,8 @@
 //             conj(F[n][s]) X[node][lane]; one workgroup per (node chunk of one
 //             atom, 256-lane tile), the chunks run in order of position, each
 //             XCD taking a contiguous run of them, so that overlapping atoms'
-//             chunks share cached X rows in one L2; the four waves
-//             split the nodes and are summed in LDS in a fixed order
+//             chunks share cached X rows in one L2; the block's row groups
+//             split the nodes and are summed in a fixed order
 //   k_nl_wsum W[s][lane] = h_s sum over the atom's chunks, in chunk order
 //   k_nl_yb   the rows grouped by node bricks: one workgroup per (brick, lane
 //             tile) stages the W rows of the brick's projectors in LDS once,
@@ -27,6 +27,7 @@
 // for the nonlocal part of Alg. 1).
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "fe_internal.h"
 
@@ -42,6 +43,7 @@ __device__ __forceinline__ uint16_t nl_f2bf(float f) {
 }
 constexpr int NL_THREADS = 256;
 constexpr int NL_TILE = 256;    // lanes per wave (4 per thread)
+constexpr int NL_W_FEW = 512;   // blocks below which the reduction takes more waves per chunk (launch_nl_w_tl)
 
 // Four adjacent lanes starting at element offset o of a row; VEC: the four
 // are in range and 4-element aligned, so one vector access moves them.
@@ -130,6 +132,22 @@ template <bool VEC> struct Pair {
   }
 };
 
+// Quad load without a branch: elements past nv (>= 1) read the last one in
+// range, so that rows in flight are not separated by conditional blocks
+template <typename TS, typename TC, bool VEC>
+__device__ __forceinline__ void quad_ld_clamped(const TS *p, int64_t o, int nv, TC v[4]) {
+  if constexpr (VEC) {
+    Quad<TS, TC, true>::ld(p, o, nv, v);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      TC t[4];
+      Quad<TS, TC, false>::ld(p, o + min(j, nv - 1), 1, t);
+      v[j] = t[0];
+    }
+  }
+}
+
 // 16 bytes of compute-type lanes per thread in the brick update
 template <typename TS, typename TC, bool VEC> struct BrickIO { using T = Quad<TS, TC, VEC>; };
 template <bool VEC> struct BrickIO<double, double, VEC> { using T = Pair<VEC>; };
@@ -149,60 +167,106 @@ __device__ __forceinline__ void nl_conj_fma(TC fr, TC fi, const TC x[4], TC acc[
   }
 }
 
-template <bool CPLX, typename TS, typename TC, bool VEC>
-__global__ void __launch_bounds__(NL_THREADS)
+// One chunk of one atom's support nodes: a row of the block is moved by TL
+// threads (four lanes each), so a wave holds 64 / TL rows at a time and the
+// block NW times as many; each group of TL threads takes every (NW 64 / TL)-th
+// node, U of them in flight.  The groups of a wave are summed by lane
+// exchanges and the waves in LDS, both in a fixed order.  PMAX bounds the
+// projectors per atom: it sizes the accumulators.
+// What bounds it: reading the rows.  Where the chunks do not fill the device
+// the time is the latency of one chunk's chain of row reads, which the node
+// indices staged in LDS, the groups and the waves shorten (times at
+// launch_nl_w_tl).
+template <bool CPLX, typename TS, typename TC, bool VEC, int PMAX, int TL, int NW>
+__global__ void __launch_bounds__(64 * NW)
 k_nl_w(const TS *__restrict__ X, int64_t ldx, int nlanes, const double *__restrict__ dinv,
-       const int *__restrict__ chunk_order, int nchunks, const int *__restrict__ chunk_atom, const int *__restrict__ chunk_n0,
-       const int *__restrict__ nodes,
-       const int *__restrict__ atom_off, const int *__restrict__ proj_off, const TC *__restrict__ F, int fstride,
+       const int4 *__restrict__ chunks, int nchunks, const int *__restrict__ nodes, const TC *__restrict__ F, int fstride,
        TC *__restrict__ part, int64_t ldp) {
-  __shared__ TC red[4][NL_TILE];
+  constexpr int C = CPLX ? 2 : 1;
+  constexpr int TILE = 4 * TL;                   // lanes per block
+  constexpr int GW = 64 / TL, G = GW * NW;       // node groups per wave, per block
+  constexpr int U = NW == 4 ? 2 : 4;             // nodes in flight per group
+  // projectors summed per step: all of them where their sums fit 32 KiB
+  constexpr int SB = (int)sizeof(TC) * PMAX * NW * TILE <= 32768 ? PMAX : 1;
+  __shared__ int snode[NL_CHUNK];
+  __shared__ TC red[SB][NW][TILE];
   // XCD-aware: block x runs on XCD x % 8, and each XCD takes a contiguous run
   // of the position-ordered chunks, so overlapping atoms' chunks share an L2
   const int item = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   if (item >= nchunks) return;                   // whole block: before any barrier
-  const int ch = chunk_order[item];
+  const int4 cd = chunks[item];                  // partial slot, first support entry, entries, projectors
+  const int ch = cd.x, n0 = cd.y, nn = cd.z, ns = cd.w;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int l0 = blockIdx.y * NL_TILE + (threadIdx.x & 63) * 4;
-  const int nv = min(4, nlanes - l0);            // lanes of this thread in range
-  const int a = chunk_atom[ch];
-  const int n0 = chunk_n0[ch];
-  const int n1 = min(n0 + NL_CHUNK, atom_off[a + 1]);
-  const int ns = proj_off[a + 1] - proj_off[a];
-  TC acc[NL_MAXP][4];
+  const int lt = (threadIdx.x & (TL - 1)) * 4;
+  const int l0 = blockIdx.y * TILE + lt;
+  // lanes past the block read its first ones; they are not stored
+  const int nv0 = min(4, nlanes - l0);
+  const int lc = nv0 > 0 ? l0 : 0, nv = nv0 > 0 ? nv0 : min(4, nlanes);
+  for (int i = threadIdx.x; i < nn; i += 64 * NW) snode[i] = nodes[n0 + i];
+  __syncthreads();
+  TC acc[PMAX][4];
 #pragma unroll
-  for (int s = 0; s < NL_MAXP; ++s)
+  for (int s = 0; s < PMAX; ++s)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[s][j] = 0;
-  constexpr int C = CPLX ? 2 : 1;
-#pragma unroll 2
-  for (int n = n0 + wv; n < n1; n += 4) {
-    const int64_t g = nodes[n];
-    TC x[4];
-    if (nv > 0) Quad<TS, TC, VEC>::ld(X, g * ldx + l0, nv, x);
-    else x[0] = x[1] = x[2] = x[3] = 0;
-    if (dinv) {
-      const TC d = (TC)dinv[g];
+  const int g = wv * GW + (GW > 1 ? (int)((threadIdx.x & 63) / TL) : 0);
+  // U rows of this group; TAIL: a group past its last node reads the chunk's
+  // last row and takes it as zero, so the trip count is the block's
+  auto rows = [&](int i0, auto tail_tag) {
+    constexpr bool TAIL = decltype(tail_tag)::value;
+    TC x[U][4];
+    int idx[U];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) x[j] *= d;
+    for (int u = 0; u < U; ++u) {
+      idx[u] = i0 + u * G + g;
+      if constexpr (TAIL) idx[u] = min(idx[u], nn - 1);
+      int node = snode[idx[u]];
+      if constexpr (GW == 1) node = __builtin_amdgcn_readfirstlane(node);
+      quad_ld_clamped<TS, TC, VEC>(X, (int64_t)node * ldx + lc, nv, x[u]);
+      if (dinv) {
+        const TC d = (TC)dinv[node];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[u][j] *= d;
+      }
+      if constexpr (TAIL)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[u][j] = i0 + u * G + g < nn ? x[u][j] : (TC)0;
     }
-    const TC *f = F + (int64_t)n * fstride * C;
 #pragma unroll
-    for (int s = 0; s < NL_MAXP; ++s)
-      if (s < ns) nl_conj_fma<CPLX>(f[s * C], CPLX ? f[s * C + 1] : (TC)0, x, acc[s]);
-  }
-  // fixed-order sum of the four waves, one projector at a time
+    for (int u = 0; u < U; ++u) {
+      const TC *f = F + (int64_t)(n0 + idx[u]) * fstride * C;
 #pragma unroll
-  for (int s = 0; s < NL_MAXP; ++s) {
-    if (s < ns) {
+      for (int s = 0; s < PMAX; ++s)
+        if (s < ns) nl_conj_fma<CPLX>(f[s * C], CPLX ? f[s * C + 1] : (TC)0, x[u], acc[s]);
+    }
+  };
+  int i0 = 0;
+  for (; i0 + U * G <= nn; i0 += U * G) rows(i0, std::false_type{});
+  if (i0 < nn) rows(i0, std::true_type{});
+  // fixed-order sums, SB projectors at a time
 #pragma unroll
-      for (int j = 0; j < 4; ++j) red[wv][(threadIdx.x & 63) * 4 + j] = acc[s][j];
+  for (int s0 = 0; s0 < PMAX; s0 += SB) {
+    if (s0 < ns) {
+#pragma unroll
+      for (int s = s0; s < s0 + SB; ++s) {
+#pragma unroll
+        for (int o = TL; o < 64; o <<= 1)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[s][j] += __shfl_xor(acc[s][j], o);
+        if ((threadIdx.x & 63) < TL)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) red[s - s0][wv][lt + j] = acc[s][j];
+      }
       __syncthreads();
-      const int l = threadIdx.x;                 // one lane of the tile per thread
-      const TC sum = ((red[0][l] + red[1][l]) + red[2][l]) + red[3][l];
-      const int glo = blockIdx.y * NL_TILE + l;
-      if (glo < nlanes) part[((int64_t)ch * NL_MAXP + s) * ldp + glo] = sum;
-      __syncthreads();
+      for (int e = threadIdx.x; e < SB * TILE; e += 64 * NW) {
+        const int s = e / TILE, l = e % TILE;
+        TC sum = red[s][0][l];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += red[s][w][l];
+        const int glo = blockIdx.y * TILE + l;
+        if (glo < nlanes && s0 + s < ns) part[((int64_t)ch * NL_MAXP + s0 + s) * ldp + glo] = sum;
+      }
+      if (SB < PMAX) __syncthreads();
     }
   }
 }
@@ -216,8 +280,16 @@ __global__ void k_nl_wsum(const TC *__restrict__ part, int64_t ldp, const int *_
   const int s = (int)(t / nlanes), l = (int)(t % nlanes);
   const int a = proj_atom[s];
   const int sl = s - proj_off[a];
+  // in chunk order, eight loads in flight
+  const int c1 = atom_chunk0[a + 1];
   TC sum = 0;
-  for (int ch = atom_chunk0[a]; ch < atom_chunk0[a + 1]; ++ch) sum += part[((int64_t)ch * NL_MAXP + sl) * ldp + l];
+  for (int c0 = atom_chunk0[a]; c0 < c1; c0 += 8) {
+    TC v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = part[((int64_t)min(c0 + u, c1 - 1) * NL_MAXP + sl) * ldp + l];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) sum += c0 + u < c1 ? v[u] : (TC)0;
+  }
   W[(int64_t)s * ldw + l] = (TC)h[s] * sum;
 }
 
@@ -485,14 +557,41 @@ k_nl_ybm(double *__restrict__ Y, int64_t ldy, int nlanes, int nbrick, const int 
 }
 
 namespace {
+template <bool CPLX, typename TS, typename TC, bool VEC, int PMAX, int TL, int NW>
+void launch_nl_w_as(Mesh *m, const TS *X, int64_t ldx, int nlanes, const double *dinv, const TC *F, TC *part,
+                    int64_t ldp, hipStream_t s) {
+  const int tiles = (nlanes + 4 * TL - 1) / (4 * TL);
+  const unsigned gx = (unsigned)(m->nl_nchunks + 7) / 8 * 8;   // a multiple of the 8 XCDs
+  hipLaunchKernelGGL((k_nl_w<CPLX, TS, TC, VEC, PMAX, TL, NW>), dim3(gx, tiles), dim3(64 * NW), 0, s, X, ldx,
+                     nlanes, dinv, (const int4 *)m->nl_chunks, m->nl_nchunks, m->nl_atom_nodes, F, m->nl_maxproj, part, ldp);
+}
+
+// The narrowest row group that holds the lanes: 32 lanes on eight threads move
+// eight rows per wave access where one row per access left 56 of 64 threads
+// idle (18-chunk FP64 system of 31,500 DoFs x 32 lanes: 190 -> 17 us; eight
+// complex atoms, 74,088 DoFs x 48 lanes: 213 -> 35 us).  Sixteen waves per
+// chunk where the chunks do not fill the device: about 130 chunks x 128 FP64
+// lanes 217 -> 79 us, 270 chunks x 192 FP32 lanes 333 -> 286 us (beside the
+// local launches); with 940 chunks x 256 FP64 lanes the device is full and
+// four waves are the faster (392 us; sixteen waves 11% slower), so the line
+// lies at two blocks per CU.
+template <bool CPLX, typename TS, typename TC, bool VEC, int PMAX>
+void launch_nl_w_tl(Mesh *m, const TS *X, int64_t ldx, int nlanes, const double *dinv, const TC *F, TC *part,
+                    int64_t ldp, hipStream_t s) {
+  constexpr int NB = PMAX <= 4 || sizeof(TC) == 4 ? 16 : 8;   // waves of a block whose accumulators fit its registers
+  if (nlanes <= 32) launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 8, NB>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
+  else if (nlanes <= 64) launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 16, NB>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
+  else if (nlanes <= 128) launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 32, NB>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
+  else if ((int64_t)m->nl_nchunks * ((nlanes + 255) / 256) < NL_W_FEW)
+    launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 64, NB>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
+  else launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 64, 4>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
+}
+
 template <bool CPLX, typename TS, typename TC, bool VEC>
 void launch_nl_w(Mesh *m, const TS *X, int64_t ldx, int nlanes, const double *dinv, const TC *F, TC *part,
                  int64_t ldp, TC *W, int64_t ldw, hipStream_t s) {
-  const int tiles = (nlanes + NL_TILE - 1) / NL_TILE;
-  const unsigned gx = (unsigned)(m->nl_nchunks + 7) / 8 * 8;   // a multiple of the 8 XCDs
-  hipLaunchKernelGGL((k_nl_w<CPLX, TS, TC, VEC>), dim3(gx, tiles), dim3(NL_THREADS), 0, s, X, ldx,
-                     nlanes, dinv, m->nl_chunk_order, m->nl_nchunks, m->nl_chunk_atom, m->nl_chunk_n0, m->nl_atom_nodes, m->nl_atom_off,
-                     m->nl_atom_proj, F, m->nl_maxproj, part, ldp);
+  if (m->nl_maxproj <= 4) launch_nl_w_tl<CPLX, TS, TC, VEC, 4>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
+  else launch_nl_w_tl<CPLX, TS, TC, VEC, NL_MAXP>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
   const int64_t nw = (int64_t)m->ns * nlanes;
   hipLaunchKernelGGL((k_nl_wsum<TC>), dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, s, part, ldp,
                      m->nl_atom_chunk0, m->nl_atom_proj, m->nl_proj_atom, m->nl_h, m->ns, nlanes, W, ldw);
