@@ -188,8 +188,8 @@ fe_status fe_apply_H(fe_mesh_t mesh, const void *X, int64_t ldx, void *Y,
  * same Y = H X with the same kernels, arguments, layout and errors as
  * fe_apply_H, but it calls no hipMalloc / hipFree / hipStreamCreate and no
  * allocating library routine.  The projector term's per-chunk partials and W
- * live in one static device array of FE_NOALLOC_SCRATCH_BYTES that the
- * library holds on every device it runs on until the process ends; a call
+ * live in FE_NOALLOC_SCRATCH_BYTES (followed by 16 MiB for the local operator's
+ * segment planes) of one static device array that the library holds on every device it runs on until the process ends; a call
  * whose projector workspace ((chunks x 10 + projectors) x ceil4(real lanes)
  * x 8 bytes) exceeds it returns FE_EINVAL.  The projector reduction runs on
  * 'stream' itself in every precision.  All calls on one device
@@ -289,7 +289,9 @@ fe_status fe_batch_apply(int32_t n, const fe_mesh_t *meshes, const void *const *
  * (fe_cheb_filter: H D^-1 R, D^-1 applied while gathering).  vt is the vector tile in real lanes per workgroup:
  * {2, 4, 8, 16} for FE_F64, plus 10 where n_q = n_p (2 only where 4 does not
  * fit the LDS), {8, 16, 32} for FE_F32 / FE_BF16 (the matrix-core BF16 kernel
- * runs 8 as 16); 0 restores the built-in default.  fe_set_tile refuses
+ * runs 8 as 16); 0 restores the built-in default.  FE_F64 with n_q = n_p on
+ * cells with a diagonal metric runs one wave per tile, whose width the number
+ * of points sets: a tile is kept there and has no effect.  fe_set_tile refuses
  * (FE_EINVAL) a tile whose local-operator block does not fit the LDS on this
  * mesh (16 FP64 lanes at n_p = 8, two lanes wherever four fit, ...).
  * fe_autotune runs every

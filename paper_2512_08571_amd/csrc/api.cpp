@@ -44,7 +44,7 @@ void Mesh::dev_free_all() {
 
 fe_status ensure_workspace(Mesh *m, int slot, int64_t bytes) {
   if (m->ws_bytes[slot] >= bytes) return FE_OK;
-  const bool filter_slot = slot <= 4 || slot == 8 || slot == 9;   // the slots a filter pass uses
+  const bool filter_slot = slot <= 4 || slot == 8 || slot == 9 || slot == 11;   // the slots a filter pass uses
   if (m->ws[slot] && filter_slot && m->graphs > 0)
     return set_error(FE_ESTATE, "a captured filter graph holds this mesh's workspace; destroy it before a call that "
                                 "needs a larger one");
@@ -249,6 +249,73 @@ double chi_value(int l, int mm, const double r[3], double sigma, double rc) {
 
 }  // namespace
 
+// Coefficients of cell c for the plane kernels (layout at Mesh::pcoef64).
+void plane_coefficients(const Mesh *m, const double *vloc, const double *vgga, double *out) {
+  const int nq = m->nq, nq3 = nq * nq * nq;
+  double f[3][3];                    // c_s = sum_a f[s][a] V^G_a
+  for (int s = 0; s < 3; ++s)
+    for (int a = 0; a < 3; ++a) f[s][a] = m->Jinv[s][a] / std::sqrt(m->gdiag[s]);
+  for (int z = 0; z < nq; ++z)
+    for (int y = 0; y < nq; ++y)
+      for (int x = 0; x < nq; ++x) {
+        const int Q = (z * nq + y) * nq + x;
+        double c[3] = {0.0, 0.0, 0.0};
+        if (vgga)
+          for (int s = 0; s < 3; ++s)
+            for (int a = 0; a < 3; ++a) c[s] += f[s][a] * vgga[3 * Q + a];
+        double *zv = out + 2 * ((x * nq + y) * nq + z);
+        zv[0] = (vloc ? vloc[Q] : 0.0) + m->k2half;
+        zv[1] = c[2];
+        out[2 * nq3 + (y * nq + z) * nq + x] = c[0];
+        out[3 * nq3 + (x * nq + z) * nq + y] = c[1];
+      }
+}
+
+// Tables of the plane kernels (PlaneTab).  The point weight w_a w_b w_c det J
+// and D^-1 (assembled GLL weights: 2 w_0 at the cell ends, which two cells
+// share) are products of 1D factors on affine cells; each axis takes the cube
+// root of det J.
+std::vector<double> plane_tables(const Mesh *m) {
+  const int np = m->np, nq = m->nq;
+  const PlaneTab L = plane_tab(np, nq);
+  std::vector<double> tab(L.total), A;
+  const std::vector<double> &N = m->t1.N, &Dt = m->t1.Dt, &w = m->t1.wq;
+  const double dj = std::cbrt(m->detJ);
+  auto put = [&](int off, const std::vector<double> &A, int nout, int nin, int sym) {
+    const std::vector<double> v = eo_pack(A, nout, nin, sym);
+    std::copy(v.begin(), v.end(), tab.begin() + off);
+    int e = off + (int)v.size();
+    for (int q = 0; q < (nout + 1) / 2; ++q)
+      for (int c = 0; c < nin; ++c)
+        if (c != 0 && c != (nin + 1) / 2) tab[e++] = v[q * nin + c];
+  };
+  put(L.n, N, nq, np, +1);
+  A.assign((size_t)nq * np, 0.0);
+  for (int q = 0; q < nq; ++q)
+    for (int i = 0; i < np; ++i) A[q * np + i] = N[q * np + i] / (m->t1.gllw[i] * (i == 0 || i == np - 1 ? 2.0 : 1.0) * dj);
+  put(L.nd, A, nq, np, +1);
+  A.assign((size_t)np * nq, 0.0);
+  for (int i = 0; i < np; ++i)
+    for (int q = 0; q < nq; ++q) A[i * nq + q] = N[q * np + i] * w[q] * dj;
+  put(L.nt, A, np, nq, +1);
+  for (int d = 0; d < 3; ++d) {
+    const double g = std::sqrt(m->gdiag[d]);
+    std::vector<double> D((size_t)nq * nq), H((size_t)nq * nq), K((size_t)nq * nq, 0.0);
+    for (int q = 0; q < nq; ++q)
+      for (int r = 0; r < nq; ++r) {
+        D[q * nq + r] = g * Dt[q * nq + r];
+        H[q * nq + r] = g * Dt[r * nq + q] * w[r] / w[q];
+      }
+    for (int q = 0; q < nq; ++q)
+      for (int s = 0; s < nq; ++s)
+        for (int r = 0; r < nq; ++r) K[q * nq + r] += H[q * nq + s] * D[s * nq + r];
+    put(L.d + d * L.dsz, D, nq, nq, -1);
+    put(L.dh + d * L.dsz, H, nq, nq, -1);
+    put(L.k + d * L.dsz, K, nq, nq, +1);
+  }
+  return tab;
+}
+
 // Every device array that depends on the cell geometry: the mass-operator
 // coefficients (one shared block, or one per cell on the general-metric
 // path), the lumped mass D and its inverse, and the operator coefficients of
@@ -257,7 +324,8 @@ fe_status build_geometry(Mesh *m) {
   const int np = m->np, nq = m->nq, nq3 = nq * nq * nq;
   m->ncoef = m->offd ? NCOEF_GEN : 4;
   release(m, m->coefM64); release(m, m->coefM32); release(m, m->dmass); release(m, m->dinv);
-  release(m, m->coef64); release(m, m->coef32);
+  release(m, m->coef64); release(m, m->coef32); release(m, m->ptab64); release(m, m->ptab32);
+  release(m, m->pcoef64); release(m, m->pcoef32);
   fe_status st;
   // the consistent mass: w_Q det J(xi_Q) in block 0, the other blocks zero
   const int64_t ncm = m->distorted ? m->E : 1;
@@ -300,6 +368,16 @@ fe_status build_geometry(Mesh *m) {
   for (int64_t c = 0; c < m->E; ++c) cell_coefficients(m, c, nullptr, nullptr, &coef[(size_t)c * m->ncoef * nq3]);
   if ((st = upload(m, &m->coef64, coef))) return st;
   if ((st = upload(m, &m->coef32, to_f32(coef)))) return st;
+  if (!m->offd) {
+    const std::vector<double> ptab = plane_tables(m);
+    if ((st = upload(m, &m->ptab64, ptab))) return st;
+    if ((st = upload(m, &m->ptab32, to_f32(ptab)))) return st;
+    for (int d = 0; d < 3; ++d) m->pkap[d] = m->kap[d] / std::sqrt(m->gdiag[d]);
+    std::vector<double> pc((size_t)m->E * 4 * nq3);
+    for (int64_t c = 0; c < m->E; ++c) plane_coefficients(m, nullptr, nullptr, &pc[(size_t)c * 4 * nq3]);
+    if ((st = upload(m, &m->pcoef64, pc))) return st;
+    if ((st = upload(m, &m->pcoef32, to_f32(pc)))) return st;
+  }
   m->has_gga = false;
   return FE_OK;
 }
@@ -476,6 +554,7 @@ fe_status fe_mesh_destroy(fe_mesh_t mesh) {
     hipDeviceSynchronize();
     if (mesh->ev_fork) hipEventDestroy(mesh->ev_fork);
     if (mesh->ev_join) hipEventDestroy(mesh->ev_join);
+    if (mesh->side_ev) hipEventDestroy(mesh->side_ev);
     if (mesh->side) hipStreamDestroy(mesh->side);
     mesh->dev_free_all();
   }
@@ -583,6 +662,14 @@ fe_status fe_set_potential(fe_mesh_t m, const double *vloc, const double *vgga) 
   FE_HIP_TRY(hipMemcpy(m->coef64, coef.data(), coef.size() * sizeof(double), hipMemcpyHostToDevice));
   std::vector<float> c32 = to_f32(coef);
   FE_HIP_TRY(hipMemcpy(m->coef32, c32.data(), c32.size() * sizeof(float), hipMemcpyHostToDevice));
+  if (!m->offd) {
+    std::vector<double> pc((size_t)m->E * 4 * nq3);
+    for (int64_t c = 0; c < m->E; ++c)
+      plane_coefficients(m, vloc + c * nq3, vgga ? vgga + 3 * c * nq3 : nullptr, &pc[(size_t)c * 4 * nq3]);
+    FE_HIP_TRY(hipMemcpy(m->pcoef64, pc.data(), pc.size() * sizeof(double), hipMemcpyHostToDevice));
+    c32 = to_f32(pc);
+    FE_HIP_TRY(hipMemcpy(m->pcoef32, c32.data(), c32.size() * sizeof(float), hipMemcpyHostToDevice));
+  }
   m->has_gga = vgga != nullptr;
   return FE_OK;
 }

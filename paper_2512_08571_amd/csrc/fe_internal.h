@@ -75,6 +75,30 @@ inline TabLayout tab_layout(int np, int nq) {
   return t;
 }
 
+// Tables of the plane kernels (k_local_planes.h), as offsets in elements: n (N),
+// nd (N with D^-1's 1D factor), nt ((N W)^T), per direction d (sqrt(g_d) Dtilde),
+// dh (sqrt(g_d) W^-1 Dtilde^T W) and k (dh d), each of dsz.  A table is the
+// even-odd packed matrix (eo_pack) followed by a copy of its entries past the
+// first column of E and of O, row by row, padded to a multiple of 16.
+struct PlaneTab {
+  int n, nd, nt, d, dh, k, dsz, total;
+};
+constexpr int plane_bcast(int nin, int nout) { return ((nout + 1) / 2 * (nin - 2) + 15) / 16 * 16; }
+constexpr int plane_tab1(int nin, int nout) { return (nout + 1) / 2 * nin + plane_bcast(nin, nout); }
+constexpr PlaneTab plane_tab(int np, int nq) {
+  PlaneTab t{};
+  const int ns = plane_tab1(np, nq), ts = plane_tab1(nq, np);
+  t.dsz = plane_tab1(nq, nq);
+  t.n = 0;
+  t.nd = ns;
+  t.nt = 2 * ns;
+  t.d = t.nt + ts;
+  t.dh = t.d + 3 * t.dsz;
+  t.k = t.dh + 3 * t.dsz;
+  t.total = t.k + 3 * t.dsz;
+  return t;
+}
+
 // ---- local-operator launch description --------------------------------------
 struct LocalLaunch {
   const void *X = nullptr;
@@ -85,10 +109,20 @@ struct LocalLaunch {
   const double *dinv_gather = nullptr;  // scale gathered X by D^-1 (filter)
   bool mass = false;          // the consistent mass operator M instead of H
   int vt = 0, nt = 0;         // vector tile / threads (0: tuned default)
+  void *side = nullptr;       // PLANE_SIDE_BYTES the caller provides (null: the mesh's own)
   bool store32 = false;       // FE_BF16 arithmetic on FP32 blocks (the filter's recurrence state)
 };
 
 struct Mesh;
+// Segments a column of cells is cut into by the plane kernels with tiles of vt
+// lanes, and the block for their first planes (see plane_segments)
+constexpr int64_t PLANE_SIDE_BYTES = 16LL << 20;
+int plane_segment_count(const Mesh *m, int nlanes, int64_t ldy, int vt, int elem_bytes);
+int plane_segments(Mesh *m, const LocalLaunch &L, int vt, int elem_bytes, hipStream_t s, void **side, bool *shared);
+int64_t plane_side_need(const Mesh *m, int nlanes, int64_t ldy, int prec);
+fe_status plane_side_enter(Mesh *m, hipStream_t s);
+fe_status plane_side_leave(Mesh *m, hipStream_t s);
+
 // Several local-operator applications of one class (degree, quadrature,
 // real/complex, precision, vector tile) launched together.
 struct LocalBatch {
@@ -132,6 +166,8 @@ struct FilterPlan {
   std::vector<double> alpha, s2;   // per step k = 2..degree: 2 sigma2 / e, sigma sigma2
   double *Y = nullptr, *tab = nullptr;
   void *RY = nullptr, *RX = nullptr, *Ylp = nullptr, *T = nullptr;
+  void *side = nullptr;            // captured passes: the mesh's segment planes (LocalLaunch::side)
+  int64_t side_need = 0;           // their bytes
   int k = 2;                       // next recurrence step
 };
 fe_status filter_setup(FilterPlan &P, Mesh *m, double *X, int64_t ldx_lanes, const double *lam, int64_t nvec,
@@ -177,6 +213,13 @@ struct Mesh {
   int mass_kind = 0;                    // filter / Rayleigh-Ritz mass: 0 lumped D, 1 consistent M
   double *coef64 = nullptr;   // [E][4][nq^3]: (V + |k|^2/2) w detJ, then Vtilde_s w detJ
   float *coef32 = nullptr;
+  // plane kernels (affine cells with a diagonal metric): tables (PlaneTab),
+  // unweighted coefficients [E][4][nq^3] and Bloch factors kappa_d / sqrt(g_d).
+  // Per cell, (x, y, z) the point: {V + |k|^2/2, c_2} pairs at [x][y][z], c_0 at
+  // [y][z][x], c_1 at [x][z][y] (each stage's line contiguous), c_d = Vtilde^G_d / sqrt(g_d)
+  double *ptab64 = nullptr, *pcoef64 = nullptr;
+  float *ptab32 = nullptr, *pcoef32 = nullptr;
+  double pkap[3]{};
   bool has_gga = false;
   double *dmass = nullptr, *dinv = nullptr;   // lumped mass and its inverse [m]
   std::vector<double> h_dmass;
@@ -243,9 +286,13 @@ struct Mesh {
   // FP32 / BF16 filter: no slots 0 and 8; slot 2 holds R_X and, at
   // filter_t_offset, H D^-1 R_Y, and the FP64 Y (read only by the prologue)
   // spans both (slot 2 padded to 8 bytes per element where they are smaller).
-  static constexpr int NWS = 11;
+  // 11 the plane kernels' segment planes.
+  static constexpr int NWS = 12;
   void *ws[NWS] = {};
   int64_t ws_bytes[NWS] = {};
+  hipStream_t side_stream = nullptr;   // slot 11: the stream of its last use, and the event after it once a
+  hipEvent_t side_ev = nullptr;        // second stream has used it (plane_side_enter)
+  bool side_used = false;
 
   int64_t footprint = 0;
   std::vector<std::pair<void *, size_t>> owned;

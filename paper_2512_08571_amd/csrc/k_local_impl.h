@@ -149,6 +149,12 @@ template <typename TC> struct KArgs {
   const double *dinv;
   const float *mxtab;  // full 1D matrices [4][8][8] (N, N^T, Dtilde, Dtilde^T) for the MFMA path
   int ncoef;           // coefficient blocks per cell (4, or NCOEF_GEN with the per-point metric)
+  const TC *ptab;      // plane kernels: tables (PlaneTab), the gather's N table, coefficients, Bloch factors
+  const TC *pgather;
+  const TC *pcoef;
+  TC pkap[3];
+  int nseg;            // plane kernels: segments a column is cut into, and the block of their first planes
+  void *side;
 };
 
 // ---- even-odd application of a packed centro-(anti)symmetric 1D matrix ----------
@@ -1015,6 +1021,12 @@ template <typename TC> KArgs<TC> make_args(Mesh *m, const LocalLaunch &L, int vt
     a.coef_cell = m->coefM_cell;
     a.gga = 0;
   }
+  a.ptab = f64 ? (const TC *)m->ptab64 : (const TC *)m->ptab32;
+  const PlaneTab pt = plane_tab(m->np, m->nq);
+  a.pgather = a.ptab + (L.dinv_gather ? pt.nd : pt.n);
+  a.pcoef = f64 ? (const TC *)m->pcoef64 : (const TC *)m->pcoef32;
+  for (int d = 0; d < 3; ++d) a.pkap[d] = (TC)m->pkap[d];
+  a.nseg = 1;
   a.dinv = L.dinv_gather;
   a.mxtab = m->tabmx;
   a.ntiles = (L.nlanes + vt - 1) / vt;

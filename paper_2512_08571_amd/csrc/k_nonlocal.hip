@@ -568,7 +568,7 @@ void launch_nl_w_as(Mesh *m, const TS *X, int64_t ldx, int nlanes, const double 
 
 // The narrowest row group that holds the lanes: 32 lanes on eight threads move
 // eight rows per wave access where one row per access left 56 of 64 threads
-// idle (18-chunk FP64 system of 31,500 DoFs x 32 lanes: 190 -> 17 us; eight
+// idle (FP64, 31,500 DoFs x 32 lanes: 190 -> 17 us; eight
 // complex atoms, 74,088 DoFs x 48 lanes: 213 -> 35 us).  Sixteen waves per
 // chunk where the chunks do not fill the device: about 130 chunks x 128 FP64
 // lanes 217 -> 79 us, 270 chunks x 192 FP32 lanes 333 -> 286 us (beside the
@@ -764,11 +764,11 @@ fe_status apply_with_nonlocal(Mesh *m, const LocalLaunch &L, int prec, const dou
 
 // ---- the application that allocates nothing ----------------------------------
 // Scratch for fe_apply_H_noalloc: the projector partials and W of one
-// application, in a file-scope device array (each device holds its own copy
+// application, then the local operator's segment planes, in a file-scope device array (each device holds its own copy
 // for the life of the process).  Host code never passes the array's name to a
 // kernel: its device address comes from hipGetSymbolAddress, once per device
 // with that device current, and only that address is used.
-static __device__ __align__(256) unsigned char scratch[FE_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[FE_NOALLOC_SCRATCH_BYTES + PLANE_SIDE_BYTES];
 
 namespace {
 constexpr int SCRATCH_MAXDEV = 64;
@@ -815,11 +815,12 @@ extern "C" fe_status fe_apply_H_noalloc(fe_mesh_t m, const void *X, int64_t ldx,
   if (hipSetDevice(m->device) != hipSuccess) return set_error(FE_EDEVICE, "hipSetDevice failed");
   void *ws = nullptr;
   fe_status st;
-  if (m->ns > 0 && (st = scratch_address(m->device, &ws))) return st;
+  if ((st = scratch_address(m->device, &ws))) return st;
   hipStream_t s = (hipStream_t)stream;
   LocalLaunch L;
   L.X = X; L.Y = Y; L.ldx = ldx * C; L.ldy = ldy * C; L.nlanes = nlanes; L.prec = prec;
   L.vt = m->vt_pref[prec][0];
+  L.side = (unsigned char *)ws + FE_NOALLOC_SCRATCH_BYTES;
   // projector reduction, local operator, projector update on the caller's
   // stream, as in fe_apply_H
   if ((st = dispatch_nl(m, X, L.ldx, nullptr, 0, nlanes, prec, nullptr, 0.0, 1, s, ws))) return st;

@@ -22,6 +22,7 @@
 #include <rocblas/rocblas.h>
 #include <rocsolver/rocsolver.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -298,6 +299,9 @@ fe_status filter_setup(FilterPlan &P, Mesh *m, double *X, int64_t ldx_l, const d
   if (m->mass_kind == FE_MASS_CONSISTENT && (st = ensure_workspace(m, 9, n * (int64_t)sizeof(double))))
     return st;                                                                  // M X (FP64)
   if ((st = ensure_nl_workspace(m, P.lanes))) return st;
+  // the segment planes of the FP64 prologue and of the steps
+  P.side_need = std::max(plane_side_need(m, P.lanes, P.lanes, FE_F64), plane_side_need(m, P.lanes, P.lanes, prec));
+  if (m->graphs == 0 && (st = ensure_workspace(m, 11, P.side_need))) return st;
   P.Y = (double *)m->ws[share ? 2 : 0];
   P.RY = m->ws[1];
   P.RX = m->ws[2];
@@ -317,6 +321,7 @@ fe_status filter_prologue(FilterPlan &P, hipStream_t s) {
   LocalLaunch L0;
   L0.X = P.X; L0.Y = P.Y; L0.ldx = P.ldx; L0.ldy = P.lanes; L0.nlanes = P.lanes; L0.prec = FE_F64;
   L0.vt = m->vt_pref[FE_F64][0];
+  L0.side = P.side;
   fe_status st;
   if ((st = apply_with_nonlocal(m, L0, FE_F64, nullptr, 1.0, s))) return st;
   const double *MX = nullptr;
@@ -352,6 +357,7 @@ LocalLaunch filter_step_local(const FilterPlan &P) {
   L.X = P.RY; L.Y = P.T; L.ldx = P.lanes; L.ldy = P.lanes; L.nlanes = P.lanes; L.prec = P.prec;
   L.store32 = P.prec == FE_BF16;
   L.dinv_gather = P.m->dinv;
+  L.side = P.side;
   L.vt = P.m->vt_pref[P.prec][1];
   return L;
 }
@@ -726,6 +732,7 @@ fe_status fe_filter_graph_create(fe_mesh_t m, void *X, int64_t ldx, const double
     delete G;
     return set_error(FE_EDEVICE, "hipStreamBeginCapture failed");
   }
+  if (m->ws_bytes[11] >= G->P.side_need) G->P.side = m->ws[11];   // else one segment
   FilterPlan P = G->P;   // enqueueing advances the step and swaps the blocks
   st = filter_enqueue(P, cs);
   hipGraph_t g = nullptr;
@@ -749,8 +756,10 @@ fe_status fe_filter_graph_create(fe_mesh_t m, void *X, int64_t ldx, const double
 fe_status fe_filter_graph_launch(fe_filter_graph_t G, void *stream) {
   if (!G || !G->ex) return set_error(FE_EINVAL, "NULL graph");
   if (hipSetDevice(G->P.m->device) != hipSuccess) return set_error(FE_EDEVICE, "hipSetDevice failed");
+  fe_status st;
+  if (G->P.side && (st = plane_side_enter(G->P.m, (hipStream_t)stream))) return st;
   FE_HIP_TRY(hipGraphLaunch(G->ex, (hipStream_t)stream));
-  return FE_OK;
+  return G->P.side ? plane_side_leave(G->P.m, (hipStream_t)stream) : (fe_status)FE_OK;
 }
 
 fe_status fe_filter_graph_destroy(fe_filter_graph_t G) {

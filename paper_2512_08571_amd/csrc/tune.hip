@@ -164,7 +164,8 @@ fe_status fe_autotune(fe_mesh_t m, int32_t prec, int32_t kind, int64_t nvec, int
     L.store32 = store32;
     if (kind == 1) L.dinv_gather = m->dinv;   // a filter step: D^-1 applied at the gather
     float ms = INFINITY;
-    fe_status st = launch_local(m, L, s);   // warm-up; a tile whose LDS does not fit is skipped
+    // warm-up; a tile that fe_set_tile refuses on this mesh is skipped
+    fe_status st = tile_fits(m, prec, cand[i]) ? launch_local(m, L, s) : (fe_status)FE_EUNSUPPORTED;
     if (st == FE_OK) {
       FE_HIP_TRY(hipEventRecord(e0, s));
       for (int r = 0; r < reps && st == FE_OK; ++r) st = launch_local(m, L, s);
