@@ -289,22 +289,25 @@ std::vector<double> plane_tables(const Mesh *m) {
       for (int c = 0; c < nin; ++c)
         if (c != 0 && c != (nin + 1) / 2) tab[e++] = v[q * nin + c];
   };
-  put(L.n, N, nq, np, +1);
+  std::vector<double> Nh((size_t)nq * np);
+  for (int q = 0; q < nq; ++q)
+    for (int i = 0; i < np; ++i) Nh[q * np + i] = N[q * np + i] * std::sqrt(w[q] * dj);
+  put(L.n, Nh, nq, np, +1);
   A.assign((size_t)nq * np, 0.0);
   for (int q = 0; q < nq; ++q)
-    for (int i = 0; i < np; ++i) A[q * np + i] = N[q * np + i] / (m->t1.gllw[i] * (i == 0 || i == np - 1 ? 2.0 : 1.0) * dj);
+    for (int i = 0; i < np; ++i) A[q * np + i] = Nh[q * np + i] / (m->t1.gllw[i] * (i == 0 || i == np - 1 ? 2.0 : 1.0) * dj);
   put(L.nd, A, nq, np, +1);
   A.assign((size_t)np * nq, 0.0);
   for (int i = 0; i < np; ++i)
-    for (int q = 0; q < nq; ++q) A[i * nq + q] = N[q * np + i] * w[q] * dj;
+    for (int q = 0; q < nq; ++q) A[i * nq + q] = Nh[q * np + i];
   put(L.nt, A, np, nq, +1);
   for (int d = 0; d < 3; ++d) {
     const double g = std::sqrt(m->gdiag[d]);
     std::vector<double> D((size_t)nq * nq), H((size_t)nq * nq), K((size_t)nq * nq, 0.0);
     for (int q = 0; q < nq; ++q)
       for (int r = 0; r < nq; ++r) {
-        D[q * nq + r] = g * Dt[q * nq + r];
-        H[q * nq + r] = g * Dt[r * nq + q] * w[r] / w[q];
+        D[q * nq + r] = g * Dt[q * nq + r] * std::sqrt(w[q] / w[r]);
+        H[r * nq + q] = D[q * nq + r];
       }
     for (int q = 0; q < nq; ++q)
       for (int s = 0; s < nq; ++s)
@@ -494,20 +497,6 @@ fe_status fe_mesh_create(const fe_mesh_desc *desc, fe_mesh_t *out) {
       for (int a2 = 0; a2 < nq; ++a2) wq[b * nq + a2] = m->t1.wq[a2] * m->t1.wq[b];
     if ((st = upload(m, &m->tab64, tab))) throw std::runtime_error("upload");
     if ((st = upload(m, &m->tab32, to_f32(tab)))) throw std::runtime_error("upload");
-    // the four 1D matrices in full, zero padded to 8 x 8, rows = outputs:
-    // N [q][i], N^T [i][q], Dtilde [q][r], Dtilde^T [r][q]
-    std::vector<float> mx(4 * 64, 0.0f);
-    for (int q = 0; q < nq && q < 8; ++q)
-      for (int i = 0; i < np && i < 8; ++i) {
-        mx[0 * 64 + q * 8 + i] = (float)m->t1.N[q * np + i];
-        mx[1 * 64 + i * 8 + q] = (float)m->t1.N[q * np + i];
-      }
-    for (int q = 0; q < nq && q < 8; ++q)
-      for (int r = 0; r < nq && r < 8; ++r) {
-        mx[2 * 64 + q * 8 + r] = (float)m->t1.Dt[q * nq + r];
-        mx[3 * 64 + r * 8 + q] = (float)m->t1.Dt[q * nq + r];
-      }
-    if ((st = upload(m, &m->tabmx, mx))) throw std::runtime_error("upload");
     if ((st = upload(m, &m->wq64, wq))) throw std::runtime_error("upload");
     if ((st = upload(m, &m->wq32, to_f32(wq)))) throw std::runtime_error("upload");
     // the consistent mass M = sum_e N3^T (w det J) N3: the same tables with the

@@ -75,9 +75,10 @@ inline TabLayout tab_layout(int np, int nq) {
   return t;
 }
 
-// Tables of the plane kernels (k_local_planes.h), as offsets in elements: n (N),
-// nd (N with D^-1's 1D factor), nt ((N W)^T), per direction d (sqrt(g_d) Dtilde),
-// dh (sqrt(g_d) W^-1 Dtilde^T W) and k (dh d), each of dsz.  A table is the
+// Tables of the plane kernels (k_local_planes.h), as offsets in elements: n
+// (W^1/2 N, W the 1D weights and the Jacobian's cube root), nd (that with D^-1's
+// 1D factor), nt (n^T), per direction d (sqrt(g_d) W^1/2 Dtilde W^-1/2), dh (d^T)
+// and k (dh d), each of dsz.  A table is the
 // even-odd packed matrix (eo_pack) followed by a copy of its entries past the
 // first column of E and of O, row by row, padded to a multiple of 16.
 struct PlaneTab {
@@ -109,16 +110,31 @@ struct LocalLaunch {
   const double *dinv_gather = nullptr;  // scale gathered X by D^-1 (filter)
   bool mass = false;          // the consistent mass operator M instead of H
   int vt = 0, nt = 0;         // vector tile / threads (0: tuned default)
-  void *side = nullptr;       // PLANE_SIDE_BYTES the caller provides (null: the mesh's own)
+  void *side = nullptr;       // segment planes the caller provides (null: the mesh's own)
+  int64_t side_bytes = 0;
   bool store32 = false;       // FE_BF16 arithmetic on FP32 blocks (the filter's recurrence state)
 };
 
 struct Mesh;
-// Segments a column of cells is cut into by the plane kernels with tiles of vt
-// lanes, and the block for their first planes (see plane_segments)
-constexpr int64_t PLANE_SIDE_BYTES = 16LL << 20;
-int plane_segment_count(const Mesh *m, int nlanes, int64_t ldy, int vt, int elem_bytes);
-int plane_segments(Mesh *m, const LocalLaunch &L, int vt, int elem_bytes, hipStream_t s, void **side, bool *shared);
+// Lanes of a plane kernel's wave with lpt lanes per thread: an even number of
+// threads per plane.
+constexpr int plane_vt(int nq, int lpt) { return ((64 / nq) & ~1) * lpt; }
+// Its waves per SIMD: as many as the registers of its plane and one direction's
+// stage allow (512 per lane of a SIMD: 93, 135, 168, 207, 256, 302, 382 for FP64
+// and 3..9 points, 77 to 339 for two FP32 lanes, 54 to 202 for one), and the LDS
+// (two FP32 lanes at eight points: 37 KB each).
+constexpr int plane_waves(int nq, bool f64, int lpt) {
+  constexpr int w[3][7] = {{5, 3, 3, 2, 2, 1, 1}, {6, 4, 3, 2, 2, 1, 1}, {8, 6, 5, 4, 3, 2, 2}};
+  return w[f64 ? 0 : lpt == 2 ? 1 : 2][nq - 3];
+}
+// Segments a column of cells is cut into by the plane kernels, and the block for their first planes (see plane_segments)
+constexpr int64_t PLANE_SIDE_BYTES = 16LL << 20;    // beside the static scratch
+constexpr int64_t PLANE_SIDE_MAX = 64LL << 20;      // of a mesh
+int plane_segment_count(const Mesh *m, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes, double *cost);
+int plane_segments(Mesh *m, const LocalLaunch &L, int lpt, int elem_bytes, hipStream_t s, void **side, bool *shared);
+struct LocalBatch;
+bool plane_pairs(const LocalBatch &B, size_t elem_bytes);
+bool plane_pairs_pay(const LocalBatch &B, size_t elem_bytes);
 int64_t plane_side_need(const Mesh *m, int nlanes, int64_t ldy, int prec);
 fe_status plane_side_enter(Mesh *m, hipStream_t s);
 fe_status plane_side_leave(Mesh *m, hipStream_t s);
@@ -202,7 +218,6 @@ struct Mesh {
   // device tables / coefficients (compute precision copies)
   double *tab64 = nullptr;
   float *tab32 = nullptr;
-  float *tabmx = nullptr;               // [4][8][8] full N, N^T, Dtilde, Dtilde^T (MFMA operands), zero padded
   double *wq64 = nullptr;               // [nq2] w_a w_b: the two 1D weights off a line
   float *wq32 = nullptr;
   // the consistent mass operator on the same kernel: tables without the

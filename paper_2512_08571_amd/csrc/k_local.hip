@@ -7,7 +7,7 @@
 
 namespace fehx {
 
-constexpr int PLANE_WAVES = 2048;
+constexpr int PLANE_SIMDS = 1024;   // four per CU, 256 CUs
 
 fe_status launch_local_f64(const LocalBatch &B, hipStream_t s);
 fe_status launch_local_f32(const LocalBatch &B, hipStream_t s);
@@ -15,33 +15,71 @@ fe_status launch_local_bf16(const LocalBatch &B, hipStream_t s);
 
 // A wave of the plane kernels walks its cells one after another, so a launch
 // with few columns and tiles leaves most of the device idle for the length of
-// a column.  Its columns are then cut into segments: enough for two waves per
-// SIMD of 256 CUs, at most one per cell, and at most PLANE_SIDE_BYTES for the
-// planes that two segments share (each segment's first plane goes to a side
-// block of planes laid out as Y's, added to Y after the last colour phase).
-int plane_segment_count(const Mesh *m, int nlanes, int64_t ldy, int vt, int elem_bytes) {
+// a column.  Its columns are then cut into segments (each segment's first
+// plane, shared with the one below, goes to a side block of planes laid out as
+// Y's, added to Y after the last colour phase).  The count is the one of least
+// cost: rounds of the device's waves times cells per wave.  A wave's first
+// gather and last plane cost about half a cell; a cell takes a wave about
+// 1 + 2 k with k waves on its SIMD (FP64, 7 points: 20 us alone, 34 us by twos).
+// The side block is at most side_bytes.
+int plane_segment_count(const Mesh *m, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes,
+                        double *cost) {
+  const int vt = plane_vt(m->nq, lpt), per = plane_waves(m->nq, f64, lpt);
   const int64_t waves = (int64_t)(m->phase_off[1] - m->phase_off[0]) * ((nlanes + vt - 1) / vt);
   const int64_t plane = (int64_t)m->Mn[0] * m->Mn[1] * ldy * elem_bytes;
-  int64_t n = (PLANE_WAVES + waves - 1) / waves;
-  n = std::min<int64_t>(n, m->N[2]);
-  n = std::min<int64_t>(n, PLANE_SIDE_BYTES / plane);
-  return (int)std::max<int64_t>(n, 1);
+  const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(m->N[2], side_bytes / plane));
+  auto round = [](int64_t k) { return k ? 1.0 + 2.0 * k : 0.0; };
+  int best = 1;
+  double least = 0;
+  for (int64_t n = 1; n <= cap; ++n) {
+    const int64_t per_simd = (waves * n + PLANE_SIMDS - 1) / PLANE_SIMDS;
+    const double c = ((double)(per_simd / per) * round(per) + round(per_simd % per)) * ((m->N[2] + n - 1) / n + 0.5);
+    if (n == 1 || c < least) { best = (int)n; least = c; }
+  }
+  if (cost) *cost = least;
+  return best;
 }
-
-int plane_vt(int nq, int lpt) { return ((64 / nq) & ~1) * lpt; }
 
 bool plane_mesh(const Mesh *m) { return !m->offd && m->nq == m->np; }
 
-// bytes of the side block of an application to a block of nlanes lanes with
-// leading dimension ldy (lanes), for either width of a thread
-int64_t plane_side_need(const Mesh *m, int nlanes, int64_t ldy, int prec) {
-  if (!plane_mesh(m) || prec != FE_F64) return 0;
-  const int es = 8;
-  int64_t need = 0;
-  for (int lpt = 1; lpt <= 1; ++lpt) {
-    const int n = plane_segment_count(m, nlanes, ldy, plane_vt(m->nq, lpt), es);
-    if (n > 1) need = std::max(need, (int64_t)n * m->Mn[0] * m->Mn[1] * ldy * es);
+// Whether every block of the launch can be read in pairs of lanes.
+bool plane_pairs(const LocalBatch &B, size_t elem_bytes) {
+  for (int i = 0; i < B.n; ++i) {
+    const LocalLaunch &L = B.Ls[i];
+    if ((L.ldx | L.ldy | L.nlanes) & 1) return false;
+    if (((uintptr_t)L.X | (uintptr_t)L.Y) % (2 * elem_bytes)) return false;
   }
+  return true;
+}
+
+// Whether threads of two lanes (a third faster per lane on a full device) beat
+// threads of one (0.55 of the time per cell, twice the waves) for real blocks.
+bool plane_pairs_pay(const LocalBatch &B, size_t elem_bytes) {
+  double one = 0, two = 0;
+  for (int i = 0; i < B.n; ++i) {
+    const LocalLaunch &L = B.Ls[i];
+    const int64_t side = L.side ? L.side_bytes : PLANE_SIDE_MAX;
+    double c1, c2;
+    plane_segment_count(B.ms[i], L.nlanes, L.ldy, false, 1, (int)elem_bytes, side, &c1);
+    plane_segment_count(B.ms[i], L.nlanes, L.ldy, false, 2, (int)elem_bytes, side, &c2);
+    one += 0.55 * c1;
+    two += c2;
+  }
+  return two <= one;
+}
+
+// bytes of the side block of an application to a block of nlanes lanes with
+// leading dimension ldy (lanes), for either width of a thread, and for FE_BF16
+// with either block type
+int64_t plane_side_need(const Mesh *m, int nlanes, int64_t ldy, int prec) {
+  if (!plane_mesh(m)) return 0;
+  const bool f64 = prec == FE_F64;
+  int64_t need = 0;
+  for (int lpt = 1; lpt <= (f64 ? 1 : 2); ++lpt)
+    for (int es = prec == FE_BF16 ? 2 : f64 ? 8 : 4; es <= (f64 ? 8 : 4); es *= 2) {
+      const int n = plane_segment_count(m, nlanes, ldy, f64, lpt, es, PLANE_SIDE_MAX, nullptr);
+      if (n > 1) need = std::max(need, (int64_t)n * m->Mn[0] * m->Mn[1] * ldy * es);
+    }
   return need;
 }
 
@@ -71,8 +109,8 @@ fe_status plane_side_leave(Mesh *m, hipStream_t s) {
 // (then *shared: enter and leave around the use).  A block that cannot be had
 // now (the stream is capturing, a captured graph holds the mesh's smaller one,
 // no memory) means one segment.
-int plane_segments(Mesh *m, const LocalLaunch &L, int vt, int elem_bytes, hipStream_t s, void **side, bool *shared) {
-  const int n = plane_segment_count(m, L.nlanes, L.ldy, vt, elem_bytes);
+int plane_segments(Mesh *m, const LocalLaunch &L, int lpt, int elem_bytes, hipStream_t s, void **side, bool *shared) {
+  const int n = plane_segment_count(m, L.nlanes, L.ldy, L.prec == FE_F64, lpt, elem_bytes, L.side ? L.side_bytes : PLANE_SIDE_MAX, nullptr);
   *side = L.side;
   *shared = false;
   if (n == 1 || L.side) return n;

@@ -147,7 +147,6 @@ template <typename TC> struct KArgs {
   int64_t coef_cell;   // coefficient elements per cell (0: one block for all cells)
   int gga;
   const double *dinv;
-  const float *mxtab;  // full 1D matrices [4][8][8] (N, N^T, Dtilde, Dtilde^T) for the MFMA path
   int ncoef;           // coefficient blocks per cell (4, or NCOEF_GEN with the per-point metric)
   const TC *ptab;      // plane kernels: tables (PlaneTab), the gather's N table, coefficients, Bloch factors
   const TC *pgather;
@@ -1028,7 +1027,6 @@ template <typename TC> KArgs<TC> make_args(Mesh *m, const LocalLaunch &L, int vt
   for (int d = 0; d < 3; ++d) a.pkap[d] = (TC)m->pkap[d];
   a.nseg = 1;
   a.dinv = L.dinv_gather;
-  a.mxtab = m->tabmx;
   a.ntiles = (L.nlanes + vt - 1) / vt;
   return a;
 }

@@ -18,14 +18,15 @@
 // the A -> B exchange, then u's return, then parks the partial sum, then the
 // C -> D exchange.
 //
-// The weights of eqn refact are folded into the 1D tables: with T_d = D_d u,
-// D_d = sqrt(g_d) Dtilde, Dh_d = sqrt(g_d) W^-1 Dtilde^T W and
-// c_d = Vtilde^G_d / sqrt(g_d),
-//   r = V u + sum_d [c_d T_d + Dh_d (T_d + c_d u) - i kappa_d / sqrt(g_d) T_d],
-//   Y^(e) = (N W)^T x 3 r,
-// which is eqn refact divided by the point weight w_a w_b w_c det J, restored
-// by the three N^T tables.  In filter steps D^-1 (a product of 1D factors on
-// affine cells) is folded into the gather's N tables the same way.
+// The weights of eqn refact are folded into the 1D tables, half on each side:
+// with N' = W^1/2 N (W the 1D weights and the Jacobian's cube root), u = N' x 3 X,
+// T_d = D_d u, D_d = sqrt(g_d) W^1/2 Dtilde W^-1/2 and c_d = Vtilde^G_d / sqrt(g_d),
+//   r = V u + sum_d [c_d T_d + D_d^T (T_d + c_d u) - i kappa_d / sqrt(g_d) T_d],
+//   Y^(e) = N'^T x 3 r,
+// which is eqn refact: the weights commute with the factors at the points.
+// The symmetric form needs two tables at a time, N' and one D_d, each applied
+// both ways.  In filter steps D^-1 (a product of 1D factors on affine cells)
+// is folded into the gather's N tables the same way.
 //
 // Scatter: as in k_local_impl.h (columns coloured, one launch per colour
 // phase, nodes of several columns stored by the lowest phase and
@@ -316,22 +317,28 @@ template <int E0> struct DppRow2<3, 3, E0> {
 #undef FEHX_FM
 #undef FEHX_T
 
-// A table as a stage holds it: FP32 keeps the pointer, FP64 the register pairs
+// A table as a stage holds it: FP32 keeps the pointer, opaque once per stage so
+// that the stage's lines share the loaded entries; FP64 the register pairs
 // (lane l of pair k: entry 16 k + l % 16 of the broadcast copy behind the
-// packed one, see PlaneTab).
-template <int NIN, int NOUT, typename TC> struct Table1D {
-  const TC *p;
-  __device__ __forceinline__ void load(const TC *q) { p = q; }
+// packed one, see PlaneTab).  TR: the transpose, applied from the table itself
+// in FP32 (eo_tr), from its own packed copy in FP64.
+template <int NIN, int NOUT, typename TC, bool TR = false> struct Table1D {
+  cptr<TC> p;
+  __device__ __forceinline__ void load(const TC *q) { p = scalar_table(q); }
+  __device__ __forceinline__ void load(const Table1D<NOUT, NIN, TC, false> &t, const TC *) { p = t.p; }
+  __device__ __forceinline__ void load(const TC *q, const PlaneTab &L) { p = scalar_table(q + L.n); }
 };
-template <int NIN, int NOUT> struct Table1D<NIN, NOUT, double> {
-  const double *p;
+template <int NIN, int NOUT, bool TR> struct Table1D<NIN, NOUT, double, TR> {
+  cptr<double> p;
   double t[DppTable<NIN, NOUT>::PT];
   __device__ __forceinline__ void load(const double *q) {
-    p = q;
-    const auto d = (cptr<double>)(uint64_t)(q + ((NOUT + 1) / 2) * NIN) + (threadIdx.x & 15);
+    p = scalar_table(q);
+    const auto d = p + ((NOUT + 1) / 2) * NIN + (threadIdx.x & 15);
 #pragma unroll
     for (int k = 0; k < DppTable<NIN, NOUT>::PT; ++k) t[k] = d[16 * k];
   }
+  template <typename T> __device__ __forceinline__ void load(const T &, const double *q) { load(q); }
+  __device__ __forceinline__ void load(const double *q, const PlaneTab &L) { load(q + L.nt); }
 };
 
 // e + o and their difference into rows Q and NOUT - 1 - Q of y (+)= A x
@@ -343,12 +350,12 @@ __device__ __forceinline__ void eo_put(V e, V o, V (&y)[NOUT]) {
 }
 
 // rows Q.. of y (+)= A x from xp = x_i + x_{n-1-i}, xm = x_i - x_{n-1-i}
-template <int NIN, int NOUT, int SYM, bool ADD, int Q, typename TC, typename V>
-__device__ __forceinline__ void eo_rows(const Table1D<NIN, NOUT, TC> &T, cptr<TC> p, const V *xp, const V *xm, V (&y)[NOUT]) {
+template <int NIN, int NOUT, int SYM, bool ADD, int Q, typename TC, bool TR, typename V>
+__device__ __forceinline__ void eo_rows(const Table1D<NIN, NOUT, TC, TR> &T, const V *xp, const V *xm, V (&y)[NOUT]) {
   constexpr int CI = (NIN + 1) / 2, HI = NIN / 2, CO = (NOUT + 1) / 2, HO = NOUT / 2;
   constexpr bool mid = (NOUT & 1) && Q == HO;
   if constexpr (Q < CO) {
-    cptr<TC> E = p + Q * NIN;
+    cptr<TC> E = T.p + Q * NIN;
     cptr<TC> O = E + CI;
     if constexpr (std::is_same<V, double>::value) {
       constexpr int R = DppTable<NIN, NOUT>::R, E0 = Q * R;
@@ -358,18 +365,18 @@ __device__ __forceinline__ void eo_rows(const Table1D<NIN, NOUT, TC> &T, cptr<TC
         else if constexpr (HI > 1) DppChain<HI - 1, E0 + CI - 1>::run(v, O[0], T.t, xm);
         else v = O[0] * xm[0];
         y[Q] = ADD ? y[Q] + v : v;
-        eo_rows<NIN, NOUT, SYM, ADD, Q + 1, TC, V>(T, p, xp, xm, y);
+        eo_rows<NIN, NOUT, SYM, ADD, Q + 1>(T, xp, xm, y);
       } else if constexpr (Q + 1 < HO && R <= 6) {
         double e, o, f, g;
         DppRow2<CI - 1, HI - 1, E0>::run(e, o, f, g, E[0], O[0], E[NIN], O[NIN], T.t, xp, xm);
         eo_put<NOUT, SYM, ADD, Q>(e, o, y);
         eo_put<NOUT, SYM, ADD, Q + 1>(f, g, y);
-        eo_rows<NIN, NOUT, SYM, ADD, Q + 2, TC, V>(T, p, xp, xm, y);
+        eo_rows<NIN, NOUT, SYM, ADD, Q + 2>(T, xp, xm, y);
       } else {
         double e, o;
         DppRow<CI - 1, HI - 1, E0>::run(e, o, E[0], O[0], T.t, xp, xm);
         eo_put<NOUT, SYM, ADD, Q>(e, o, y);
-        eo_rows<NIN, NOUT, SYM, ADD, Q + 1, TC, V>(T, p, xp, xm, y);
+        eo_rows<NIN, NOUT, SYM, ADD, Q + 1>(T, xp, xm, y);
       }
     } else {
       V e = 0, o = 0;
@@ -389,13 +396,16 @@ __device__ __forceinline__ void eo_rows(const Table1D<NIN, NOUT, TC> &T, cptr<TC
       } else {
         eo_put<NOUT, SYM, ADD, Q>(e, o, y);
       }
-      eo_rows<NIN, NOUT, SYM, ADD, Q + 1, TC, V>(T, p, xp, xm, y);
+      eo_rows<NIN, NOUT, SYM, ADD, Q + 1>(T, xp, xm, y);
     }
   }
 }
 
-template <int SYM, bool ADD, int NIN, int NOUT, typename TC, typename V>
-__device__ __forceinline__ void eo(const Table1D<NIN, NOUT, TC> &T, const V (&x)[NIN], V (&y)[NOUT]) {
+// y (+)= A x; T transposed: y (+)= A^T x from A's packed rows (FP32).  There the
+// half of x that meets E is the one A's rows sum into E's half of y: the even
+// one for a symmetric A, the odd one for an antisymmetric A.
+template <int SYM, bool ADD, int NIN, int NOUT, typename TC, bool TR, typename V>
+__device__ __forceinline__ void eo(const Table1D<NIN, NOUT, TC, TR> &T, const V (&x)[NIN], V (&y)[NOUT]) {
   constexpr int CI = (NIN + 1) / 2, HI = NIN / 2;
   V xp[CI], xm[HI];
 #pragma unroll
@@ -404,7 +414,28 @@ __device__ __forceinline__ void eo(const Table1D<NIN, NOUT, TC> &T, const V (&x)
     xm[i] = x[i] - x[NIN - 1 - i];
   }
   if constexpr (NIN & 1) xp[HI] = x[HI];
-  eo_rows<NIN, NOUT, SYM, ADD, 0, TC, V>(T, std::is_same<V, double>::value ? (cptr<TC>)(uint64_t)T.p : scalar_table(T.p), xp, xm, y);
+  if constexpr (TR && !std::is_same<TC, double>::value) {
+    constexpr int CO = (NOUT + 1) / 2, HO = NOUT / 2;    // A is NIN x NOUT: columns are y's
+    constexpr int KE = SYM > 0 ? CI : HI, KO = SYM > 0 ? HI : CI;
+    const V *xe = SYM > 0 ? xp : xm, *xo = SYM > 0 ? xm : xp;
+#pragma unroll
+    for (int i = 0; i < CO; ++i) {
+      V e = T.p[i] * xe[0];
+#pragma unroll
+      for (int q = 1; q < KE; ++q) e = vfma(T.p[q * NOUT + i], xe[q], e);
+      if (i == HO) {
+        y[i] = ADD ? y[i] + e : e;
+      } else {
+        V o = T.p[CO + i] * xo[0];
+#pragma unroll
+        for (int q = 1; q < KO; ++q) o = vfma(T.p[q * NOUT + CO + i], xo[q], o);
+        y[i] = ADD ? y[i] + (e + o) : e + o;
+        y[NOUT - 1 - i] = ADD ? y[NOUT - 1 - i] + (e - o) : e - o;
+      }
+    }
+  } else {
+    eo_rows<NIN, NOUT, SYM, ADD, 0>(T, xp, xm, y);
+  }
 }
 
 // Order this wave's LDS operations (no instruction: LDS runs a wave's
@@ -412,6 +443,19 @@ __device__ __forceinline__ void eo(const Table1D<NIN, NOUT, TC> &T, const V (&x)
 __device__ __forceinline__ void wave_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+}
+
+// FP32 (plain code, where FP64 has asm blocks): keeps the scheduler from
+// interleaving lines beyond the registers
+template <typename TC> __device__ __forceinline__ void line_end() {
+  if constexpr (!std::is_same<TC, double>::value) __builtin_amdgcn_sched_barrier(0);
+}
+
+// FP32: a value formed here, not sunk past the next branch (a whole plane's
+// inputs would stay live up to there)
+template <typename TC, typename V> __device__ __forceinline__ V in_line(V x) {
+  if constexpr (!std::is_same<TC, double>::value) asm volatile("" : "+v"(x));
+  return x;
 }
 
 // A wave-uniform value the compiler cannot see through: products with it are
@@ -439,8 +483,12 @@ constexpr unsigned BUF_SPAN = 0x7fffffffu, BUF_OFF = 0x80000000u;
 __device__ __forceinline__ BufRsrc buf_at(void *p) {
   return __builtin_amdgcn_make_buffer_rsrc(p, (short)0, (int)BUF_SPAN, 0x00027000);
 }
+// R is an element as a load leaves it, up() its value: BF16 stays packed while
+// the gather is in flight.
 template <typename TS, typename V> struct LaneIO;
 template <typename V> struct LaneIO64 {                  // eight bytes as they are
+  typedef V R;
+  static __device__ __forceinline__ V up(R v) { return v; }
   static __device__ __forceinline__ V ldb(BufRsrc r, int o) {
     return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, o, 0, 0));
   }
@@ -455,8 +503,10 @@ template <> struct LaneIO<float, f32x2> : LaneIO64<f32x2> {
   static __device__ __forceinline__ f32x2 ld(const float *p) { return *(const f32x2 *)p; }
 };
 template <> struct LaneIO<float, float> {
-  static __device__ __forceinline__ float ld(const float *p) { return *p; }
-  static __device__ __forceinline__ float ldb(BufRsrc r, int o) {
+  typedef float R;
+  static __device__ __forceinline__ float up(R v) { return v; }
+  static __device__ __forceinline__ R ld(const float *p) { return *p; }
+  static __device__ __forceinline__ R ldb(BufRsrc r, int o) {
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0));
   }
   static __device__ __forceinline__ void stb(BufRsrc r, int o, float v) {
@@ -464,20 +514,19 @@ template <> struct LaneIO<float, float> {
   }
 };
 template <> struct LaneIO<bf16s, float> {
-  static __device__ __forceinline__ float ld(const bf16s *p) { return bf16_to_f(p->b); }
-  static __device__ __forceinline__ float ldb(BufRsrc r, int o) {
-    return bf16_to_f(__builtin_amdgcn_raw_buffer_load_b16(r, o, 0, 0));
-  }
+  typedef uint16_t R;
+  static __device__ __forceinline__ float up(R v) { return bf16_to_f(v); }
+  static __device__ __forceinline__ R ld(const bf16s *p) { return p->b; }
+  static __device__ __forceinline__ R ldb(BufRsrc r, int o) { return __builtin_amdgcn_raw_buffer_load_b16(r, o, 0, 0); }
   static __device__ __forceinline__ void stb(BufRsrc r, int o, float v) {
     __builtin_amdgcn_raw_buffer_store_b16(f_to_bf16(v), r, o, 0, 0);
   }
 };
 template <> struct LaneIO<bf16s, f32x2> {
-  static __device__ __forceinline__ f32x2 two(uint32_t w) {
-    return (f32x2){__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u)};
-  }
-  static __device__ __forceinline__ f32x2 ld(const bf16s *p) { return two(*(const uint32_t *)p); }
-  static __device__ __forceinline__ f32x2 ldb(BufRsrc r, int o) { return two(__builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0)); }
+  typedef uint32_t R;
+  static __device__ __forceinline__ f32x2 up(R w) { return (f32x2){__uint_as_float(w << 16), __uint_as_float(w & 0xffff0000u)}; }
+  static __device__ __forceinline__ R ld(const bf16s *p) { return *(const uint32_t *)p; }
+  static __device__ __forceinline__ R ldb(BufRsrc r, int o) { return __builtin_amdgcn_raw_buffer_load_b32(r, o, 0, 0); }
   static __device__ __forceinline__ void stb(BufRsrc r, int o, f32x2 v) {
     __builtin_amdgcn_raw_buffer_store_b32((uint32_t)f_to_bf16(v.x) | ((uint32_t)f_to_bf16(v.y) << 16), r, o, 0, 0);
   }
@@ -489,7 +538,7 @@ template <> struct LaneIO<bf16s, f32x2> {
 // six of the seven slots exist, the last x parking its sum in registers: eight
 // waves of 18.8 KB then share a CU's LDS instead of seven of 22 KB.
 template <int NQ, bool CPLX, int LPT> struct PlaneShape {
-  static constexpr int TV = (64 / NQ) & ~1;
+  static constexpr int TV = plane_vt(NQ, 1);
   static constexpr int VT = TV * LPT;
   static constexpr int SZ = TV;
   static constexpr int SY = NQ * TV + ((NQ * TV * 2) % 64 == 0 ? 8 : 0);
@@ -559,25 +608,22 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
     if constexpr (LPT == 1) return vfma(kap * ksgn, swap_pair(t), z);
     else { z.x = fmaf(kap, t.y, z.x); z.y = fmaf(-kap, t.x, z.y); return z; }
   };
-  // one direction's line: out (+)= c T + Dh (T + c u) [- i kappa T], T = D u;
-  // without a GGA field out (+)= K u (real) or Dh T - i kappa T
-  Table1D<NP, NQ, TC> tn;        // N (filter steps: N D^-1)
-  Table1D<NQ, NP, TC> tt;        // (N W)^T
-  Table1D<NQ, NQ, TC> td, th;    // the current direction's D (or K) and Dh
+  // one direction's line: out += c T + D^T (T + c u) [- i kappa T], T = D u;
+  // without a GGA field out += K u (real) or D^T T - i kappa T
+  Table1D<NP, NQ, TC> tn;              // N' (filter steps: N' D^-1)
+  Table1D<NQ, NP, TC, true> tt;        // N'^T
+  Table1D<NQ, NQ, TC> td;              // the current direction's D (or K)
+  Table1D<NQ, NQ, TC, true> th;        // D^T
   auto stage_tables = [&](int d) {
-    const TC *q = scalar_ptr(a.ptab + (GGA || CPLX ? L.d : L.k) + d * L.dsz);
-    td.load(q);
-    if constexpr (GGA || CPLX) th.load(scalar_ptr(a.ptab + L.dh + d * L.dsz));
+    td.load(a.ptab + (GGA || CPLX ? L.d : L.k) + d * L.dsz);
+    if constexpr (GGA || CPLX) th.load(td, a.ptab + L.dh + d * L.dsz);
   };
-  auto stage = [&](auto dtag, auto add_tag, const V (&u)[NQ], V (&o)[NQ], const TC (&c)[NQ]) {
+  auto stage = [&](auto dtag, const V (&u)[NQ], V (&o)[NQ], const TC (&c)[NQ]) {
     constexpr int D = decltype(dtag)::value;
-    constexpr bool ADD = decltype(add_tag)::value;
     if constexpr (GGA || CPLX) {
       V T[NQ];
       eo<-1, false>(td, u, T);
-      if (!ADD)
-#pragma unroll
-        for (int i = 0; i < NQ; ++i) o[i] = 0;
+      line_end<TC>();
       if constexpr (CPLX) {
         const TC kap = a.pkap[D];
 #pragma unroll
@@ -590,9 +636,10 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
           T[i] = vfma(c[i], u[i], T[i]);
         }
       }
+      line_end<TC>();
       eo<-1, true>(th, T, o);
     } else {
-      eo<1, ADD>(td, u, o);
+      eo<1, true>(td, u, o);
     }
   };
 
@@ -601,6 +648,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
   for (int i = 0; i < NP; ++i) carry[i] = 0;
 
   V w[NQ][NQ];                                           // the plane [x][y]
+  typename IO::R wr[NP][NP];                             // the next cell's, as stored
   // gather of the (x, y) plane at node z = pl of cell cz (a thread past the
   // node planes repeats the last one; its results are not used)
   auto gather = [&](int cz) {
@@ -612,11 +660,11 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
     const TS *next = zp + (int64_t)(gy0 + 1) * rs;
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
-      w[0][j] = IO::ld(row + gxf * sx);
+      wr[0][j] = IO::ld(row + gxf * sx);
       const TS *q = row + (gx0 + 1) * sx;
 #pragma unroll
-      for (int i = 1; i < NP - 1; ++i, q += sx) w[i][j] = IO::ld(q);
-      w[NP - 1][j] = IO::ld(row + gxl * sx);
+      for (int i = 1; i < NP - 1; ++i, q += sx) wr[i][j] = IO::ld(q);
+      wr[NP - 1][j] = IO::ld(row + gxl * sx);
       if (j == NP - 2) row = zp + gyl * rs;
       else { row = next; next += rs; }
     }
@@ -644,7 +692,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
   TC cn[NQ];
   const int c0 = seg_start(seg, a.N2, a.nseg), c1 = seg_start(seg + 1, a.N2, a.nseg);
   gather(c0);
-  tn.load(scalar_ptr(a.pgather));
+  tn.load(a.pgather);
   stage_tables(2);
   for (int cz = c0; cz < c1; ++cz) {
     cell = cell_of(cz);
@@ -656,7 +704,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
         const bool in = zin && (j != 0 || y0) && (j != NP - 1 || y1);
 #pragma unroll
         for (int i = 0; i < NP; ++i)
-          w[i][j] = in && (i != 0 || x0) && (i != NP - 1 || x1) ? w[i][j] : (V)0;
+          wr[i][j] = in && (i != 0 || x0) && (i != NP - 1 || x1) ? wr[i][j] : (typename IO::R)0;
       }
     }
     // A: N along x
@@ -664,10 +712,11 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
     for (int j = 0; j < NP; ++j) {
       V x[NP], y[NQ];
 #pragma unroll
-      for (int i = 0; i < NP; ++i) x[i] = w[i][j];
+      for (int i = 0; i < NP; ++i) x[i] = IO::up(wr[i][j]);
       eo<1, false>(tn, x, y);
 #pragma unroll
       for (int i = 0; i < NQ; ++i) w[i][j] = y[i];
+      line_end<TC>();
     }
     // B per x (those parked in registers first, through slot 0): N along y,
     // exchange, N along z, u back to (x, y) planes, the z-direction stage and
@@ -688,6 +737,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
 #pragma unroll
         for (int q = 0; q < NQ; ++q) sw[q * S::SY] = y[q];
       }
+      line_end<TC>();
       wave_order();
       V x[NP], u[NQ], o[NQ];
 #pragma unroll
@@ -700,9 +750,11 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
 #pragma unroll
       for (int q = 0; q < NQ; ++q) w[i][q] = sw[q * S::SY];
       wave_order();
-      stage(std::integral_constant<int, 2>{}, std::false_type{}, u, o, cc);
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) sr[q * S::SZ] = vfma(vl[q], u[q], o[q]);
+      for (int q = 0; q < NQ; ++q) o[q] = vl[q] * u[q];
+      stage(std::integral_constant<int, 2>{}, u, o, cc);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) sr[q * S::SZ] = o[q];
       if (ii < NR) {
         wave_order();
 #pragma unroll
@@ -727,7 +779,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
         u[i] = w[i][j];
         o[i] = i < S::NS ? sw[i * S::SLOT] : orr[NQ - 1 - i][j];
       }
-      stage(std::integral_constant<int, 0>{}, std::true_type{}, u, o, cc);
+      stage(std::integral_constant<int, 0>{}, u, o, cc);
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         if (i < S::NS) sw[i * S::SLOT] = o[i];
@@ -736,7 +788,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
       __builtin_amdgcn_sched_barrier(0);
     }
     stage_tables(1);
-    tt.load(scalar_ptr(a.ptab + L.nt));
+    tt.load(a.ptab, L);
     wave_order();
     // the y-direction stage completes the sum; N^T along y
 #pragma unroll
@@ -752,10 +804,10 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
         u[j] = w[i][j];
         o[j] = i < S::NS ? sw[j * S::SY] : orr[NQ - 1 - i][j];
       }
-      stage(std::integral_constant<int, 1>{}, std::true_type{}, u, o, cc);
+      stage(std::integral_constant<int, 1>{}, u, o, cc);
       eo<1, false>(tt, o, y);
 #pragma unroll
-      for (int j = 0; j < NP; ++j) w[i][j] = y[j];
+      for (int j = 0; j < NP; ++j) w[i][j] = in_line<TC>(y[j]);
       __builtin_amdgcn_sched_barrier(0);
     }
     wave_order();
@@ -768,7 +820,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
     // a segment's first plane, which the segment below stores, goes to the
     // side block (same layout as a plane of Y)
     TS *const Y0 = a.nseg > 1 && cz == c0 ? (TS *)a.side + seg * sz : z0 ? Yz : Yz + sz;
-    V old[NP][NP - 1];                                   // [x][z]
+    typename IO::R old[NP][NP - 1];                      // [x][z]
     auto xnode = [&](int i) { return (i == 0 ? gxf : i == NP - 1 ? gxl : gx0 + i) * sy; };
     auto read_back = [&](int i) {
       const unsigned o = i == 0 ? or0 : i == NP - 1 ? or1 : orm;
@@ -796,11 +848,17 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
         if (i < S::NS) sw[i * S::SLOT] = y[i];
         else we[i - S::NS][j] = y[i];
       }
+      line_end<TC>();
     }
     wave_order();
     __builtin_amdgcn_sched_barrier(0);
     // the next cell's plane, in flight from here on
-    if (cz + 1 < c1) gather(cz + 1);
+    if (cz + 1 < c1) {
+      gather(cz + 1);
+    } else {                                             // (none of this cell's is live past here)
+#pragma unroll
+      for (int i = 0; i < NP * NP; ++i) wr[i / NP][i % NP] = 0;
+    }
     __builtin_amdgcn_sched_barrier(0);
     // D: N^T along z, the plane shared with the next cell, scatter
 #pragma unroll
@@ -808,7 +866,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
       const int i = line(ii);
       if (ii + RB < NP) read_back(line(ii + RB));
       if (ii == NP - 2 && cz + 1 < c1) {
-        tn.load(scalar_ptr(a.pgather));
+        tn.load(a.pgather);
         stage_tables(2);
       }
       const V *sr = B + v + pl * S::SY + (i < S::NS ? i : 0) * S::SLOT;
@@ -826,10 +884,11 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
       y[0] += carry[i];
       carry[i] = y[NP - 1];
       const unsigned oi = i == 0 ? ow0 : i == NP - 1 ? ow1 : ow;
-      IO::stb(buf_at(opaque(Y0) + xnode(i)), (int)(z0 ? oi : BUF_OFF), old[i][0] + y[0]);
+      IO::stb(buf_at(opaque(Y0) + xnode(i)), (int)(z0 ? oi : BUF_OFF), IO::up(old[i][0]) + y[0]);
       TS *q = opaque(Yz) + xnode(i);
 #pragma unroll
-      for (int k = 1; k < NP - 1; ++k) IO::stb(buf_at(q += sz), (int)oi, old[i][k] + y[k]);
+      for (int k = 1; k < NP - 1; ++k) IO::stb(buf_at(q += sz), (int)oi, IO::up(old[i][k]) + y[k]);
+      line_end<TC>();
     }
     wave_order();
   }
@@ -845,7 +904,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
       const BufRsrc r = buf_at((TS *)a.Y + gz * MM * a.ldy + (int64_t)(i == 0 ? gxf : i == NP - 1 ? gxl : gx0 + i) * a.ldy);
       const unsigned oi = i == 0 ? ow0 : i == NP - 1 ? ow1 : ow;
       const unsigned o = a.nseg == 1 ? oi : i == 0 ? or0 : i == NP - 1 ? or1 : orm;
-      IO::stb(r, (int)oi, IO::ldb(r, (int)o) + carry[i]);
+      IO::stb(r, (int)oi, IO::up(IO::ldb(r, (int)o)) + carry[i]);
     }
   }
 }
@@ -863,16 +922,12 @@ __global__ void k_planes_join(TS *__restrict__ Y, const TS *__restrict__ side, i
   for (int l = threadIdx.x; l < nlanes; l += blockDim.x) Cvt<TS, TC>::st(q, l, Cvt<TS, TC>::ld(q, l) + Cvt<TS, TC>::ld(r, l));
 }
 
-// Registers: two waves per SIMD up to seven points per direction (a plane and
-// one direction's stage fit 256 registers), one wave with 512 beyond.  Waves
-// are independent; they are grouped into blocks of four, which the device
-// spreads over a CU's four SIMDs (single-wave blocks may share one while
-// others idle).  One wave per SIMD with a whole cell of loads in flight took
-// 831 us at eight points (873 as here) but more than two waves at seven and
-// below.
-template <int NQ> struct PlaneWaves { static constexpr int value = NQ <= 7 ? 2 : 1; };
+// Waves are independent; they are grouped into blocks of four, which the
+// device spreads over a CU's four SIMDs (single-wave blocks may share one
+// while others idle).
 constexpr int PLANE_WPB = 4;
-#define FEHX_PLANE_BOUNDS __launch_bounds__(64 * PLANE_WPB) __attribute__((amdgpu_waves_per_eu(PlaneWaves<NQ>::value, PlaneWaves<NQ>::value)))
+#define FEHX_PLANE_WAVES (plane_waves(NQ, sizeof(TC) == 8, LPT))
+#define FEHX_PLANE_BOUNDS __launch_bounds__(64 * PLANE_WPB) __attribute__((amdgpu_waves_per_eu(FEHX_PLANE_WAVES, FEHX_PLANE_WAVES)))
 
 template <int NP, int NQ, bool CPLX, typename TS, typename TC, int LPT>
 __device__ __forceinline__ void plane_item(const KArgs<TC> &a, int w) {
@@ -913,7 +968,7 @@ template <int NP, int NQ, bool CPLX, typename TS, typename TC, int LPT>
 inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
   typedef PlaneShape<NQ, CPLX, LPT> S;
   constexpr size_t shm = (size_t)S::elems * LPT * sizeof(TC) * PLANE_WPB;
-  static_assert(shm <= LDS_MAX, "the plane exchange exceeds the LDS");
+  static_assert(shm * plane_waves(NQ, sizeof(TC) == 8, LPT) <= LDS_MAX, "the plane exchange exceeds the LDS");
   const bool single = Bt.n == 1 && !Bt.persistent;
   const void *kern = single ? (const void *)k_planes<NP, NQ, CPLX, TS, TC, LPT> : (const void *)k_planes_batch<NP, NQ, CPLX, TS, TC, LPT>;
   FE_HIP_TRY(plane_lds(kern, shm));
@@ -925,7 +980,7 @@ inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
     as.push_back(make_args<TC>(m, Bt.Ls[i], S::VT));
     KArgs<TC> &a = as.back();
     bool shared = false;
-    a.nseg = plane_segments(m, Bt.Ls[i], S::VT, sizeof(TS), s, &a.side, &shared);
+    a.nseg = plane_segments(m, Bt.Ls[i], LPT, sizeof(TS), s, &a.side, &shared);
     if (shared) {
       const fe_status st = plane_side_enter(m, s);
       if (st) return st;
@@ -992,6 +1047,26 @@ template <int NP, int NQ> fe_status pick_planes_f64(const LocalBatch &B, hipStre
   if (!planes_ok(B, sizeof(double))) return pick_cplx_f64<NP, NQ>(B, s);
   return B.ms[0]->cplx ? run_planes<NP, NQ, true, double, double, 1>(B, s)
                        : run_planes<NP, NQ, false, double, double, 1>(B, s);
+}
+
+// FP32 and BF16: threads of two adjacent lanes (a complex vector) where every
+// block's rows start on such a pair, else, real, of one.
+template <int NP, int NQ, typename TS> bool run_planes_f32(const LocalBatch &B, hipStream_t s, fe_status *st) {
+  if (!planes_ok(B, sizeof(TS))) return false;
+  const bool cplx = B.ms[0]->cplx;
+  const bool pairs = plane_pairs(B, sizeof(TS)) && (cplx || plane_pairs_pay(B, sizeof(TS)));
+  if (cplx && !pairs) return false;
+  *st = cplx ? run_planes<NP, NQ, true, TS, float, 2>(B, s)
+             : pairs ? run_planes<NP, NQ, false, TS, float, 2>(B, s) : run_planes<NP, NQ, false, TS, float, 1>(B, s);
+  return true;
+}
+template <int NP, int NQ> fe_status pick_planes_f32(const LocalBatch &B, hipStream_t s) {
+  fe_status st = FE_OK;
+  return run_planes_f32<NP, NQ, float>(B, s, &st) ? st : pick_cplx_f32<NP, NQ>(B, s);
+}
+template <int NP, int NQ> fe_status pick_planes_bf16(const LocalBatch &B, hipStream_t s) {
+  fe_status st = FE_OK;
+  return run_planes_f32<NP, NQ, bf16s>(B, s, &st) ? st : pick_cplx_bf16<NP, NQ>(B, s);
 }
 
 }  // namespace fehx

@@ -821,6 +821,7 @@ extern "C" fe_status fe_apply_H_noalloc(fe_mesh_t m, const void *X, int64_t ldx,
   L.X = X; L.Y = Y; L.ldx = ldx * C; L.ldy = ldy * C; L.nlanes = nlanes; L.prec = prec;
   L.vt = m->vt_pref[prec][0];
   L.side = (unsigned char *)ws + FE_NOALLOC_SCRATCH_BYTES;
+  L.side_bytes = PLANE_SIDE_BYTES;
   // projector reduction, local operator, projector update on the caller's
   // stream, as in fe_apply_H
   if ((st = dispatch_nl(m, X, L.ldx, nullptr, 0, nlanes, prec, nullptr, 0.0, 1, s, ws))) return st;

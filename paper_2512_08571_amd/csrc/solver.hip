@@ -5,8 +5,7 @@
 // Filter data flow (Alg. 4; D^-1 is always the lumped inverse):
 //   Y   = H X  (FP64), then one streaming pass forms Y - M X Lambda,
 //         R_Y = (sigma1/e) Y, Ylp = Y in the block precision, R_X = 0
-//   (block precision: FP64 for FP64 steps, FP32 for FP32 and for BF16 steps,
-//    whose operator alone takes BF16 operands on the matrix cores)
+//   (block precision: FP64 for FP64 steps, FP32 for FP32 and for BF16 steps)
 //   step k: T = H D^-1 R_Y  (local + nonlocal operator on R_Y, D^-1 applied
 //           at the gather), then one streaming pass
 //           R_X <- a T - a c R_Y + a Lambda_Y Ylp - sigma sigma2 R_X;
@@ -267,8 +266,7 @@ fe_status filter_setup(FilterPlan &P, Mesh *m, double *X, int64_t ldx_l, const d
                        int degree, double lmin, double lT, double lmax, int prec) {
   P = FilterPlan();
   P.m = m; P.X = X; P.ldx = ldx_l; P.lam = lam; P.nvec = nvec; P.degree = degree; P.prec = prec;
-  // BF16 steps keep the recurrence state in FP32; only the operator's
-  // contractions take BF16 (hi/lo) operands on the matrix cores
+  // BF16 steps keep the recurrence state in FP32, and so run as FP32 steps
   P.sprec = prec == FE_F64 ? FE_F64 : FE_F32;
   const int C = m->cplx ? 2 : 1;
   P.lanes = (int)(nvec * C);
@@ -321,7 +319,7 @@ fe_status filter_prologue(FilterPlan &P, hipStream_t s) {
   LocalLaunch L0;
   L0.X = P.X; L0.Y = P.Y; L0.ldx = P.ldx; L0.ldy = P.lanes; L0.nlanes = P.lanes; L0.prec = FE_F64;
   L0.vt = m->vt_pref[FE_F64][0];
-  L0.side = P.side;
+  L0.side = P.side; L0.side_bytes = P.side_need;
   fe_status st;
   if ((st = apply_with_nonlocal(m, L0, FE_F64, nullptr, 1.0, s))) return st;
   const double *MX = nullptr;
@@ -357,7 +355,7 @@ LocalLaunch filter_step_local(const FilterPlan &P) {
   L.X = P.RY; L.Y = P.T; L.ldx = P.lanes; L.ldy = P.lanes; L.nlanes = P.lanes; L.prec = P.prec;
   L.store32 = P.prec == FE_BF16;
   L.dinv_gather = P.m->dinv;
-  L.side = P.side;
+  L.side = P.side; L.side_bytes = P.side_need;
   L.vt = P.m->vt_pref[P.prec][1];
   return L;
 }
