@@ -176,15 +176,19 @@ void quad_point(const Mesh *m, int64_t c, int q1, int q2, int q3, double x[3], d
 void cell_coefficients(const Mesh *m, int64_t c, const double *vloc, const double *vgga, double *out) {
   const int nq = m->nq, nq3 = nq * nq * nq;
   const double *k = m->desc.kpoint;
+  double J[3][3], Ji[3][3], dj = 0.0;                    // the same at every point of an affine cell
   for (int q3 = 0; q3 < nq; ++q3)
     for (int q2 = 0; q2 < nq; ++q2)
       for (int q1 = 0; q1 < nq; ++q1) {
         const int Q = (q3 * nq + q2) * nq + q1;
-        const double xi[3] = {m->t1.xq[q1], m->t1.xq[q2], m->t1.xq[q3]};
-        double x[3], J[3][3], Ji[3][3];
-        point_geometry(m, c, xi, x, J);
-        const double w = m->t1.wq[q1] * m->t1.wq[q2] * m->t1.wq[q3] * det3(J);
-        inv3(J, Ji);
+        if (m->distorted || Q == 0) {
+          const double xi[3] = {m->t1.xq[q1], m->t1.xq[q2], m->t1.xq[q3]};
+          double x[3];
+          point_geometry(m, c, xi, x, J);
+          dj = det3(J);
+          inv3(J, Ji);
+        }
+        const double w = m->t1.wq[q1] * m->t1.wq[q2] * m->t1.wq[q3] * dj;
         out[Q] = ((vloc ? vloc[Q] : 0.0) + m->k2half) * w;
         for (int s = 0; s < 3; ++s) {
           // reference-frame GGA coefficient sum_a (J^-1)_{s a} V^G_a (reading C-2)
@@ -316,6 +320,11 @@ std::vector<double> plane_tables(const Mesh *m) {
     put(L.dh + d * L.dsz, H, nq, nq, -1);
     put(L.k + d * L.dsz, K, nq, nq, +1);
   }
+  A.assign((size_t)np * np, 0.0);
+  for (int i = 0; i < np; ++i)
+    for (int j = 0; j < np; ++j)
+      for (int q = 0; q < nq; ++q) A[i * np + j] += Nh[q * np + i] * Nh[q * np + j];
+  put(L.m, A, np, np, +1);
   return tab;
 }
 
@@ -368,16 +377,23 @@ fe_status build_geometry(Mesh *m) {
   if ((st = upload(m, &m->dinv, dinv))) return st;
   // zero potential: (0 + |k|^2/2) w det J, no GGA, the metric and Bloch blocks
   std::vector<double> coef((size_t)m->E * m->ncoef * nq3, 0.0);
-  for (int64_t c = 0; c < m->E; ++c) cell_coefficients(m, c, nullptr, nullptr, &coef[(size_t)c * m->ncoef * nq3]);
+  for (int64_t c = 0; c < m->E; ++c) {
+    const size_t nc = (size_t)m->ncoef * nq3;
+    if (m->distorted || c == 0) cell_coefficients(m, c, nullptr, nullptr, &coef[c * nc]);
+    else std::copy_n(coef.begin(), nc, coef.begin() + c * nc);   // affine: every cell's are the same
+  }
   if ((st = upload(m, &m->coef64, coef))) return st;
   if ((st = upload(m, &m->coef32, to_f32(coef)))) return st;
-  if (!m->offd) {
+  if (!m->distorted) {
     const std::vector<double> ptab = plane_tables(m);
     if ((st = upload(m, &m->ptab64, ptab))) return st;
     if ((st = upload(m, &m->ptab32, to_f32(ptab)))) return st;
     for (int d = 0; d < 3; ++d) m->pkap[d] = m->kap[d] / std::sqrt(m->gdiag[d]);
+  }
+  if (plane_mesh(m)) {
     std::vector<double> pc((size_t)m->E * 4 * nq3);
-    for (int64_t c = 0; c < m->E; ++c) plane_coefficients(m, nullptr, nullptr, &pc[(size_t)c * 4 * nq3]);
+    plane_coefficients(m, nullptr, nullptr, pc.data());
+    for (int64_t c = 1; c < m->E; ++c) std::copy_n(pc.begin(), 4 * nq3, pc.begin() + c * 4 * nq3);
     if ((st = upload(m, &m->pcoef64, pc))) return st;
     if ((st = upload(m, &m->pcoef32, to_f32(pc)))) return st;
   }
@@ -651,7 +667,7 @@ fe_status fe_set_potential(fe_mesh_t m, const double *vloc, const double *vgga) 
   FE_HIP_TRY(hipMemcpy(m->coef64, coef.data(), coef.size() * sizeof(double), hipMemcpyHostToDevice));
   std::vector<float> c32 = to_f32(coef);
   FE_HIP_TRY(hipMemcpy(m->coef32, c32.data(), c32.size() * sizeof(float), hipMemcpyHostToDevice));
-  if (!m->offd) {
+  if (plane_mesh(m)) {
     std::vector<double> pc((size_t)m->E * 4 * nq3);
     for (int64_t c = 0; c < m->E; ++c)
       plane_coefficients(m, vloc + c * nq3, vgga ? vgga + 3 * c * nq3 : nullptr, &pc[(size_t)c * 4 * nq3]);

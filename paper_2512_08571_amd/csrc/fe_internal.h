@@ -78,11 +78,11 @@ inline TabLayout tab_layout(int np, int nq) {
 // Tables of the plane kernels (k_local_planes.h), as offsets in elements: n
 // (W^1/2 N, W the 1D weights and the Jacobian's cube root), nd (that with D^-1's
 // 1D factor), nt (n^T), per direction d (sqrt(g_d) W^1/2 Dtilde W^-1/2), dh (d^T)
-// and k (dh d), each of dsz.  A table is the
+// and k (dh d), each of dsz, and m (n^T n, the 1D mass).  A table is the
 // even-odd packed matrix (eo_pack) followed by a copy of its entries past the
 // first column of E and of O, row by row, padded to a multiple of 16.
 struct PlaneTab {
-  int n, nd, nt, d, dh, k, dsz, total;
+  int n, nd, nt, d, dh, k, m, dsz, total;
 };
 constexpr int plane_bcast(int nin, int nout) { return ((nout + 1) / 2 * (nin - 2) + 15) / 16 * 16; }
 constexpr int plane_tab1(int nin, int nout) { return (nout + 1) / 2 * nin + plane_bcast(nin, nout); }
@@ -96,7 +96,8 @@ constexpr PlaneTab plane_tab(int np, int nq) {
   t.d = t.nt + ts;
   t.dh = t.d + 3 * t.dsz;
   t.k = t.dh + 3 * t.dsz;
-  t.total = t.k + 3 * t.dsz;
+  t.m = t.k + 3 * t.dsz;
+  t.total = t.m + plane_tab1(np, np);
   return t;
 }
 
@@ -130,11 +131,12 @@ constexpr int plane_waves(int nq, bool f64, int lpt) {
 // Segments a column of cells is cut into by the plane kernels, and the block for their first planes (see plane_segments)
 constexpr int64_t PLANE_SIDE_BYTES = 16LL << 20;    // beside the static scratch
 constexpr int64_t PLANE_SIDE_MAX = 64LL << 20;      // of a mesh
-int plane_segment_count(const Mesh *m, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes, double *cost);
-int plane_segments(Mesh *m, const LocalLaunch &L, int lpt, int elem_bytes, hipStream_t s, void **side, bool *shared);
+int plane_segment_count(const Mesh *m, int nq, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes, double *cost);
+int plane_segments(Mesh *m, const LocalLaunch &L, int nq, int lpt, int elem_bytes, hipStream_t s, void **side, bool *shared);
+bool plane_mesh(const Mesh *m);
 struct LocalBatch;
 bool plane_pairs(const LocalBatch &B, size_t elem_bytes);
-bool plane_pairs_pay(const LocalBatch &B, size_t elem_bytes);
+bool plane_pairs_pay(const LocalBatch &B, int nq, size_t elem_bytes);
 int64_t plane_side_need(const Mesh *m, int nlanes, int64_t ldy, int prec);
 fe_status plane_side_enter(Mesh *m, hipStream_t s);
 fe_status plane_side_leave(Mesh *m, hipStream_t s);

@@ -12,6 +12,8 @@ constexpr int PLANE_SIMDS = 1024;   // four per CU, 256 CUs
 fe_status launch_local_f64(const LocalBatch &B, hipStream_t s);
 fe_status launch_local_f32(const LocalBatch &B, hipStream_t s);
 fe_status launch_local_bf16(const LocalBatch &B, hipStream_t s);
+fe_status launch_local_mass(const LocalBatch &B, hipStream_t s);
+bool local_mass_ok(const LocalBatch &B);
 
 // A wave of the plane kernels walks its cells one after another, so a launch
 // with few columns and tiles leaves most of the device idle for the length of
@@ -22,9 +24,9 @@ fe_status launch_local_bf16(const LocalBatch &B, hipStream_t s);
 // gather and last plane cost about half a cell; a cell takes a wave about
 // 1 + 2 k with k waves on its SIMD (FP64, 7 points: 20 us alone, 34 us by twos).
 // The side block is at most side_bytes.
-int plane_segment_count(const Mesh *m, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes,
+int plane_segment_count(const Mesh *m, int nq, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes,
                         double *cost) {
-  const int vt = plane_vt(m->nq, lpt), per = plane_waves(m->nq, f64, lpt);
+  const int vt = plane_vt(nq, lpt), per = plane_waves(nq, f64, lpt);
   const int64_t waves = (int64_t)(m->phase_off[1] - m->phase_off[0]) * ((nlanes + vt - 1) / vt);
   const int64_t plane = (int64_t)m->Mn[0] * m->Mn[1] * ldy * elem_bytes;
   const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(m->N[2], side_bytes / plane));
@@ -54,14 +56,14 @@ bool plane_pairs(const LocalBatch &B, size_t elem_bytes) {
 
 // Whether threads of two lanes (a third faster per lane on a full device) beat
 // threads of one (0.55 of the time per cell, twice the waves) for real blocks.
-bool plane_pairs_pay(const LocalBatch &B, size_t elem_bytes) {
+bool plane_pairs_pay(const LocalBatch &B, int nq, size_t elem_bytes) {
   double one = 0, two = 0;
   for (int i = 0; i < B.n; ++i) {
     const LocalLaunch &L = B.Ls[i];
     const int64_t side = L.side ? L.side_bytes : PLANE_SIDE_MAX;
     double c1, c2;
-    plane_segment_count(B.ms[i], L.nlanes, L.ldy, false, 1, (int)elem_bytes, side, &c1);
-    plane_segment_count(B.ms[i], L.nlanes, L.ldy, false, 2, (int)elem_bytes, side, &c2);
+    plane_segment_count(B.ms[i], nq, L.nlanes, L.ldy, false, 1, (int)elem_bytes, side, &c1);
+    plane_segment_count(B.ms[i], nq, L.nlanes, L.ldy, false, 2, (int)elem_bytes, side, &c2);
     one += 0.55 * c1;
     two += c2;
   }
@@ -70,14 +72,15 @@ bool plane_pairs_pay(const LocalBatch &B, size_t elem_bytes) {
 
 // bytes of the side block of an application to a block of nlanes lanes with
 // leading dimension ldy (lanes), for either width of a thread, and for FE_BF16
-// with either block type
+// with either block type: H where the plane kernels run it, and the mass
 int64_t plane_side_need(const Mesh *m, int nlanes, int64_t ldy, int prec) {
-  if (!plane_mesh(m)) return 0;
+  if (m->distorted || (!plane_mesh(m) && m->mass_kind != FE_MASS_CONSISTENT)) return 0;
+  const int nq = plane_mesh(m) ? m->nq : m->np;
   const bool f64 = prec == FE_F64;
   int64_t need = 0;
   for (int lpt = 1; lpt <= (f64 ? 1 : 2); ++lpt)
     for (int es = prec == FE_BF16 ? 2 : f64 ? 8 : 4; es <= (f64 ? 8 : 4); es *= 2) {
-      const int n = plane_segment_count(m, nlanes, ldy, f64, lpt, es, PLANE_SIDE_MAX, nullptr);
+      const int n = plane_segment_count(m, nq, nlanes, ldy, f64, lpt, es, PLANE_SIDE_MAX, nullptr);
       if (n > 1) need = std::max(need, (int64_t)n * m->Mn[0] * m->Mn[1] * ldy * es);
     }
   return need;
@@ -109,8 +112,8 @@ fe_status plane_side_leave(Mesh *m, hipStream_t s) {
 // (then *shared: enter and leave around the use).  A block that cannot be had
 // now (the stream is capturing, a captured graph holds the mesh's smaller one,
 // no memory) means one segment.
-int plane_segments(Mesh *m, const LocalLaunch &L, int lpt, int elem_bytes, hipStream_t s, void **side, bool *shared) {
-  const int n = plane_segment_count(m, L.nlanes, L.ldy, L.prec == FE_F64, lpt, elem_bytes, L.side ? L.side_bytes : PLANE_SIDE_MAX, nullptr);
+int plane_segments(Mesh *m, const LocalLaunch &L, int nq, int lpt, int elem_bytes, hipStream_t s, void **side, bool *shared) {
+  const int n = plane_segment_count(m, nq, L.nlanes, L.ldy, L.prec == FE_F64, lpt, elem_bytes, L.side ? L.side_bytes : PLANE_SIDE_MAX, nullptr);
   *side = L.side;
   *shared = false;
   if (n == 1 || L.side) return n;
@@ -135,6 +138,7 @@ fe_status launch_local_batch(const LocalBatch &B, hipStream_t s) {
     if (B.Ls[i].prec != B.Ls[0].prec || B.Ls[i].vt != B.Ls[0].vt || B.Ls[i].store32 != B.Ls[0].store32)
       return set_error(FE_EINVAL, "a batched launch needs one precision, block type and vector tile");
   }
+  if (local_mass_ok(B)) return launch_local_mass(B, s);
   // general-metric systems and the rest run different kernels: one launch set each
   auto general = [&](int i) { return B.ms[i]->offd && !B.Ls[i].mass; };
   int ngen = 0;

@@ -28,6 +28,10 @@
 // both ways.  In filter steps D^-1 (a product of 1D factors on affine cells)
 // is folded into the gather's N tables the same way.
 //
+// The consistent mass of affine cells is separable, M^(e) = M x 3 with
+// M = N'^T N': MASS applies it along x and y in the gathered plane and along z
+// after the one exchange, with no coefficients.
+//
 // Scatter: as in k_local_impl.h (columns coloured, one launch per colour
 // phase, nodes of several columns stored by the lowest phase and
 // read-modify-written by later ones; fixed summation order, no atomics).
@@ -547,7 +551,7 @@ template <int NQ, bool CPLX, int LPT> struct PlaneShape {
   static constexpr int elems = NS * SLOT;      // LDS elements of LPT lanes
 };
 
-template <int NP, int NQ, bool CPLX, bool GGA, typename TS, typename TC, int LPT>
+template <int NP, int NQ, bool CPLX, bool GGA, typename TS, typename TC, int LPT, bool MASS>
 __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, const int seg, const int tile) {
   typedef typename LaneVec<TC, LPT>::T V;
   typedef PlaneShape<NQ, CPLX, LPT> S;
@@ -693,7 +697,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
   const int c0 = seg_start(seg, a.N2, a.nseg), c1 = seg_start(seg + 1, a.N2, a.nseg);
   gather(c0);
   tn.load(a.pgather);
-  stage_tables(2);
+  if constexpr (!MASS) stage_tables(2);
   for (int cz = c0; cz < c1; ++cz) {
     cell = cell_of(cz);
     if (a.dmask) {
@@ -718,6 +722,15 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
       for (int i = 0; i < NQ; ++i) w[i][j] = y[i];
       line_end<TC>();
     }
+    if constexpr (MASS) {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        V y[NP];
+        eo<1, false>(tn, w[i], y);
+#pragma unroll
+        for (int j = 0; j < NP; ++j) w[i][j] = in_line<TC>(y[j]);
+      }
+    } else {
     // B per x (those parked in registers first, through slot 0): N along y,
     // exchange, N along z, u back to (x, y) planes, the z-direction stage and
     // the potential parked
@@ -810,6 +823,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
       for (int j = 0; j < NP; ++j) w[i][j] = in_line<TC>(y[j]);
       __builtin_amdgcn_sched_barrier(0);
     }
+    }
     wave_order();
     // The values this cell's scatter reads back, RB lines ahead of their use.  The
     // last plane of a cell is carried to the next one (after the column's last
@@ -841,7 +855,12 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
       V x[NQ], y[NP];
 #pragma unroll
       for (int i = 0; i < NQ; ++i) x[i] = w[i][j];
-      eo<1, false>(tt, x, y);
+      if constexpr (MASS) {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) y[i] = x[i];
+      } else {
+        eo<1, false>(tt, x, y);
+      }
       V *sw = B + v + pl * S::SZ + j * S::SY;
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
@@ -865,7 +884,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
     for (int ii = 0; ii < NP; ++ii) {
       const int i = line(ii);
       if (ii + RB < NP) read_back(line(ii + RB));
-      if (ii == NP - 2 && cz + 1 < c1) {
+      if (!MASS && ii == NP - 2 && cz + 1 < c1) {
         tn.load(a.pgather);
         stage_tables(2);
       }
@@ -880,7 +899,8 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
 #pragma unroll
       for (int q = 0; q < NQ; ++q) z[q] = sr[q * S::SZ];
       if (ii <= NX) wave_order();
-      eo<1, false>(tt, z, y);
+      if constexpr (MASS) eo<1, false>(tn, z, y);
+      else eo<1, false>(tt, z, y);
       y[0] += carry[i];
       carry[i] = y[NP - 1];
       const unsigned oi = i == 0 ? ow0 : i == NP - 1 ? ow1 : ow;
@@ -929,30 +949,34 @@ constexpr int PLANE_WPB = 4;
 #define FEHX_PLANE_WAVES (plane_waves(NQ, sizeof(TC) == 8, LPT))
 #define FEHX_PLANE_BOUNDS __launch_bounds__(64 * PLANE_WPB) __attribute__((amdgpu_waves_per_eu(FEHX_PLANE_WAVES, FEHX_PLANE_WAVES)))
 
-template <int NP, int NQ, bool CPLX, typename TS, typename TC, int LPT>
+template <int NP, int NQ, bool CPLX, typename TS, typename TC, int LPT, bool MASS>
 __device__ __forceinline__ void plane_item(const KArgs<TC> &a, int w) {
   const int cs = w / a.ntiles, tile = w - cs * a.ntiles;
   const int col = cs / a.nseg, seg = cs - col * a.nseg;
-  if (a.gga) plane_column<NP, NQ, CPLX, true, TS, TC, LPT>(a, col, seg, tile);
-  else plane_column<NP, NQ, CPLX, false, TS, TC, LPT>(a, col, seg, tile);
+  if constexpr (MASS) {
+    plane_column<NP, NQ, CPLX, false, TS, TC, LPT, true>(a, col, seg, tile);
+  } else {
+    if (a.gga) plane_column<NP, NQ, CPLX, true, TS, TC, LPT, false>(a, col, seg, tile);
+    else plane_column<NP, NQ, CPLX, false, TS, TC, LPT, false>(a, col, seg, tile);
+  }
 }
 
-template <int NP, int NQ, bool CPLX, typename TS, typename TC, int LPT>
+template <int NP, int NQ, bool CPLX, typename TS, typename TC, int LPT, bool MASS>
 __global__ void FEHX_PLANE_BOUNDS k_planes(KArgs<TC> a) {
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int w = xcd_item(blockIdx.x, gridDim.x) * PLANE_WPB + wv;
   if (w >= a.ncols * a.nseg * a.ntiles) return;
-  plane_item<NP, NQ, CPLX, TS, TC, LPT>(a, w);
+  plane_item<NP, NQ, CPLX, TS, TC, LPT, MASS>(a, w);
 }
 
-template <int NP, int NQ, bool CPLX, typename TS, typename TC, int LPT>
+template <int NP, int NQ, bool CPLX, typename TS, typename TC, int LPT, bool MASS>
 __global__ void FEHX_PLANE_BOUNDS k_planes_batch(BatchArgs<TC> Bt) {
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int w = xcd_item(blockIdx.x, gridDim.x) * PLANE_WPB + wv;
   if (w >= Bt.total) return;
   int sidx = 0;
   while (sidx + 1 < Bt.nsys && w >= Bt.off[sidx + 1]) ++sidx;
-  plane_item<NP, NQ, CPLX, TS, TC, LPT>(Bt.sys[sidx], w - Bt.off[sidx]);
+  plane_item<NP, NQ, CPLX, TS, TC, LPT, MASS>(Bt.sys[sidx], w - Bt.off[sidx]);
 }
 
 // blocks above 64 KiB raise the kernel's dynamic-LDS attribute first
@@ -964,13 +988,13 @@ inline unsigned plane_grid(int waves) {
   return (unsigned)((b + 7) / 8 * 8);
 }
 
-template <int NP, int NQ, bool CPLX, typename TS, typename TC, int LPT>
+template <int NP, int NQ, bool CPLX, typename TS, typename TC, int LPT, bool MASS = false>
 inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
   typedef PlaneShape<NQ, CPLX, LPT> S;
   constexpr size_t shm = (size_t)S::elems * LPT * sizeof(TC) * PLANE_WPB;
   static_assert(shm * plane_waves(NQ, sizeof(TC) == 8, LPT) <= LDS_MAX, "the plane exchange exceeds the LDS");
   const bool single = Bt.n == 1 && !Bt.persistent;
-  const void *kern = single ? (const void *)k_planes<NP, NQ, CPLX, TS, TC, LPT> : (const void *)k_planes_batch<NP, NQ, CPLX, TS, TC, LPT>;
+  const void *kern = single ? (const void *)k_planes<NP, NQ, CPLX, TS, TC, LPT, MASS> : (const void *)k_planes_batch<NP, NQ, CPLX, TS, TC, LPT, MASS>;
   FE_HIP_TRY(plane_lds(kern, shm));
   std::vector<KArgs<TC>> as;
   std::vector<Mesh *> sharing;
@@ -979,8 +1003,9 @@ inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
     Mesh *m = Bt.ms[i];
     as.push_back(make_args<TC>(m, Bt.Ls[i], S::VT));
     KArgs<TC> &a = as.back();
+    if constexpr (MASS) a.pgather = a.ptab + plane_tab(m->np, m->nq).m;
     bool shared = false;
-    a.nseg = plane_segments(m, Bt.Ls[i], LPT, sizeof(TS), s, &a.side, &shared);
+    a.nseg = plane_segments(m, Bt.Ls[i], NQ, LPT, sizeof(TS), s, &a.side, &shared);
     if (shared) {
       const fe_status st = plane_side_enter(m, s);
       if (st) return st;
@@ -1008,8 +1033,8 @@ inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
       if (B.nsys == 0) continue;
       B.total = B.off[B.nsys];
       const dim3 grid(plane_grid(B.total)), block(64 * PLANE_WPB);
-      if (single) hipLaunchKernelGGL((k_planes<NP, NQ, CPLX, TS, TC, LPT>), grid, block, shm, s, B.sys[0]);
-      else hipLaunchKernelGGL((k_planes_batch<NP, NQ, CPLX, TS, TC, LPT>), grid, block, shm, s, B);
+      if (single) hipLaunchKernelGGL((k_planes<NP, NQ, CPLX, TS, TC, LPT, MASS>), grid, block, shm, s, B.sys[0]);
+      else hipLaunchKernelGGL((k_planes_batch<NP, NQ, CPLX, TS, TC, LPT, MASS>), grid, block, shm, s, B);
       FE_HIP_TRY(hipGetLastError());
     }
   }
@@ -1043,6 +1068,16 @@ inline bool planes_ok(const LocalBatch &B, size_t es) {
   return true;
 }
 
+// The mass operator of affine cells, any rule; complex blocks as their lanes.
+inline bool plane_mass_ok(const LocalBatch &B, size_t es) {
+  for (int i = 0; i < B.n; ++i) {
+    const Mesh *m = B.ms[i];
+    if (!B.Ls[i].mass || m->distorted) return false;
+    if ((int64_t)m->Mn[0] * m->Mn[1] * B.Ls[i].ldy * (int64_t)es >= (int64_t)BUF_SPAN) return false;
+  }
+  return true;
+}
+
 template <int NP, int NQ> fe_status pick_planes_f64(const LocalBatch &B, hipStream_t s) {
   if (!planes_ok(B, sizeof(double))) return pick_cplx_f64<NP, NQ>(B, s);
   return B.ms[0]->cplx ? run_planes<NP, NQ, true, double, double, 1>(B, s)
@@ -1054,7 +1089,7 @@ template <int NP, int NQ> fe_status pick_planes_f64(const LocalBatch &B, hipStre
 template <int NP, int NQ, typename TS> bool run_planes_f32(const LocalBatch &B, hipStream_t s, fe_status *st) {
   if (!planes_ok(B, sizeof(TS))) return false;
   const bool cplx = B.ms[0]->cplx;
-  const bool pairs = plane_pairs(B, sizeof(TS)) && (cplx || plane_pairs_pay(B, sizeof(TS)));
+  const bool pairs = plane_pairs(B, sizeof(TS)) && (cplx || plane_pairs_pay(B, NQ, sizeof(TS)));
   if (cplx && !pairs) return false;
   *st = cplx ? run_planes<NP, NQ, true, TS, float, 2>(B, s)
              : pairs ? run_planes<NP, NQ, false, TS, float, 2>(B, s) : run_planes<NP, NQ, false, TS, float, 1>(B, s);
