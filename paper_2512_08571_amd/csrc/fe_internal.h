@@ -132,7 +132,9 @@ constexpr int plane_waves(int nq, bool f64, int lpt) {
 constexpr int64_t PLANE_SIDE_BYTES = 16LL << 20;    // beside the static scratch
 constexpr int64_t PLANE_SIDE_MAX = 64LL << 20;      // of a mesh
 int plane_segment_count(const Mesh *m, int nq, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes, double *cost);
-int plane_segments(Mesh *m, const LocalLaunch &L, int nq, int lpt, int elem_bytes, hipStream_t s, void **side, bool *shared);
+int64_t side_limit(const LocalLaunch &L);
+int block_segment_count(const Mesh *m, int64_t ldy, int tiles, int per_cu, int elem_bytes, int64_t side_bytes);
+int side_segments(Mesh *m, const LocalLaunch &L, int n, int elem_bytes, hipStream_t s, void **side, bool *shared);
 bool plane_mesh(const Mesh *m);
 struct LocalBatch;
 bool plane_pairs(const LocalBatch &B, size_t elem_bytes);

@@ -7,7 +7,7 @@
 
 namespace fehx {
 
-constexpr int PLANE_SIMDS = 1024;   // four per CU, 256 CUs
+constexpr int DEVICE_CUS = 256;
 
 fe_status launch_local_f64(const LocalBatch &B, hipStream_t s);
 fe_status launch_local_f32(const LocalBatch &B, hipStream_t s);
@@ -15,32 +15,47 @@ fe_status launch_local_bf16(const LocalBatch &B, hipStream_t s);
 fe_status launch_local_mass(const LocalBatch &B, hipStream_t s);
 bool local_mass_ok(const LocalBatch &B);
 
-// A wave of the plane kernels walks its cells one after another, so a launch
-// with few columns and tiles leaves most of the device idle for the length of
-// a column.  Its columns are then cut into segments (each segment's first
-// plane, shared with the one below, goes to a side block of planes laid out as
-// Y's, added to Y after the last colour phase).  The count is the one of least
-// cost: rounds of the device's waves times cells per wave.  A wave's first
-// gather and last plane cost about half a cell; a cell takes a wave about
-// 1 + 2 k with k waves on its SIMD (FP64, 7 points: 20 us alone, 34 us by twos).
-// The side block is at most side_bytes.
-int plane_segment_count(const Mesh *m, int nq, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes,
-                        double *cost) {
-  const int vt = plane_vt(nq, lpt), per = plane_waves(nq, f64, lpt);
-  const int64_t waves = (int64_t)(m->phase_off[1] - m->phase_off[0]) * ((nlanes + vt - 1) / vt);
-  const int64_t plane = (int64_t)m->Mn[0] * m->Mn[1] * ldy * elem_bytes;
-  const int64_t cap = std::max<int64_t>(1, std::min<int64_t>(m->N[2], side_bytes / plane));
+// A wave (or block) walks its cells one after another, so a launch with few
+// columns and tiles leaves most of the device idle for the length of a column.
+// Its columns are then cut into segments (each segment's first plane, shared
+// with the one below, goes to a side block of planes laid out as Y's, added to
+// Y after the last colour phase).  The count is the one of least cost, summed
+// over the colour phases (odd cell counts have five small ones): rounds of the
+// device's units, per_unit items each, times cells per item.  An item's first
+// gather and last plane cost about half a cell; a cell takes about 1 + 2 k with
+// k waves on a SIMD (FP64, 7 points: 20 us alone, 34 us by twos).
+static int segment_count(const Mesh *m, int tiles, int units, int per_unit, int64_t cap, double *cost) {
   auto round = [](int64_t k) { return k ? 1.0 + 2.0 * k : 0.0; };
   int best = 1;
   double least = 0;
-  for (int64_t n = 1; n <= cap; ++n) {
-    const int64_t per_simd = (waves * n + PLANE_SIMDS - 1) / PLANE_SIMDS;
-    const double c = ((double)(per_simd / per) * round(per) + round(per_simd % per)) * ((m->N[2] + n - 1) / n + 0.5);
+  for (int64_t n = 1; n <= std::max<int64_t>(1, std::min<int64_t>(m->N[2], cap)); ++n) {
+    double c = 0;
+    for (int ph = 0; ph < m->nphase; ++ph) {
+      const int64_t k = ((int64_t)(m->phase_off[ph + 1] - m->phase_off[ph]) * tiles * n + units - 1) / units;
+      c += (double)(k / per_unit) * round(per_unit) + round(k % per_unit);
+    }
+    c *= (m->N[2] + n - 1) / n + 0.5;
     if (n == 1 || c < least) { best = (int)n; least = c; }
   }
   if (cost) *cost = least;
   return best;
 }
+
+static int64_t side_plane(const Mesh *m, int64_t ldy, int elem_bytes) { return (int64_t)m->Mn[0] * m->Mn[1] * ldy * elem_bytes; }
+
+int plane_segment_count(const Mesh *m, int nq, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes,
+                        double *cost) {
+  const int vt = plane_vt(nq, lpt);
+  return segment_count(m, (nlanes + vt - 1) / vt, 4 * DEVICE_CUS, plane_waves(nq, f64, lpt),
+                       side_bytes / side_plane(m, ldy, elem_bytes), cost);
+}
+
+// the same for the staged kernels: blocks on CUs
+int block_segment_count(const Mesh *m, int64_t ldy, int tiles, int per_cu, int elem_bytes, int64_t side_bytes) {
+  return segment_count(m, tiles, DEVICE_CUS, per_cu, side_bytes / side_plane(m, ldy, elem_bytes), nullptr);
+}
+
+int64_t side_limit(const LocalLaunch &L) { return L.side ? L.side_bytes : PLANE_SIDE_MAX; }
 
 bool plane_mesh(const Mesh *m) { return !m->offd && m->nq == m->np; }
 
@@ -60,7 +75,7 @@ bool plane_pairs_pay(const LocalBatch &B, int nq, size_t elem_bytes) {
   double one = 0, two = 0;
   for (int i = 0; i < B.n; ++i) {
     const LocalLaunch &L = B.Ls[i];
-    const int64_t side = L.side ? L.side_bytes : PLANE_SIDE_MAX;
+    const int64_t side = side_limit(L);
     double c1, c2;
     plane_segment_count(B.ms[i], nq, L.nlanes, L.ldy, false, 1, (int)elem_bytes, side, &c1);
     plane_segment_count(B.ms[i], nq, L.nlanes, L.ldy, false, 2, (int)elem_bytes, side, &c2);
@@ -71,18 +86,19 @@ bool plane_pairs_pay(const LocalBatch &B, int nq, size_t elem_bytes) {
 }
 
 // bytes of the side block of an application to a block of nlanes lanes with
-// leading dimension ldy (lanes), for either width of a thread, and for FE_BF16
-// with either block type: H where the plane kernels run it, and the mass
+// leading dimension ldy (lanes): for the plane kernels with either width of a
+// thread and, for FE_BF16, either block type; one segment per cell elsewhere
 int64_t plane_side_need(const Mesh *m, int nlanes, int64_t ldy, int prec) {
-  if (m->distorted || (!plane_mesh(m) && m->mass_kind != FE_MASS_CONSISTENT)) return 0;
-  const int nq = plane_mesh(m) ? m->nq : m->np;
   const bool f64 = prec == FE_F64;
   int64_t need = 0;
-  for (int lpt = 1; lpt <= (f64 ? 1 : 2); ++lpt)
-    for (int es = prec == FE_BF16 ? 2 : f64 ? 8 : 4; es <= (f64 ? 8 : 4); es *= 2) {
-      const int n = plane_segment_count(m, nq, nlanes, ldy, f64, lpt, es, PLANE_SIDE_MAX, nullptr);
-      if (n > 1) need = std::max(need, (int64_t)n * m->Mn[0] * m->Mn[1] * ldy * es);
+  for (int es = prec == FE_BF16 ? 2 : f64 ? 8 : 4; es <= (f64 ? 8 : 4); es *= 2) {
+    const int64_t plane = side_plane(m, ldy, es);
+    for (int lpt = 1; lpt <= (f64 ? 1 : 2); ++lpt) {
+      const int64_t n = plane_mesh(m) ? plane_segment_count(m, m->nq, nlanes, ldy, f64, lpt, es, PLANE_SIDE_MAX, nullptr)
+                                      : std::min<int64_t>(m->N[2], PLANE_SIDE_MAX / plane);
+      if (n > 1) need = std::max(need, n * plane);
     }
+  }
   return need;
 }
 
@@ -108,18 +124,17 @@ fe_status plane_side_leave(Mesh *m, hipStream_t s) {
   return FE_OK;
 }
 
-// The count for a launch and its side block: the launch's own, or the mesh's
+// The side block of a launch with n segments, and their count: the launch's own block, or the mesh's
 // (then *shared: enter and leave around the use).  A block that cannot be had
 // now (the stream is capturing, a captured graph holds the mesh's smaller one,
 // no memory) means one segment.
-int plane_segments(Mesh *m, const LocalLaunch &L, int nq, int lpt, int elem_bytes, hipStream_t s, void **side, bool *shared) {
-  const int n = plane_segment_count(m, nq, L.nlanes, L.ldy, L.prec == FE_F64, lpt, elem_bytes, L.side ? L.side_bytes : PLANE_SIDE_MAX, nullptr);
+int side_segments(Mesh *m, const LocalLaunch &L, int n, int elem_bytes, hipStream_t s, void **side, bool *shared) {
   *side = L.side;
   *shared = false;
   if (n == 1 || L.side) return n;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return 1;
-  const int64_t need = (int64_t)n * m->Mn[0] * m->Mn[1] * L.ldy * elem_bytes;
+  const int64_t need = n * side_plane(m, L.ldy, elem_bytes);
   if (m->ws_bytes[11] < need && (m->graphs > 0 || ensure_workspace(m, 11, need))) return 1;
   *side = m->ws[11];
   *shared = true;

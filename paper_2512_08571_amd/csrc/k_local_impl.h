@@ -9,26 +9,22 @@
 // even-odd decomposition (each thread applies one 1D matrix to one line of
 // points for one lane, table rows read as wave-uniform scalars) and the
 // quadrature-point stage of eqn refact, on LDS blocks [point][lane] (lanes
-// fastest).  With n_q = n_p and a diagonal metric (local_column_lines) the
-// gather X^(e) = Q^(e) X lands in registers as x-lines and seven passes run
-// per cell: N along x, N along y, [N along z + the z-direction stage] on
-// z-lines, the x-direction stage on x-lines, [the y-direction stage + N^T
-// along y] on y-lines, N^T along x, [N^T along z + scatter] on z-lines (the
-// transposed sweeps may run in any axis order and a line's owner can chain
-// two steps).  Otherwise (n_q > n_p, the general metric, or a per-cell core)
-// the block is staged in LDS first and every sweep is its own pass.
+// fastest); the block is staged in LDS and every sweep is its own pass.  These
+// kernels serve n_q > n_p and the general metric (sheared and distorted
+// cells); k_local_planes.h serves n_q = n_p with a diagonal metric.
 //
 // Scatter Y += Q^(e)T Y^(e) without atomics and deterministically:
-//  * along a_2 the shared node plane of consecutive cells is summed in
-//    registers (line-gather path) or LDS (and the periodic first/last plane
-//    of the column at the end);
+//  * along a_2 the shared node plane of consecutive cells is summed in LDS
+//    (and the periodic first/last plane of the column at the end);
 //  * across columns the columns are coloured 2 (or 3 for an odd count) per
 //    axis and launched colour by colour; a node shared by several columns is
 //    stored by the column of the lowest colour phase and read-modify-written
 //    by the later ones, so no two concurrently running workgroups touch the
 //    same node and the summation order is fixed.
 #pragma once
+#include <algorithm>
 #include <type_traits>
+#include <vector>
 
 #include "fe_internal.h"
 
@@ -342,67 +338,8 @@ __device__ __forceinline__ void grad_pass(const TC *__restrict__ src, TC *__rest
   }
 }
 
-// x-lines of the interpolated field src: dst += the x-direction contribution
-template <int NQ, int VT, bool CPLX, int NT, typename TC>
-__device__ __forceinline__ void xdir_pass(const TC *__restrict__ src, TC *__restrict__ dst, const TC *tD,
-                                          const TC *tDT, const TC *tgw, const TC *tkw, const KArgs<TC> &a,
-                                          const TC *__restrict__ C, const TC *__restrict__ W2, int lane0) {
-  constexpr int NQ2 = NQ * NQ;
-  for (int t = threadIdx.x; t < NQ2 * VT; t += NT) {
-    const int v = t % VT, l = t / VT;
-    const int base = l * NQ;
-    TC u[NQ], o[NQ];
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) u[i] = src[(base + i) * VT + v];
-    dir_line<0, NQ, VT, CPLX>(u, o, l, base, 1, tD, tDT, tgw, tkw, a, C, W2, lane0 + v);
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) dst[(base + i) * VT + v] += o[i];
-  }
-}
-
-// z-lines (NP = NQ): interpolation along z of buf (N_x, N_y already applied)
-// written to u, and the z-direction contribution written over buf's line
-template <int NQ, int VT, bool CPLX, int NT, typename TC>
-__device__ __forceinline__ void zpass(TC *__restrict__ buf, TC *__restrict__ uout, const TC *tN, const TC *tD,
-                                      const TC *tDT, const TC *tgw, const TC *tkw, const KArgs<TC> &a,
-                                      const TC *__restrict__ C, const TC *__restrict__ W2, int lane0) {
-  constexpr int NQ2 = NQ * NQ;
-  for (int t = threadIdx.x; t < NQ2 * VT; t += NT) {
-    const int v = t % VT, l = t / VT;
-    TC x[NQ], u[NQ], o[NQ];
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) x[i] = buf[(l + i * NQ2) * VT + v];
-    eo_apply<NQ, NQ, 1>(scalar_table(tN), x, u);
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) uout[(l + i * NQ2) * VT + v] = u[i];
-    dir_line<2, NQ, VT, CPLX>(u, o, l, l, NQ2, tD, tDT, tgw, tkw, a, C, W2, lane0 + v);
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) buf[(l + i * NQ2) * VT + v] = o[i];
-  }
-}
-
-// y-lines (NP = NQ): the y-direction contribution of u completes the sum in
-// acc; the transposed interpolation along y of the complete line is written
-// over u's line
-template <int NQ, int VT, bool CPLX, int NT, typename TC>
-__device__ __forceinline__ void ypass(TC *__restrict__ u_io, const TC *__restrict__ acc, const TC *tNT, const TC *tD,
-                                      const TC *tDT, const TC *tgw, const TC *tkw, const KArgs<TC> &a,
-                                      const TC *__restrict__ C, const TC *__restrict__ W2, int lane0) {
-  constexpr int NQ2 = NQ * NQ;
-  for (int t = threadIdx.x; t < NQ2 * VT; t += NT) {
-    const int v = t % VT, l = t / VT;
-    const int base = (l / NQ) * NQ2 + (l % NQ);
-    TC u[NQ], o[NQ], y[NQ];
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) u[i] = u_io[(base + i * NQ) * VT + v];
-    dir_line<1, NQ, VT, CPLX>(u, o, l, base, NQ, tD, tDT, tgw, tkw, a, C, W2, lane0 + v);
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) o[i] += acc[(base + i * NQ) * VT + v];
-    eo_apply<NQ, NQ, 1>(scalar_table(tNT), o, y);
-#pragma unroll
-    for (int i = 0; i < NQ; ++i) u_io[(base + i * NQ) * VT + v] = y[i];
-  }
-}
+// first cell of segment s of a column of n cells cut into nseg
+__device__ __host__ __forceinline__ int seg_start(int s, int n, int nseg) { return (int)((int64_t)s * n / nseg); }
 
 __device__ __forceinline__ int colour_of(int c, int n) { return ((n & 1) && c == n - 1) ? 2 : (c & 1); }
 
@@ -414,316 +351,19 @@ template <int NQ, int VT, typename TC> struct BlockSize {
   static constexpr int raw = ((NQ * NQ * VT + 63) / 64) * 64;
   static constexpr int value = raw > MaxThreads<TC>::value ? MaxThreads<TC>::value : (raw < 128 ? 128 : raw);
 };
-// A per-cell core (the sweeps of one cell between the staged block and the
-// completed Y^(e)) other than the line passes below sets its own block size
-// and may ask for LDS elements after the line weights.
-template <class Core> struct CoreLds { static constexpr int elems = Core::extra_lds_elems; };
-template <> struct CoreLds<void> { static constexpr int elems = 0; };
-template <int NQ, int VT, typename TC, class Core> struct Threads { static constexpr int value = Core::threads; };
-template <int NQ, int VT, typename TC> struct Threads<NQ, VT, TC, void> {
-  static constexpr int value = BlockSize<NQ, VT, TC>::value;
-};
 
-// The line-gather path below serves FP64 with n_q = n_p and no per-cell core,
-// except complex blocks at n_p = 8.  FP32 / BF16 blocks keep the staged path:
-// their 16-byte element loads and stores (four or eight lanes per access) beat
-// single-lane lines (FP32 filter steps, Mid operator, 512 vectors: 259 vs
-// 313 ms per pass).  At n_p = 8 the 64 lines of a pass fill whole waves on
-// either path, and complex blocks run 3.7% faster staged (12^3 cells, p = 7,
-// 128 complex vectors, best tile each: 0.619 vs 0.642 ms per colour phase);
-// real blocks there, and every other n_p measured (4, 6, 7, 9), run as fast
-// or faster on lines (n_p = 7: 0.65 vs 0.79 ms on the Mid operator).
-template <int NP, int NQ, typename TC, class Core, bool CPLX> struct LinesPath {
-  static constexpr bool value =
-      std::is_void<Core>::value && NP == NQ && std::is_same<TC, double>::value && !(CPLX && NP == 8);
-};
-
-// One work item on the line-gather path (n_q = n_p, diagonal metric, no
-// per-cell core): the cell's block is gathered from X straight into x-lines
-// (registers) and the completed Y^(e) leaves from z-lines (registers), so
-// there is no staging pass through LDS, the node plane shared by consecutive
-// cells of the column stays in registers (its z-line belongs to the same
-// thread in every cell), and a cell takes six barriers.  Every thread keeps
-// the same (line, lane) items in all passes, so their line bases are computed
-// once per work item.  Passes (LDS A, B = [point][lane]):
-//   1  x-lines: N along x of the gathered lines          (regs -> B)
-//   2  y-lines: N along y                                (B -> A)
-//   3  z-lines: N along z + the z-direction stage        (A -> u in B, z part in A)
-//   4  x-lines: the x-direction stage                    (B -> A, added)
-//   5  y-lines: the y-direction stage + N^T along y      (B, A -> B)
-//   6  x-lines: N^T along x                              (B -> A)
-//   7  z-lines: N^T along z, the carried plane, scatter  (A -> regs -> Y)
-// The next cell's lines, D^-1 entries, coefficients and the values this
-// cell's scatter reads back are loaded after pass 5 and land during 6 and 7.
-template <int NP, int VT, bool CPLX, typename TS, typename TC, int NT>
-__device__ __forceinline__ void local_column_lines(const KArgs<TC> &a, const int col, const int tile) {
-  constexpr int NQ = NP, NP2 = NP * NP, NQ2 = NP2, NQ3 = NP2 * NP;
-  constexpr int NI = NQ2 * VT;                      // (line, lane) items of a pass
-  constexpr int IT = (NI + NT - 1) / NT;            // items per thread
-  constexpr int CPT = (4 * NQ3 + NT - 1) / NT;      // coefficients per thread
-  constexpr int OFF_N = 0;
-  constexpr int OFF_NT = OFF_N + ((NQ + 1) / 2) * NP;
-  constexpr int OFF_D = OFF_NT + ((NP + 1) / 2) * NQ;
-  constexpr int OFF_DT = OFF_D + ((NQ + 1) / 2) * NQ;
-  constexpr int OFF_GW = OFF_DT + ((NQ + 1) / 2) * NQ;
-  constexpr int OFF_KW = OFF_GW + 3 * NQ;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  TC *A = reinterpret_cast<TC *>(smem_raw);
-  TC *B = A + NQ3 * VT;
-  TC *Cf = B + NQ3 * VT;             // cell coefficients [4][NQ3]
-  TC *W2 = Cf + 4 * NQ3;             // w_a w_b per line [NQ2]
-
-  const int cx = a.cols[2 * col], cy = a.cols[2 * col + 1];
-  const int lane0 = tile * VT;
-  const int tid = threadIdx.x;
-  const TS *__restrict__ X = (const TS *)a.X;
-  TS *__restrict__ Y = (TS *)a.Y;
-  const TC *tN = a.tab + OFF_N, *tNT = a.tab + OFF_NT, *tD = a.tab + OFF_D, *tDT = a.tab + OFF_DT;
-  const TC *tGW = a.tab + OFF_GW, *tKW = a.tab + OFF_KW;
-  const int p = a.p;
-  const int xoff = a.dmask & 1, yoff = (a.dmask >> 1) & 1, zoff = (a.dmask >> 2) & 1;
-  const int ax = colour_of(cx, a.N0), by = colour_of(cy, a.N1);
-  const int axl = colour_of(cx == 0 ? a.N0 - 1 : cx - 1, a.N0);
-  const int axr = colour_of(cx == a.N0 - 1 ? 0 : cx + 1, a.N0);
-  const int byl = colour_of(cy == 0 ? a.N1 - 1 : cy - 1, a.N1);
-  const int byr = colour_of(cy == a.N1 - 1 ? 0 : cy + 1, a.N1);
-  // node coordinate along an axis: cell c, local index i; periodic axes wrap,
-  // a Dirichlet axis numbers its interior nodes g - 1 and has no DoF on its faces
-  auto coord = [&](int c, int i, int off, int M, bool &in) {
-    int g = c * p + i - off;
-    if (off) in = in && g >= 0 && g < M;
-    else if (g >= M) g -= M;
-    return g;
-  };
-
-  // per item: line l = t / VT, lane v = t % VT; the gather x-line is
-  // (j, k) = (l % NP, l / NP), the scatter z-line (i, j) = (l % NP, l / NP)
-  int gxs[IT], gys[IT];      // scatter: node x and y of the z-line
-  int gyg[IT], kg[IT];       // gather: node y and plane k of the x-line
-  int flags[IT];             // bit 0 lane in range, 1 gather y in range, 2 scatter x/y in range, 3 read-modify-write
-#pragma unroll
-  for (int r = 0; r < IT; ++r) {
-    const int t = tid + r * NT;
-    const int l = t / VT, v = t % VT;
-    const bool item = t < NI && lane0 + v < a.nlanes;
-    bool ing = true, ins = true;
-    gyg[r] = coord(cy, l % NP, yoff, a.M1, ing);
-    kg[r] = l / NP;
-    const int i = l % NP, j = l / NP;
-    gxs[r] = coord(cx, i, xoff, a.M0, ins);
-    gys[r] = coord(cy, j, yoff, a.M1, ins);
-    const bool xs = (i == 0) || (i == NP - 1), ys = (j == 0) || (j == NP - 1);
-    const int axo = (i == 0) ? axl : axr, byo = (j == 0) ? byl : byr;
-    const bool rmw = !((!xs || ax < axo) && (!ys || by < byo));
-    flags[r] = (item ? 1 : 0) | (ing ? 2 : 0) | (ins ? 4 : 0) | (rmw ? 8 : 0);
-  }
-  const int64_t MM = (int64_t)a.M0 * a.M1;
-  int ll[IT], vv[IT], py[IT];   // line index, lane, first point of the y-line
-#pragma unroll
-  for (int r = 0; r < IT; ++r) {
-    const int t = tid + r * NT;
-    ll[r] = t / VT;
-    vv[r] = t % VT;
-    py[r] = (ll[r] / NQ) * NQ2 + ll[r] % NQ;
-  }
-
-  for (int t = tid; t < NQ2; t += NT) W2[t] = a.wq[t];
-  TC xl[IT][NP], dl[IT][NP], cpre[CPT], ypre[IT][NP];
-  // the gathered x-lines of cell cz (and their D^-1 entries) and its coefficients
-  auto prefetch = [&](int cz) {
-#pragma unroll
-    for (int r = 0; r < IT; ++r) {
-      const int v = vv[r];
-      bool in = (flags[r] & 3) == 3;
-      const int gz = coord(cz, kg[r], zoff, a.M2, in);
-      const int64_t row = (int64_t)gyg[r] * a.M0 + MM * gz;
-#pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        bool ini = in;
-        const int gx = coord(cx, i, xoff, a.M0, ini);
-        xl[r][i] = 0;
-        dl[r][i] = 1;
-        if (ini) {
-          xl[r][i] = Cvt<TS, TC>::ld(X, (row + gx) * a.ldx + lane0 + v);
-          if (a.dinv) dl[r][i] = (TC)a.dinv[row + gx];
-        }
-      }
-    }
-    const TC *src = a.coef + (cx + (int64_t)a.N0 * (cy + (int64_t)a.N1 * cz)) * a.coef_cell;
-    const int nst = (a.ncoef < 4 ? a.ncoef : 4) * NQ3;
-#pragma unroll
-    for (int r = 0; r < CPT; ++r) {
-      const int e = tid + r * NT;
-      cpre[r] = e < nst ? src[e] : (TC)0;
-    }
-  };
-  auto stage_coef = [&]() {
-#pragma unroll
-    for (int r = 0; r < CPT; ++r) {
-      const int e = tid + r * NT;
-      if (e < 4 * NQ3) Cf[e] = cpre[r];
-    }
-  };
-  prefetch(0);
-  stage_coef();
-  TC carry[IT], first[IT];
-#pragma unroll
-  for (int r = 0; r < IT; ++r) carry[r] = first[r] = 0;
-
-  for (int cz = 0; cz < a.N2; ++cz) {
-    const int kskip0 = (cz == 0) ? 0 : -1;             // plane held back for the wrap
-    const int kskip1 = (cz < a.N2 - 1) ? NP - 1 : -1;  // plane carried to the next cell
-    // 1: N along x of the gathered lines (D^-1 applied first in filter steps)
-#pragma unroll
-    for (int r = 0; r < IT; ++r) {
-      const int t = tid + r * NT;
-      if (t < NI) {
-        const int v = vv[r], l = ll[r];
-        TC x[NP], y[NQ];
-#pragma unroll
-        for (int i = 0; i < NP; ++i) x[i] = xl[r][i] * dl[r][i];
-        eo_apply<NP, NQ, 1>(scalar_table(tN), x, y);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) B[(l * NQ + q) * VT + v] = y[q];
-      }
-    }
-    __syncthreads();
-    // 2: N along y
-#pragma unroll
-    for (int r = 0; r < IT; ++r) {
-      if (tid + r * NT >= NI) break;
-      const int ey = py[r] * VT + vv[r];
-      TC x[NP], y[NQ];
-#pragma unroll
-      for (int i = 0; i < NP; ++i) x[i] = B[ey + i * NQ * VT];
-      eo_apply<NP, NQ, 1>(scalar_table(tN), x, y);
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) A[ey + q * NQ * VT] = y[q];
-    }
-    __syncthreads();
-    // 3: z sweep fused with the z-direction stage: u -> B, z part -> A
-#pragma unroll
-    for (int r = 0; r < IT; ++r) {
-      if (tid + r * NT >= NI) break;
-      const int ez = ll[r] * VT + vv[r];
-      TC x[NQ], u[NQ], o[NQ];
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) x[i] = A[ez + i * NQ2 * VT];
-      eo_apply<NQ, NQ, 1>(scalar_table(tN), x, u);
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) B[ez + i * NQ2 * VT] = u[i];
-      dir_line<2, NQ, VT, CPLX>(u, o, ll[r], ll[r], NQ2, tD, tDT, tGW, tKW, a, Cf, W2, lane0 + vv[r]);
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) A[ez + i * NQ2 * VT] = o[i];
-    }
-    __syncthreads();
-    // 4: the x-direction stage added into A
-#pragma unroll
-    for (int r = 0; r < IT; ++r) {
-      if (tid + r * NT >= NI) break;
-      const int ex = ll[r] * NQ * VT + vv[r];
-      TC u[NQ], o[NQ];
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) u[i] = B[ex + i * VT];
-      dir_line<0, NQ, VT, CPLX>(u, o, ll[r], ll[r] * NQ, 1, tD, tDT, tGW, tKW, a, Cf, W2, lane0 + vv[r]);
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) A[ex + i * VT] += o[i];
-    }
-    __syncthreads();
-    // 5: the y-direction stage completes the sum; N^T along y (-> B)
-#pragma unroll
-    for (int r = 0; r < IT; ++r) {
-      if (tid + r * NT >= NI) break;
-      const int ey = py[r] * VT + vv[r];
-      TC u[NQ], o[NQ], y[NP];
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) u[i] = B[ey + i * NQ * VT];
-      dir_line<1, NQ, VT, CPLX>(u, o, ll[r], py[r], NQ, tD, tDT, tGW, tKW, a, Cf, W2, lane0 + vv[r]);
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) o[i] += A[ey + i * NQ * VT];
-      eo_apply<NQ, NP, 1>(scalar_table(tNT), o, y);
-#pragma unroll
-      for (int i = 0; i < NP; ++i) B[ey + i * NQ * VT] = y[i];
-    }
-    // the next cell's lines and coefficients, and this cell's read-back values
-    if (cz + 1 < a.N2) prefetch(cz + 1);
-#pragma unroll
-    for (int r = 0; r < IT; ++r) {
-      const int v = vv[r];
-      const bool rm = (flags[r] & 13) == 13;
-#pragma unroll
-      for (int k = 0; k < NP; ++k) {
-        ypre[r][k] = 0;
-        bool in = rm && k != kskip0 && k != kskip1;
-        const int gz = coord(cz, k, zoff, a.M2, in);
-        if (in) ypre[r][k] = Cvt<TS, TC>::ld(Y, (gxs[r] + (int64_t)gys[r] * a.M0 + MM * gz) * a.ldy + lane0 + v);
-      }
-    }
-    __syncthreads();
-    // 6: N^T along x (B -> A)
-#pragma unroll
-    for (int r = 0; r < IT; ++r) {
-      if (tid + r * NT >= NI) break;
-      const int ex = ll[r] * NQ * VT + vv[r];
-      TC x[NQ], y[NP];
-#pragma unroll
-      for (int i = 0; i < NQ; ++i) x[i] = B[ex + i * VT];
-      eo_apply<NQ, NP, 1>(scalar_table(tNT), x, y);
-#pragma unroll
-      for (int i = 0; i < NP; ++i) A[ex + i * VT] = y[i];
-    }
-    __syncthreads();
-    // 7: N^T along z of the z-lines, the shared planes, the scatter
-#pragma unroll
-    for (int r = 0; r < IT; ++r) {
-      const int t = tid + r * NT;
-      if (t < NI) {
-        const int v = vv[r], l = ll[r];
-        TC z[NQ], y[NP];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) z[q] = A[(l + q * NP2) * VT + v];
-        eo_apply<NQ, NP, 1>(scalar_table(tNT), z, y);
-        // plane 0 takes the carry (or, in the column's first cell, is held
-        // back); plane NP-1 is carried, or in the last cell takes the first plane
-        if (cz == 0) first[r] = y[0];
-        else y[0] += carry[r];
-        if (cz == a.N2 - 1) y[NP - 1] += (cz == 0) ? y[0] : first[r];
-        carry[r] = y[NP - 1];
-        if (flags[r] & 1 && flags[r] & 4) {
-#pragma unroll
-          for (int k = 0; k < NP; ++k) {
-            bool in = k != kskip0 && k != kskip1;
-            const int gz = coord(cz, k, zoff, a.M2, in);
-            if (in)
-              Cvt<TS, TC>::st(Y, (gxs[r] + (int64_t)gys[r] * a.M0 + MM * gz) * a.ldy + lane0 + v,
-                              (flags[r] & 8) ? ypre[r][k] + y[k] : y[k]);
-          }
-        }
-      }
-    }
-    if (cz + 1 < a.N2) stage_coef();
-  }
-  __syncthreads();
-}
-
-// One work item: the column (cx, cy) = a.cols[col] of cells along a_2 for
-// vector lanes [tile VT, tile VT + VT).  Ends with a barrier, so the block may
+// One work item: segment seg of the column (cx, cy) = a.cols[col] of cells
+// along a_2 for vector lanes [tile VT, tile VT + VT).  Ends with a barrier, so the block may
 // start another item right away.
 //
 // Block elements: LPE consecutive lanes of one node (LPE = 1, or the 16-byte
 // wide form when every block, leading dimension and lane count is aligned to
 // it), so a node's VT lanes are VT / LPE elements and one element is one
 // global and one LDS vector access.
-template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, int LPE, bool SH, class Core = void>
-__device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, const int tile) {
+template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, int LPE, bool SH>
+__device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, const int seg, const int tile) {
   constexpr int NP2 = NP * NP, NP3 = NP2 * NP, NQ2 = NQ * NQ, NQ3 = NQ2 * NQ;
-  constexpr int NT = Threads<NQ, VT, TC, Core>::value;
-  if constexpr (LinesPath<NP, NQ, TC, Core, CPLX>::value) {
-    if (!SH || !a.offd) {
-      local_column_lines<NP, VT, CPLX, TS, TC, NT>(a, col, tile);
-      return;
-    }
-  }
+  constexpr int NT = BlockSize<NQ, VT, TC>::value;
   static_assert(VT <= 255 && NP <= 15, "packed element metadata holds lane offsets < 256 and planes < 16");
   static_assert(VT % LPE == 0, "the vector tile must hold whole elements");
   static_assert(NQ >= NP, "n_q >= n_p");
@@ -747,6 +387,7 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
   TC *T3 = W2 + NQ2;                 // [3][NQ3][VT] gradients (sheared boxes only)
 
   const int cx = a.cols[2 * col], cy = a.cols[2 * col + 1];
+  const int c0 = seg_start(seg, a.N2, a.nseg), c1 = seg_start(seg + 1, a.N2, a.nseg);
   const int lane0 = tile * VT;
   const int tid = threadIdx.x;
   const TS *__restrict__ X = (const TS *)a.X;
@@ -793,11 +434,15 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
     if (!zoff && gz >= a.M2) gz -= a.M2;
     return (int64_t)exy[r] + MM * gz;
   };
+  // where this thread's node row is written: Y, or for the first plane of one
+  // of several segments the side block (planes laid out as Y's)
+  auto row_of = [&](int r, int cz, bool first) -> TS * {
+    return first && ek(r) == 0 ? (TS *)a.side + ((int64_t)exy[r] + MM * seg) * a.ldy : Y + node_of(r, cz) * a.ldy;
+  };
   // plane k of cell cz holds DoFs (always on a periodic a_2)
   auto zin = [&](int k, int cz) { const int gz = cz * p + k - zoff; return !zoff || (gz >= 0 && gz < a.M2); };
 
   for (int t = tid; t < NQ2; t += NT) W2[t] = a.wq[t];
-  if constexpr (!std::is_void<Core>::value) Core::begin(W2 + NQ2, a);   // read after the first barrier
   // dpre: the node's D^-1 entry (filter steps), applied when the block is
   // staged so that its load stays in flight with the others
   TC xpre[XPT][LPE], dpre[XPT], cpre[CPT], ypre[XPT][LPE];
@@ -821,9 +466,10 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
       cpre[r] = e < nst ? src[e] : (TC)0;
     }
   };
-  prefetch(0);
+  const bool one = a.nseg == 1;
+  prefetch(c0);
 
-  for (int cz = 0; cz < a.N2; ++cz) {
+  for (int cz = c0; cz < c1; ++cz) {
     // stage X^(e) = Q^(e) X -> A[k][j][i][lane] and the coefficients -> Cf
 #pragma unroll
     for (int r = 0; r < XPT; ++r) {
@@ -839,34 +485,32 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
       const int e = tid + r * NT;
       if (e < NCF * NQ3) Cf[e] = cpre[r];
     }
-    const int kskip0 = (cz == 0) ? 0 : -1;             // plane held back for the wrap
-    const int kskip1 = (cz < a.N2 - 1) ? NP - 1 : -1;  // plane carried to the next cell
+    const int kskip0 = (one && cz == 0) ? 0 : -1;      // plane held back for the wrap
+    const int kskip1 = (cz < c1 - 1) ? NP - 1 : -1;    // plane carried to the next cell
+    const bool first = !one && cz == c0;               // plane 0 goes to the side block
     __syncthreads();
-    // Y0 = (N x N x N) X^(e): along x and y here (a core does all its sweeps)
-    if constexpr (std::is_void<Core>::value) {
-      line_pass<NP, NQ, 1, VT, NT>(A, B, tN, NP2, [](int l, int &sb, int &ss, int &db, int &ds) {
-        sb = l * NP; ss = 1; db = l * NQ; ds = 1; });
-      __syncthreads();
-      line_pass<NP, NQ, 1, VT, NT>(B, A, tN, NP * NQ, [](int l, int &sb, int &ss, int &db, int &ds) {
-        const int k = l / NQ, q1 = l % NQ;
-        sb = k * NP * NQ + q1; ss = NQ; db = k * NQ2 + q1; ds = NQ; });
-      __syncthreads();
-    }
+    // Y0 = (N x N x N) X^(e): along x and y
+    line_pass<NP, NQ, 1, VT, NT>(A, B, tN, NP2, [](int l, int &sb, int &ss, int &db, int &ds) {
+      sb = l * NP; ss = 1; db = l * NQ; ds = 1; });
+    __syncthreads();
+    line_pass<NP, NQ, 1, VT, NT>(B, A, tN, NP * NQ, [](int l, int &sb, int &ss, int &db, int &ds) {
+      const int k = l / NQ, q1 = l % NQ;
+      sb = k * NP * NQ + q1; ss = NQ; db = k * NQ2 + q1; ds = NQ; });
+    __syncthreads();
     // next cell's block and coefficients, and the values this cell will
     // read-modify-write (stored by earlier phases), in flight from here on
     auto prefetch_next = [&]() {
-      if (cz + 1 < a.N2) prefetch(cz + 1);
+      if (cz + 1 < c1) prefetch(cz + 1);
 #pragma unroll
       for (int r = 0; r < XPT; ++r) {
 #pragma unroll
         for (int jj = 0; jj < LPE; ++jj) ypre[r][jj] = 0;
         if (eok(r) && ermw(r) && ek(r) != kskip0 && ek(r) != kskip1 && zin(ek(r), cz))
-          VecIO<TS, TC, LPE>::ld(Y + node_of(r, cz) * a.ldy + elane(r), ypre[r]);
+          VecIO<TS, TC, LPE>::ld(row_of(r, cz, first) + elane(r), ypre[r]);
       }
     };
-    // every sweep its own pass: n_q > n_p (the line lengths change between
-    // the sweeps), or a sheared box (the off-diagonal metric needs all three
-    // gradients at a point, staged in T3 first)
+    // every sweep its own pass; the off-diagonal metric needs all three
+    // gradients at a point, staged in T3 first
     auto separate_passes = [&](auto offd_tag) {
       constexpr bool OFFD = decltype(offd_tag)::value;
       line_pass<NP, NQ, 1, VT, NT>(A, B, tN, NQ2, [](int l, int &sb, int &ss, int &db, int &ds) {
@@ -895,54 +539,33 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
         sb = l * NQ; ss = 1; db = l * NP; ds = 1; });
       __syncthreads();
     };
-    if constexpr (!std::is_void<Core>::value) {
-      // the seven sweeps of the cell by the core (n_q = n_p, diagonal metric)
-      Core::template cell<NP, VT, CPLX>(A, B, Cf, W2, a, lane0, prefetch_next);
-    } else if (SH && a.offd) {
-      if constexpr (SH) separate_passes(std::true_type{});
-    } else if constexpr (NP != NQ) {
-      separate_passes(std::false_type{});
+    if constexpr (SH) {
+      if (a.offd) separate_passes(std::true_type{});
+      else separate_passes(std::false_type{});
     } else {
-      // z sweep fused with the z-direction quadrature work: u -> B, z part -> A
-      zpass<NQ, VT, CPLX, NT>(A, B, tN, tD, tDT, tGW, tKW, a, Cf, W2, lane0);
-      __syncthreads();
-      // x-direction quadrature work added into A
-      xdir_pass<NQ, VT, CPLX, NT>(B, A, tD, tDT, tGW, tKW, a, Cf, W2, lane0);
-      prefetch_next();
-      __syncthreads();
-      // y-direction work completes the sum; its owner applies N^T along y (-> B)
-      ypass<NQ, VT, CPLX, NT>(B, A, tNT, tD, tDT, tGW, tKW, a, Cf, W2, lane0);
-      __syncthreads();
-      // the rest of Y^(e) = (N x N x N)^T Z: along x (B -> A), then z (A -> B)
-      line_pass<NQ, NP, 1, VT, NT>(B, A, tNT, NP * NQ, [](int l, int &sb, int &ss, int &db, int &ds) {
-        sb = l * NQ; ss = 1; db = l * NP; ds = 1; });
-      __syncthreads();
-      line_pass<NQ, NP, 1, VT, NT>(A, B, tNT, NP2, [](int l, int &sb, int &ss, int &db, int &ds) {
-        sb = l; ss = NQ * NP; db = l; ds = NP2; });
-      __syncthreads();
+      separate_passes(std::false_type{});
     }
     // node planes shared along a_2: plane 0 takes the carry, plane NP-1 is
     // carried (or, in the last cell, takes the column's first plane)
     for (int t = tid; t < NP2 * VT; t += NT) {
       TC *top = B + (NP - 1) * NP2 * VT;
-      if (cz == 0) Yfst[t] = B[t];
-      else B[t] += Ycar[t];
-      if (cz == a.N2 - 1) top[t] += (cz == 0) ? B[t] : Yfst[t];
+      if (cz != c0) B[t] += Ycar[t];
+      else if (one) Yfst[t] = B[t];
+      if (one && cz == a.N2 - 1) top[t] += (cz == 0) ? B[t] : Yfst[t];
     }
     __syncthreads();
-    if (cz < a.N2 - 1)
+    if (cz < c1 - 1)
       for (int t = tid; t < NP2 * VT; t += NT) Ycar[t] = B[(NP - 1) * NP2 * VT + t];
     // write the completed planes: store (first phase) or read-modify-write
 #pragma unroll
     for (int r = 0; r < XPT; ++r) {
       if (!eok(r) || ek(r) == kskip0 || ek(r) == kskip1 || !zin(ek(r), cz)) continue;
       const int e = tid + r * NT;
-      const int64_t g = node_of(r, cz);
       TC val[LPE], out[LPE];
       LdsVec<TC, LPE>::ld(B + e * LPE, val);
 #pragma unroll
       for (int jj = 0; jj < LPE; ++jj) out[jj] = ermw(r) ? ypre[r][jj] + val[jj] : val[jj];
-      VecIO<TS, TC, LPE>::st(Y + g * a.ldy + elane(r), out);
+      VecIO<TS, TC, LPE>::st(row_of(r, cz, first) + elane(r), out);
     }
     __syncthreads();
   }
@@ -963,15 +586,34 @@ __device__ __forceinline__ int xcd_item(int b, int grid) { return (b & 7) * (gri
 template <int NP, int NQ, typename TC> struct LocalWaves {
   static constexpr int value = std::is_same<TC, double>::value && (NP >= 7 || NQ >= 8) ? 2 : 4;
 };
-#define FEHX_LOCAL_BOUNDS __launch_bounds__((Threads<NQ, VT, TC, Core>::value)) __attribute__((amdgpu_waves_per_eu(LocalWaves<NP, NQ, TC>::value)))
+#define FEHX_LOCAL_BOUNDS __launch_bounds__((BlockSize<NQ, VT, TC>::value)) __attribute__((amdgpu_waves_per_eu(LocalWaves<NP, NQ, TC>::value)))
 
-// One system, one colour phase: one block per (column, tile).
-template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, int LPE, bool SH, class Core = void>
+template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, int LPE, bool SH>
+__device__ __forceinline__ void local_item(const KArgs<TC> &a, int w) {
+  const int cs = w / a.ntiles, tile = w - cs * a.ntiles;
+  const int col = cs / a.nseg;
+  local_column<NP, NQ, VT, CPLX, TS, TC, LPE, SH>(a, col, cs - col * a.nseg, tile);
+}
+
+// Y += the segments' first planes: plane seg of the side block to the plane
+// of Y at that segment's first node; one block per node row
+template <typename TS, typename TC>
+__global__ void k_planes_join(TS *__restrict__ Y, const TS *__restrict__ side, int64_t plane, int nseg, int N2, int p,
+                              int zoff, int64_t ldy, int nlanes) {
+  const int sg = blockIdx.y;
+  const int64_t gz = (int64_t)seg_start(sg, N2, nseg) * p - zoff;
+  if (gz < 0) return;                            // a Dirichlet face: no DoFs
+  TS *q = Y + gz * plane + blockIdx.x * ldy;
+  const TS *r = side + sg * plane + blockIdx.x * ldy;
+  for (int l = threadIdx.x; l < nlanes; l += blockDim.x) Cvt<TS, TC>::st(q, l, Cvt<TS, TC>::ld(q, l) + Cvt<TS, TC>::ld(r, l));
+}
+
+// One system, one colour phase: one block per (column, segment, tile).
+template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, int LPE, bool SH>
 __global__ void FEHX_LOCAL_BOUNDS k_local(KArgs<TC> a) {
   const int w = xcd_item(blockIdx.x, gridDim.x);
-  if (w >= a.ncols * a.ntiles) return;
-  const int col = w / a.ntiles;
-  local_column<NP, NQ, VT, CPLX, TS, TC, LPE, SH, Core>(a, col, w - col * a.ntiles);
+  if (w >= a.ncols * a.nseg * a.ntiles) return;
+  local_item<NP, NQ, VT, CPLX, TS, TC, LPE, SH>(a, w);
 }
 
 // Several systems of one class (n_p, n_q, precision, real/complex), one colour
@@ -984,17 +626,14 @@ template <typename TC> struct BatchArgs {
   KArgs<TC> sys[LOCAL_MAXB];
 };
 
-template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, int LPE, bool SH, class Core = void>
+template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, int LPE, bool SH>
 __global__ void FEHX_LOCAL_BOUNDS k_local_batch(BatchArgs<TC> B) {
   for (int base = 0; base < B.total; base += gridDim.x) {
     const int w = base + xcd_item(blockIdx.x, gridDim.x);
     if (w >= B.total) return;
     int sidx = 0;
     while (sidx + 1 < B.nsys && w >= B.off[sidx + 1]) ++sidx;
-    const KArgs<TC> &a = B.sys[sidx];
-    const int lw = w - B.off[sidx];
-    const int col = lw / a.ntiles;
-    local_column<NP, NQ, VT, CPLX, TS, TC, LPE, SH, Core>(a, col, lw - col * a.ntiles);
+    local_item<NP, NQ, VT, CPLX, TS, TC, LPE, SH>(B.sys[sidx], w - B.off[sidx]);
   }
 }
 
@@ -1031,20 +670,46 @@ template <typename TC> KArgs<TC> make_args(Mesh *m, const LocalLaunch &L, int vt
   return a;
 }
 
+// Arguments of every system with its segments (count(mesh, launch, tiles)) and
+// side block; segments_end adds the segments' first planes to Y.
+template <typename TS, typename TC, typename Count>
+inline fe_status segments_begin(const LocalBatch &Bt, int vt, Count count, std::vector<KArgs<TC>> &as,
+                                std::vector<int> &waits, hipStream_t s) {
+  for (int i = 0; i < Bt.n; ++i) {
+    Mesh *m = Bt.ms[i];
+    as.push_back(make_args<TC>(m, Bt.Ls[i], vt));
+    const int n = count(m, Bt.Ls[i], as.back().ntiles);
+    bool shared = false;
+    as.back().nseg = side_segments(m, Bt.Ls[i], n, sizeof(TS), s, &as.back().side, &shared);
+    if (shared) {
+      const fe_status st = plane_side_enter(m, s);
+      if (st) return st;
+      waits.push_back(i);
+    }
+  }
+  return FE_OK;
+}
+template <typename TS, typename TC>
+inline fe_status segments_end(const LocalBatch &Bt, const std::vector<KArgs<TC>> &as, const std::vector<int> &waits, hipStream_t s) {
+  for (const KArgs<TC> &a : as) {
+    if (a.nseg == 1) continue;
+    const int rows = a.M0 * a.M1;
+    hipLaunchKernelGGL((k_planes_join<TS, TC>), dim3(rows, a.nseg), dim3(a.nlanes <= 64 ? 64 : 256), 0, s, (TS *)a.Y,
+                       (const TS *)a.side, rows * a.ldy, a.nseg, a.N2, a.p, a.dmask & 4 ? 1 : 0, a.ldy, a.nlanes);
+    FE_HIP_TRY(hipGetLastError());
+  }
+  for (int i : waits) {
+    const fe_status st = plane_side_leave(Bt.ms[i], s);
+    if (st) return st;
+  }
+  return FE_OK;
+}
+
 // LDS per workgroup on gfx950; tiles whose block cannot fit are not instantiated
 constexpr size_t LDS_MAX = 160 * 1024;
 template <int NP, int NQ> constexpr size_t lds_need(int vt, int bytes, bool offd = false) {
   return ((size_t)(2 * NQ * NQ * NQ + 2 * NP * NP) * vt + (offd ? NCOEF_GEN : 4) * NQ * NQ * NQ + NQ * NQ +
           (offd ? (size_t)3 * NQ * NQ * NQ * vt : 0)) * bytes;
-}
-
-// LDS of one block as launched: the line-gather path holds no staged carry
-// planes
-template <int NP, int NQ, typename TC, class Core, bool CPLX>
-constexpr size_t lds_local(int vt, int bytes, bool offd) {
-  return (LinesPath<NP, NQ, TC, Core, CPLX>::value && !offd)
-             ? ((size_t)2 * NQ * NQ * NQ * vt + 4 * NQ * NQ * NQ + NQ * NQ) * bytes
-             : lds_need<NP, NQ>(vt, bytes, offd);
 }
 
 inline int device_cus(int dev) {
@@ -1063,36 +728,46 @@ inline int max_lds(Mesh *m) {
   return maxshm;
 }
 
-template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, int LPE, bool SH, class Core = void>
+template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, int LPE, bool SH>
 inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
   // sheared boxes add the three staged gradients to the LDS block; a launch
   // above 64 KiB raises the kernel's dynamic-LDS attribute to its size first
   bool offd = false;
   for (int i = 0; i < Bt.n; ++i) offd = offd || (Bt.ms[i]->offd && !Bt.Ls[i].mass);
-  const size_t shm = lds_local<NP, NQ, TC, Core, CPLX>(VT, sizeof(TC), offd) + CoreLds<Core>::elems * sizeof(TC);
-  constexpr int NTB = Threads<NQ, VT, TC, Core>::value;
+  const size_t shm = lds_need<NP, NQ>(VT, sizeof(TC), offd);
+  constexpr int NTB = BlockSize<NQ, VT, TC>::value;
+  std::vector<KArgs<TC>> as;
+  std::vector<int> waits;
+  auto count = [](int per_cu) {      // blocks of this kernel on a CU
+    return [per_cu](Mesh *m, const LocalLaunch &L, int tiles) {
+      return block_segment_count(m, L.ldy, tiles, per_cu, sizeof(TS), side_limit(L));
+    };
+  };
   if (Bt.n == 1 && !Bt.persistent) {
     Mesh *m = Bt.ms[0];
-    const LocalLaunch &L = Bt.Ls[0];
-    KArgs<TC> a = make_args<TC>(m, L, VT);
-    auto kern = k_local<NP, NQ, VT, CPLX, TS, TC, LPE, SH, Core>;
+    auto kern = k_local<NP, NQ, VT, CPLX, TS, TC, LPE, SH>;
     static size_t attr_set = 65536;
+    static int per_cu[2] = {0, 0};   // blocks without / with the staged gradients
     if (shm > attr_set) {
       FE_HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));
       attr_set = shm;
     }
+    if (!per_cu[offd]) FE_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu[offd], (const void *)kern, NTB, shm));
+    const fe_status st = segments_begin<TS, TC>(Bt, VT, count(per_cu[offd]), as, waits, s);
+    if (st) return st;
+    KArgs<TC> &a = as[0];
     for (int ph = 0; ph < m->nphase; ++ph) {
       a.cols = m->cols + 2 * m->phase_off[ph];
       a.ncols = m->phase_off[ph + 1] - m->phase_off[ph];
       if (a.ncols == 0) continue;
-      const int W = a.ncols * a.ntiles;
+      const int W = a.ncols * a.nseg * a.ntiles;
       const int nb = ((W + 7) / 8) * 8;
       hipLaunchKernelGGL(kern, dim3(nb), dim3(NTB), shm, s, a);
       FE_HIP_TRY(hipGetLastError());
     }
-    return FE_OK;
+    return segments_end<TS, TC>(Bt, as, waits, s);
   }
-  auto kern = k_local_batch<NP, NQ, VT, CPLX, TS, TC, LPE, SH, Core>;
+  auto kern = k_local_batch<NP, NQ, VT, CPLX, TS, TC, LPE, SH>;
   static size_t battr_set = 65536;
   static int resident[2] = {0, 0};   // resident blocks without / with the staged gradients
   if (shm > battr_set) {
@@ -1103,6 +778,10 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
     int per_cu = 0;
     FE_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, NTB, shm));
     resident[offd] = (per_cu > 0 ? per_cu : 1) * device_cus(Bt.ms[0]->device);
+  }
+  {
+    const fe_status st = segments_begin<TS, TC>(Bt, VT, count(std::max(1, resident[offd] / device_cus(Bt.ms[0]->device))), as, waits, s);
+    if (st) return st;
   }
   const int cap = Bt.blocks_per_cu > 0 ? Bt.blocks_per_cu * device_cus(Bt.ms[0]->device) : resident[offd];
   int nphase = 0;
@@ -1117,11 +796,11 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
         if (ph >= m->nphase) continue;
         const int ncols = m->phase_off[ph + 1] - m->phase_off[ph];
         if (ncols == 0) continue;
-        KArgs<TC> a = make_args<TC>(m, Bt.Ls[i0], VT);
+        KArgs<TC> &a = as[i0];
         a.cols = m->cols + 2 * m->phase_off[ph];
         a.ncols = ncols;
         B.sys[B.nsys] = a;
-        B.off[B.nsys + 1] = B.off[B.nsys] + ncols * a.ntiles;
+        B.off[B.nsys + 1] = B.off[B.nsys] + ncols * a.nseg * a.ntiles;
         ++B.nsys;
       }
       if (B.nsys == 0) continue;
@@ -1132,7 +811,7 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
       FE_HIP_TRY(hipGetLastError());
     }
   }
-  return FE_OK;
+  return segments_end<TS, TC>(Bt, as, waits, s);
 }
 
 // The wide (16-byte) element form when every block of every system allows it.
@@ -1146,43 +825,48 @@ inline bool wide_ok(const LocalBatch &Bt, int lpe, size_t ts) {
   return true;
 }
 
-template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, bool SH = false, class Core = void>
+template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC, bool SH = false>
 inline fe_status run_local(const LocalBatch &Bt, hipStream_t s) {
   constexpr int W = WideLanes<TS>::value;
-  // the line-gather path moves single lanes: one instance serves every block
-  constexpr bool lines_only = LinesPath<NP, NQ, TC, Core, CPLX>::value && !SH;
-  if constexpr (!lines_only)
-    if (VT % W == 0 && wide_ok(Bt, W, sizeof(TS))) return run_local_lpe<NP, NQ, VT, CPLX, TS, TC, W, SH, Core>(Bt, s);
-  return run_local_lpe<NP, NQ, VT, CPLX, TS, TC, 1, SH, Core>(Bt, s);
+  if (VT % W == 0 && wide_ok(Bt, W, sizeof(TS))) return run_local_lpe<NP, NQ, VT, CPLX, TS, TC, W, SH>(Bt, s);
+  return run_local_lpe<NP, NQ, VT, CPLX, TS, TC, 1, SH>(Bt, s);
 }
 
 
 // Vector tile per precision: the caller's (the autotuner's) choice when it is
 // set and fits, else the widest default whose LDS fits.
+template <int NP, int NQ, int VT, bool CPLX, typename TS, typename TC>
+fe_status run_tile(bool od, const LocalBatch &B, hipStream_t s) {
+  if (od) return run_local<NP, NQ, VT, CPLX, TS, TC, true>(B, s);
+  // n_q = n_p with a diagonal metric comes here only past what the plane
+  // kernels address: one tile
+  if constexpr (NP != NQ || VT == 8) return run_local<NP, NQ, VT, CPLX, TS, TC>(B, s);
+  return set_error(FE_EUNSUPPORTED, "no local-operator variant for this vector tile");
+}
+
 template <int NP, int NQ, bool CPLX>
 fe_status pick_vt_f64(const LocalBatch &B, hipStream_t s) {
   const size_t mx = (size_t)max_lds(B.ms[0]);
   bool od = false;   // any system of a sheared box: the staged gradients must fit too
   for (int i = 0; i < B.n; ++i) od = od || (B.ms[i]->offd && !B.Ls[i].mass);
-  int vt = B.Ls[0].vt ? B.Ls[0].vt
+  int vt = NP == NQ && !od ? 8 : B.Ls[0].vt ? B.Ls[0].vt
                       : (lds_need<NP, NQ>(8, 8, od) <= mx ? 8 : (lds_need<NP, NQ>(4, 8, od) <= mx ? 4 : 2));
   if constexpr (lds_need<NP, NQ>(16, 8) <= LDS_MAX)
     if (vt == 16 && lds_need<NP, NQ>(16, 8, od) <= mx)
-      return od ? run_local<NP, NQ, 16, CPLX, double, double, true>(B, s) : run_local<NP, NQ, 16, CPLX, double, double>(B, s);
-  // ten lanes: 7^2 lines x 10 lanes fill 490 of a 512-thread block at n_p = 7
+      return run_tile<NP, NQ, 16, CPLX, double, double>(od, B, s);
   if constexpr (NP == NQ && lds_need<NP, NQ>(10, 8) <= LDS_MAX)
     if (vt == 10 && lds_need<NP, NQ>(10, 8, od) <= mx)
-      return od ? run_local<NP, NQ, 10, CPLX, double, double, true>(B, s) : run_local<NP, NQ, 10, CPLX, double, double>(B, s);
+      return run_tile<NP, NQ, 10, CPLX, double, double>(od, B, s);
   if constexpr (lds_need<NP, NQ>(8, 8) <= LDS_MAX)
     if (vt == 8 && lds_need<NP, NQ>(8, 8, od) <= mx)
-      return od ? run_local<NP, NQ, 8, CPLX, double, double, true>(B, s) : run_local<NP, NQ, 8, CPLX, double, double>(B, s);
+      return run_tile<NP, NQ, 8, CPLX, double, double>(od, B, s);
   if constexpr (lds_need<NP, NQ>(4, 8) <= LDS_MAX)
     if (vt == 4 && lds_need<NP, NQ>(4, 8, od) <= mx)
-      return od ? run_local<NP, NQ, 4, CPLX, double, double, true>(B, s) : run_local<NP, NQ, 4, CPLX, double, double>(B, s);
+      return run_tile<NP, NQ, 4, CPLX, double, double>(od, B, s);
   // two lanes (one complex vector): only where four do not fit (n_q = 12)
   if constexpr (lds_need<NP, NQ>(4, 8) > LDS_MAX && lds_need<NP, NQ>(2, 8) <= LDS_MAX)
     if (vt == 2 && lds_need<NP, NQ>(2, 8, od) <= mx)
-      return od ? run_local<NP, NQ, 2, CPLX, double, double, true>(B, s) : run_local<NP, NQ, 2, CPLX, double, double>(B, s);
+      return run_tile<NP, NQ, 2, CPLX, double, double>(od, B, s);
   return set_error(FE_EUNSUPPORTED, "no FP64 local-operator variant for this vector tile / LDS size");
 }
 template <int NP, int NQ, bool CPLX>
@@ -1190,16 +874,16 @@ fe_status pick_vt_f32(const LocalBatch &B, hipStream_t s) {
   const size_t mx = (size_t)max_lds(B.ms[0]);
   bool od = false;   // any system of a sheared box: the staged gradients must fit too
   for (int i = 0; i < B.n; ++i) od = od || (B.ms[i]->offd && !B.Ls[i].mass);
-  int vt = B.Ls[0].vt ? B.Ls[0].vt : (lds_need<NP, NQ>(16, 4, od) <= mx ? 16 : 8);
+  int vt = NP == NQ && !od ? 8 : B.Ls[0].vt ? B.Ls[0].vt : (lds_need<NP, NQ>(16, 4, od) <= mx ? 16 : 8);
   if constexpr (lds_need<NP, NQ>(32, 4) <= LDS_MAX)
     if (vt == 32 && lds_need<NP, NQ>(32, 4, od) <= mx)
-      return od ? run_local<NP, NQ, 32, CPLX, float, float, true>(B, s) : run_local<NP, NQ, 32, CPLX, float, float>(B, s);
+      return run_tile<NP, NQ, 32, CPLX, float, float>(od, B, s);
   if constexpr (lds_need<NP, NQ>(16, 4) <= LDS_MAX)
     if (vt == 16 && lds_need<NP, NQ>(16, 4, od) <= mx)
-      return od ? run_local<NP, NQ, 16, CPLX, float, float, true>(B, s) : run_local<NP, NQ, 16, CPLX, float, float>(B, s);
+      return run_tile<NP, NQ, 16, CPLX, float, float>(od, B, s);
   if constexpr (lds_need<NP, NQ>(8, 4) <= LDS_MAX)
     if (vt == 8 && lds_need<NP, NQ>(8, 4, od) <= mx)
-      return od ? run_local<NP, NQ, 8, CPLX, float, float, true>(B, s) : run_local<NP, NQ, 8, CPLX, float, float>(B, s);
+      return run_tile<NP, NQ, 8, CPLX, float, float>(od, B, s);
   return set_error(FE_EUNSUPPORTED, "no FP32 local-operator variant for this vector tile / LDS size");
 }
 template <int NP, int NQ, bool CPLX>
@@ -1207,16 +891,16 @@ fe_status pick_vt_bf16(const LocalBatch &B, hipStream_t s) {
   const size_t mx = (size_t)max_lds(B.ms[0]);
   bool od = false;   // any system of a sheared box: the staged gradients must fit too
   for (int i = 0; i < B.n; ++i) od = od || (B.ms[i]->offd && !B.Ls[i].mass);
-  int vt = B.Ls[0].vt ? B.Ls[0].vt : (lds_need<NP, NQ>(32, 4, od) <= mx ? 32 : (lds_need<NP, NQ>(16, 4, od) <= mx ? 16 : 8));
+  int vt = NP == NQ && !od ? 8 : B.Ls[0].vt ? B.Ls[0].vt : (lds_need<NP, NQ>(32, 4, od) <= mx ? 32 : (lds_need<NP, NQ>(16, 4, od) <= mx ? 16 : 8));
   if constexpr (lds_need<NP, NQ>(32, 4) <= LDS_MAX)
     if (vt == 32 && lds_need<NP, NQ>(32, 4, od) <= mx)
-      return od ? run_local<NP, NQ, 32, CPLX, bf16s, float, true>(B, s) : run_local<NP, NQ, 32, CPLX, bf16s, float>(B, s);
+      return run_tile<NP, NQ, 32, CPLX, bf16s, float>(od, B, s);
   if constexpr (lds_need<NP, NQ>(16, 4) <= LDS_MAX)
     if (vt == 16 && lds_need<NP, NQ>(16, 4, od) <= mx)
-      return od ? run_local<NP, NQ, 16, CPLX, bf16s, float, true>(B, s) : run_local<NP, NQ, 16, CPLX, bf16s, float>(B, s);
+      return run_tile<NP, NQ, 16, CPLX, bf16s, float>(od, B, s);
   if constexpr (lds_need<NP, NQ>(8, 4) <= LDS_MAX)
     if (vt == 8 && lds_need<NP, NQ>(8, 4, od) <= mx)
-      return od ? run_local<NP, NQ, 8, CPLX, bf16s, float, true>(B, s) : run_local<NP, NQ, 8, CPLX, bf16s, float>(B, s);
+      return run_tile<NP, NQ, 8, CPLX, bf16s, float>(od, B, s);
   return set_error(FE_EUNSUPPORTED, "no BF16 local-operator variant for this vector tile / LDS size");
 }
 template <int NP, int NQ> fe_status pick_cplx_f64(const LocalBatch &B, hipStream_t s) {

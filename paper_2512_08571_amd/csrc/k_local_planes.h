@@ -472,9 +472,6 @@ __device__ __forceinline__ int64_t opaque(int64_t x) {
 
 template <typename T> __device__ __forceinline__ T *opaque(T *p) { return reinterpret_cast<T *>(opaque(reinterpret_cast<int64_t>(p))); }
 template <typename T> __device__ __forceinline__ const T *scalar_ptr(const T *p) { return opaque(p); }
-// first cell of segment s of a column of n cells cut into nseg
-__device__ __host__ __forceinline__ int seg_start(int s, int n, int nseg) { return (int)((int64_t)s * n / nseg); }
-
 // A thread's lanes in global memory: gather loads by address, and the scatter's
 // reads and writes through a buffer descriptor, whose bounds check turns a
 // masked thread (offset BUF_OFF) into a read of zero and a dropped write.  So
@@ -929,19 +926,6 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
   }
 }
 
-// Y += the segments' first planes: plane seg of the side block to the plane
-// of Y at that segment's first node; one block per node row
-template <typename TS, typename TC>
-__global__ void k_planes_join(TS *__restrict__ Y, const TS *__restrict__ side, int64_t plane, int nseg, int N2, int p,
-                              int zoff, int64_t ldy, int nlanes) {
-  const int sg = blockIdx.y;
-  const int64_t gz = (int64_t)seg_start(sg, N2, nseg) * p - zoff;
-  if (gz < 0) return;                            // a Dirichlet face: no DoFs
-  TS *q = Y + gz * plane + blockIdx.x * ldy;
-  const TS *r = side + sg * plane + blockIdx.x * ldy;
-  for (int l = threadIdx.x; l < nlanes; l += blockDim.x) Cvt<TS, TC>::st(q, l, Cvt<TS, TC>::ld(q, l) + Cvt<TS, TC>::ld(r, l));
-}
-
 // Waves are independent; they are grouped into blocks of four, which the
 // device spreads over a CU's four SIMDs (single-wave blocks may share one
 // while others idle).
@@ -997,21 +981,15 @@ inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
   const void *kern = single ? (const void *)k_planes<NP, NQ, CPLX, TS, TC, LPT, MASS> : (const void *)k_planes_batch<NP, NQ, CPLX, TS, TC, LPT, MASS>;
   FE_HIP_TRY(plane_lds(kern, shm));
   std::vector<KArgs<TC>> as;
-  std::vector<Mesh *> sharing;
+  std::vector<int> waits;
+  fe_status st = segments_begin<TS, TC>(Bt, S::VT, [&](Mesh *m, const LocalLaunch &L, int) {
+    return plane_segment_count(m, NQ, L.nlanes, L.ldy, sizeof(TC) == 8, LPT, sizeof(TS), side_limit(L), nullptr);
+  }, as, waits, s);
+  if (st) return st;
   int nphase = 0;
   for (int i = 0; i < Bt.n; ++i) {
-    Mesh *m = Bt.ms[i];
-    as.push_back(make_args<TC>(m, Bt.Ls[i], S::VT));
-    KArgs<TC> &a = as.back();
-    if constexpr (MASS) a.pgather = a.ptab + plane_tab(m->np, m->nq).m;
-    bool shared = false;
-    a.nseg = plane_segments(m, Bt.Ls[i], NQ, LPT, sizeof(TS), s, &a.side, &shared);
-    if (shared) {
-      const fe_status st = plane_side_enter(m, s);
-      if (st) return st;
-      sharing.push_back(m);
-    }
-    nphase = std::max(nphase, m->nphase);
+    if constexpr (MASS) as[i].pgather = as[i].ptab + plane_tab(Bt.ms[i]->np, Bt.ms[i]->nq).m;
+    nphase = std::max(nphase, Bt.ms[i]->nphase);
   }
   for (int ph = 0; ph < nphase; ++ph) {
     for (int i0 = 0; i0 < Bt.n;) {
@@ -1038,19 +1016,7 @@ inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
       FE_HIP_TRY(hipGetLastError());
     }
   }
-  for (int i = 0; i < Bt.n; ++i) {
-    const KArgs<TC> &a = as[i];
-    if (a.nseg == 1) continue;
-    const int rows = a.M0 * a.M1;
-    hipLaunchKernelGGL((k_planes_join<TS, TC>), dim3(rows, a.nseg), dim3(a.nlanes <= 64 ? 64 : 256), 0, s, (TS *)a.Y,
-                       (const TS *)a.side, rows * a.ldy, a.nseg, a.N2, a.p, a.dmask & 4 ? 1 : 0, a.ldy, a.nlanes);
-    FE_HIP_TRY(hipGetLastError());
-  }
-  for (Mesh *m : sharing) {
-    const fe_status st = plane_side_leave(m, s);
-    if (st) return st;
-  }
-  return FE_OK;
+  return segments_end<TS, TC>(Bt, as, waits, s);
 }
 
 // The plane kernel where it applies (affine cells with a diagonal metric, the
