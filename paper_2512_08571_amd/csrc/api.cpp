@@ -1161,11 +1161,15 @@ fe_status fe_batch_apply(int32_t n, const fe_mesh_t *meshes, const void *const *
   hipStream_t s = (hipStream_t)stream;
   // projector reductions of every system (FP32 / BF16: on the meshes' second
   // streams), the batched local launches, then the projector updates
+  std::vector<fehx::Mesh *> all(meshes, meshes + n);
+  std::vector<fehx::LocalLaunch> calls(n);
   for (int i = 0; i < n; ++i) {
     const int C = meshes[i]->cplx ? 2 : 1;
-    fe_status st = fehx::nonlocal_reduce(meshes[i], X[i], ldx[i] * C, (int)(nvec[i] * C), prec, nullptr, s);
-    if (st) return st;
+    fehx::LocalLaunch &L = calls[i];
+    L.X = X[i]; L.Y = Y[i]; L.ldx = ldx[i] * C; L.ldy = ldy[i] * C; L.nlanes = (int)(nvec[i] * C);
+    L.prec = prec; L.vt = meshes[i]->vt_pref[prec][0];
   }
+  if (fe_status st = fehx::nonlocal_batch(all.data(), calls.data(), n, 1, s)) return st;
   // group by launch class, keeping the caller's order inside a class
   std::vector<int> done(n, 0);
   for (int i = 0; i < n; ++i) {
@@ -1177,12 +1181,8 @@ fe_status fe_batch_apply(int32_t n, const fe_mesh_t *meshes, const void *const *
       if (done[j] || b->np != a->np || b->nq != a->nq || b->cplx != a->cplx ||
           b->vt_pref[prec][0] != a->vt_pref[prec][0])
         continue;
-      const int C = b->cplx ? 2 : 1;
-      fehx::LocalLaunch L;
-      L.X = X[j]; L.Y = Y[j]; L.ldx = ldx[j] * C; L.ldy = ldy[j] * C; L.nlanes = (int)(nvec[j] * C);
-      L.prec = prec; L.vt = b->vt_pref[prec][0];
       ms.push_back(b);
-      Ls.push_back(L);
+      Ls.push_back(calls[j]);
       done[j] = 1;
     }
     // A system whose every colour phase has at least two blocks per CU
@@ -1216,12 +1216,7 @@ fe_status fe_batch_apply(int32_t n, const fe_mesh_t *meshes, const void *const *
     fe_status st = fehx::launch_local_batch(B, s);
     if (st) return st;
   }
-  for (int i = 0; i < n; ++i) {
-    const int C = meshes[i]->cplx ? 2 : 1;
-    fe_status st = fehx::nonlocal_update(meshes[i], Y[i], ldy[i] * C, (int)(nvec[i] * C), prec, 1.0, s);
-    if (st) return st;
-  }
-  return FE_OK;
+  return fehx::nonlocal_batch(all.data(), calls.data(), n, 2, s);
 }
 
 }  // extern "C"

@@ -164,6 +164,7 @@ fe_status ensure_side_stream(Mesh *m);
 // mesh's second stream) and the update after them (joining that stream)
 fe_status nonlocal_reduce(Mesh *m, const void *X, int64_t ldx, int nlanes, int prec, const double *dinv,
                           hipStream_t s);
+fe_status nonlocal_batch(Mesh *const *ms, const LocalLaunch *Ls, int n, int part, hipStream_t s);
 fe_status nonlocal_update(Mesh *m, void *Y, int64_t ldy, int nlanes, int prec, double alpha, hipStream_t s);
 fe_status apply_with_nonlocal(Mesh *m, const LocalLaunch &L, int prec, const double *dinv, double alpha,
                               hipStream_t s);

@@ -25,9 +25,12 @@
 // access and complex (re, im) pairs stay inside one thread.  The vector
 // width of these passes is the whole block row (the paper's level-0 batch
 // for the nonlocal part of Alg. 1).
+#include <algorithm>
+#include <map>
 #include <mutex>
 #include <string>
 #include <type_traits>
+#include <vector>
 
 #include "fe_internal.h"
 
@@ -132,11 +135,15 @@ template <bool VEC> struct Pair {
   }
 };
 
-// Quad load without a branch: elements past nv (>= 1) read the last one in
-// range, so that rows in flight are not separated by conditional blocks
+// Quad load without a branch: elements past nv (>= 1) read others in range, so
+// that rows in flight are not separated by conditional blocks.  FP64 in pairs
+// needs an even nv only (every complex block).
 template <typename TS, typename TC, bool VEC>
 __device__ __forceinline__ void quad_ld_clamped(const TS *p, int64_t o, int nv, TC v[4]) {
-  if constexpr (VEC) {
+  if constexpr (VEC && std::is_same<TS, double>::value) {
+    const double2 a = *(const double2 *)(p + o), b = *(const double2 *)(p + o + (nv > 2 ? 2 : 0));
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+  } else if constexpr (VEC) {
     Quad<TS, TC, true>::ld(p, o, nv, v);
   } else {
 #pragma unroll
@@ -167,6 +174,28 @@ __device__ __forceinline__ void nl_conj_fma(TC fr, TC fi, const TC x[4], TC acc[
   }
 }
 
+// One system's projector term as the kernels take it.  A launch covers up to
+// NL_GROUP systems (blockIdx.z), so that the small systems of a batch share the
+// device: eight k-points of 74,088 DoFs x 48 lanes, reduction 8 x 35 -> 250 us,
+// sums 8 x 5 -> 7, update 8 x 36 -> 191.
+constexpr int NL_GROUP = 8;
+template <typename TS, typename TC> struct NlSys {
+  const TS *X;
+  TS *Y;
+  const double *dinv, *h;
+  const TC *F;
+  TC *part, *W;                                  // chunk partials [nchunks][NL_MAXP][ldp], W [ns][ldp]
+  const int4 *chunks;
+  const int *nodes, *atom_chunk0, *proj_off, *proj_atom;
+  const int *b_row0, *b_p0, *b_proj, *b_rows, *kb;   // bricks as dense blocks (FP64)
+  const int64_t *a_off;
+  const double *A;
+  int64_t ldx, ldy, ldp;
+  int nlanes, nchunks, fstride, ns, nbrick;
+  TC alpha;
+};
+template <typename TS, typename TC> struct NlGroup { NlSys<TS, TC> a[NL_GROUP]; };
+
 // One chunk of one atom's support nodes: a row of the block is moved by TL
 // threads (four lanes each), so a wave holds 64 / TL rows at a time and the
 // block NW times as many; each group of TL threads takes every (NW 64 / TL)-th
@@ -179,22 +208,37 @@ __device__ __forceinline__ void nl_conj_fma(TC fr, TC fi, const TC x[4], TC acc[
 // launch_nl_w_tl).
 template <bool CPLX, typename TS, typename TC, bool VEC, int PMAX, int TL, int NW>
 __global__ void __launch_bounds__(64 * NW)
-k_nl_w(const TS *__restrict__ X, int64_t ldx, int nlanes, const double *__restrict__ dinv,
-       const int4 *__restrict__ chunks, int nchunks, const int *__restrict__ nodes, const TC *__restrict__ F, int fstride,
-       TC *__restrict__ part, int64_t ldp) {
+k_nl_w(NlGroup<TS, TC> grp) {
+  const NlSys<TS, TC> &a = grp.a[blockIdx.z];
+  const TS *__restrict__ X = a.X;
+  const double *__restrict__ dinv = a.dinv;
+  const int *__restrict__ nodes = a.nodes;
+  const TC *__restrict__ F = a.F;
+  TC *__restrict__ part = a.part;
+  const int64_t ldx = a.ldx, ldp = a.ldp;
+  const int nlanes = a.nlanes, fstride = a.fstride;
   constexpr int C = CPLX ? 2 : 1;
   constexpr int TILE = 4 * TL;                   // lanes per block
   constexpr int GW = 64 / TL, G = GW * NW;       // node groups per wave, per block
   constexpr int U = NW == 4 ? 2 : 4;             // nodes in flight per group
   // projectors summed per step: all of them where their sums fit 32 KiB
   constexpr int SB = (int)sizeof(TC) * PMAX * NW * TILE <= 32768 ? PMAX : 1;
+  // Projector values: wave-uniform scalar loads where a wave holds one row;
+  // with several rows a wave TE entries at a time in LDS (the space of the
+  // sums), since per-group loads of them, a chain of four to ten per X row, were
+  // most of the time (31,500 complex DoFs x 66 lanes 47 -> 25 us; eight
+  // k-points of 74,088 DoFs x 48 lanes 250 -> 164 us)
+  constexpr bool STAGE = GW > 1;
+  constexpr int TE = STAGE ? (PMAX <= 4 ? 512 : 256) : NL_CHUNK;
+  constexpr int NRED = SB * NW * TILE, NF = STAGE ? TE * PMAX * C : 0;
   __shared__ int snode[NL_CHUNK];
-  __shared__ TC red[SB][NW][TILE];
+  __shared__ TC space[NRED > NF ? NRED : NF];
+  auto red = reinterpret_cast<TC(*)[NW][TILE]>(space);
   // XCD-aware: block x runs on XCD x % 8, and each XCD takes a contiguous run
   // of the position-ordered chunks, so overlapping atoms' chunks share an L2
   const int item = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  if (item >= nchunks) return;                   // whole block: before any barrier
-  const int4 cd = chunks[item];                  // partial slot, first support entry, entries, projectors
+  if (item >= a.nchunks || (int)blockIdx.y * TILE >= nlanes) return;   // whole block: before any barrier
+  const int4 cd = a.chunks[item];                  // partial slot, first support entry, entries, projectors
   const int ch = cd.x, n0 = cd.y, nn = cd.z, ns = cd.w;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lt = (threadIdx.x & (TL - 1)) * 4;
@@ -212,6 +256,7 @@ k_nl_w(const TS *__restrict__ X, int64_t ldx, int nlanes, const double *__restri
   const int g = wv * GW + (GW > 1 ? (int)((threadIdx.x & 63) / TL) : 0);
   // U rows of this group; TAIL: a group past its last node reads the chunk's
   // last row and takes it as zero, so the trip count is the block's
+  int t0 = 0, t1 = 0;                            // the entries at hand
   auto rows = [&](int i0, auto tail_tag) {
     constexpr bool TAIL = decltype(tail_tag)::value;
     TC x[U][4];
@@ -219,7 +264,7 @@ k_nl_w(const TS *__restrict__ X, int64_t ldx, int nlanes, const double *__restri
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       idx[u] = i0 + u * G + g;
-      if constexpr (TAIL) idx[u] = min(idx[u], nn - 1);
+      if constexpr (TAIL) idx[u] = min(idx[u], t1 - 1);
       int node = snode[idx[u]];
       if constexpr (GW == 1) node = __builtin_amdgcn_readfirstlane(node);
       quad_ld_clamped<TS, TC, VEC>(X, (int64_t)node * ldx + lc, nv, x[u]);
@@ -230,19 +275,29 @@ k_nl_w(const TS *__restrict__ X, int64_t ldx, int nlanes, const double *__restri
       }
       if constexpr (TAIL)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[u][j] = i0 + u * G + g < nn ? x[u][j] : (TC)0;
+        for (int j = 0; j < 4; ++j) x[u][j] = i0 + u * G + g < t1 ? x[u][j] : (TC)0;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const TC *f = F + (int64_t)(n0 + idx[u]) * fstride * C;
+      const TC *f = STAGE ? space + (idx[u] - t0) * fstride * C : F + (int64_t)(n0 + idx[u]) * fstride * C;
 #pragma unroll
       for (int s = 0; s < PMAX; ++s)
         if (s < ns) nl_conj_fma<CPLX>(f[s * C], CPLX ? f[s * C + 1] : (TC)0, x[u], acc[s]);
     }
   };
-  int i0 = 0;
-  for (; i0 + U * G <= nn; i0 += U * G) rows(i0, std::false_type{});
-  if (i0 < nn) rows(i0, std::true_type{});
+  for (; t0 < nn; t0 = t1) {
+    t1 = min(nn, t0 + TE);
+    if constexpr (STAGE) {
+      if (t0 > 0) __syncthreads();
+      const TC *src = F + (int64_t)(n0 + t0) * fstride * C;
+      for (int e = threadIdx.x; e < (t1 - t0) * fstride * C; e += 64 * NW) space[e] = src[e];
+      __syncthreads();
+    }
+    int i0 = t0;
+    for (; i0 + U * G <= t1; i0 += U * G) rows(i0, std::false_type{});
+    if (i0 < t1) rows(i0, std::true_type{});
+  }
+  if constexpr (STAGE) __syncthreads();
   // fixed-order sums, SB projectors at a time
 #pragma unroll
   for (int s0 = 0; s0 < PMAX; s0 += SB) {
@@ -271,15 +326,18 @@ k_nl_w(const TS *__restrict__ X, int64_t ldx, int nlanes, const double *__restri
   }
 }
 
-template <typename TC>
-__global__ void k_nl_wsum(const TC *__restrict__ part, int64_t ldp, const int *__restrict__ atom_chunk0,
-                          const int *__restrict__ proj_off, const int *__restrict__ proj_atom,
-                          const double *__restrict__ h, int ns, int nlanes, TC *__restrict__ W, int64_t ldw) {
+template <typename TS, typename TC>
+__global__ void k_nl_wsum(NlGroup<TS, TC> grp) {
+  const NlSys<TS, TC> &sys = grp.a[blockIdx.z];
+  const TC *__restrict__ part = sys.part;
+  const int *__restrict__ atom_chunk0 = sys.atom_chunk0;
+  const int nlanes = sys.nlanes;
+  const int64_t ldp = sys.ldp;
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= (int64_t)ns * nlanes) return;
+  if (t >= (int64_t)sys.ns * nlanes) return;
   const int s = (int)(t / nlanes), l = (int)(t % nlanes);
-  const int a = proj_atom[s];
-  const int sl = s - proj_off[a];
+  const int a = sys.proj_atom[s];
+  const int sl = s - sys.proj_off[a];
   // in chunk order, eight loads in flight
   const int c1 = atom_chunk0[a + 1];
   TC sum = 0;
@@ -290,7 +348,7 @@ __global__ void k_nl_wsum(const TC *__restrict__ part, int64_t ldp, const int *_
 #pragma unroll
     for (int u = 0; u < 8; ++u) sum += c0 + u < c1 ? v[u] : (TC)0;
   }
-  W[(int64_t)s * ldw + l] = (TC)h[s] * sum;
+  sys.W[(int64_t)s * ldp + l] = (TC)sys.h[s] * sum;
 }
 
 template <bool CPLX, typename TS, typename TC, bool VEC>
@@ -470,8 +528,8 @@ k_nl_yb(TS *__restrict__ Y, int64_t ldy, int nlanes, int nbrick, const int *__re
 // staged in LDS) holds the W rows of the brick's projectors, the (p, im) row
 // as i W_p, so that one real product yields both parts of F W:
 //   re += Fr Wr + Fi (-Wi),  im += Fr Wi + Fi Wr.
-// One workgroup per (brick, 64-lane tile); each wave takes 16-row tiles and
-// accumulates four 16 x 16 column blocks over K with v_mfma_f64_16x16x4
+// One workgroup per (brick, 64-lane tile, part of the row tiles); each wave
+// takes 16-row tiles and accumulates four 16 x 16 column blocks over K with v_mfma_f64_16x16x4
 // (operands: lane l holds A[l & 15][l >> 4] and B[l >> 4][l & 15]; item v of
 // the result is row (l >> 4) + 4 v, column l & 15).  The K order is fixed, so
 // the update is reproducible bit for bit.  The four A values of a step come
@@ -485,20 +543,26 @@ static_assert(2 * NL_BPMAX * NL_MN * sizeof(double) <= 65536, "k_nl_ybm's LDS bl
 
 template <bool CPLX>
 __global__ void __launch_bounds__(NL_MT)
-k_nl_ybm(double *__restrict__ Y, int64_t ldy, int nlanes, int nbrick, const int *__restrict__ b_row0,
-         const int *__restrict__ b_p0, const int *__restrict__ b_proj, const int *__restrict__ b_rows,
-         const int64_t *__restrict__ a_off, const int *__restrict__ kb, const double *__restrict__ A,
-         const double *__restrict__ W, int64_t ldw, double alpha) {
+k_nl_ybm(NlGroup<double, double> grp, int parts) {
+  const NlSys<double, double> &sys = grp.a[blockIdx.z];
+  double *__restrict__ Y = sys.Y;
+  const int *__restrict__ b_row0 = sys.b_row0, *__restrict__ b_p0 = sys.b_p0, *__restrict__ b_proj = sys.b_proj;
+  const int *__restrict__ b_rows = sys.b_rows;
+  const double *__restrict__ W = sys.W;
+  const int64_t ldy = sys.ldy, ldw = sys.ldp;
+  const int nlanes = sys.nlanes;
+  const double alpha = sys.alpha;
   constexpr int NCB = NL_MN / 16;
   constexpr int NW = NL_MT / 64;
   extern __shared__ __align__(16) unsigned char nl_smem[];
   double *Bl = (double *)nl_smem;
   const int tiles = (nlanes + NL_MN - 1) / NL_MN;
   const int xcd = blockIdx.x & 7, rest = blockIdx.x >> 3;   // a brick's tiles on one XCD, as in k_nl_yb
-  const int b = (rest / tiles) * 8 + xcd, tile = rest % tiles;
-  if (b >= nbrick) return;                                   // whole block: before any barrier
+  const int part = rest % parts, bt = rest / parts;
+  const int b = (bt / tiles) * 8 + xcd, tile = bt % tiles;
+  if (b >= sys.nbrick || part * 16 >= b_row0[b + 1] - b_row0[b]) return;   // whole block: before any barrier
   const int n0 = tile * NL_MN;
-  const int p0 = b_p0[b], np = b_p0[b + 1] - p0, K = kb[b];
+  const int p0 = b_p0[b], np = b_p0[b + 1] - p0, K = sys.kb[b];
   for (int e = threadIdx.x; e < K * NL_MN; e += NL_MT) {
     const int k = e / NL_MN, j = e - k * NL_MN;
     const int p = CPLX ? k >> 1 : k;
@@ -514,8 +578,8 @@ k_nl_ybm(double *__restrict__ Y, int64_t ldy, int nlanes, int nbrick, const int 
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int i = lane & 15, kq = lane >> 4;
   const int r0 = b_row0[b], R = b_row0[b + 1] - r0;
-  const double *Ab = A + a_off[b];
-  for (int mt = wv; mt * 16 < R; mt += NW) {
+  const double *__restrict__ Ab = sys.A + sys.a_off[b];
+  for (int mt = wv * parts + part; mt * 16 < R; mt += NW * parts) {
     // this tile's Y values (rows past the brick read its last row, columns
     // past the block its last column; neither is written back)
     double y[4][NCB];
@@ -557,58 +621,70 @@ k_nl_ybm(double *__restrict__ Y, int64_t ldy, int nlanes, int nbrick, const int 
 }
 
 namespace {
+// the extents a launch over a group needs
+struct NlExtent {
+  int n = 0, nlanes = 0, nchunks = 0, kmax = 0, form = 0;
+  int64_t bricks = 0, nw = 0;   // brick groups and W entries of the largest system
+};
+
 template <bool CPLX, typename TS, typename TC, bool VEC, int PMAX, int TL, int NW>
-void launch_nl_w_as(Mesh *m, const TS *X, int64_t ldx, int nlanes, const double *dinv, const TC *F, TC *part,
-                    int64_t ldp, hipStream_t s) {
-  const int tiles = (nlanes + 4 * TL - 1) / (4 * TL);
-  const unsigned gx = (unsigned)(m->nl_nchunks + 7) / 8 * 8;   // a multiple of the 8 XCDs
-  hipLaunchKernelGGL((k_nl_w<CPLX, TS, TC, VEC, PMAX, TL, NW>), dim3(gx, tiles), dim3(64 * NW), 0, s, X, ldx,
-                     nlanes, dinv, (const int4 *)m->nl_chunks, m->nl_nchunks, m->nl_atom_nodes, F, m->nl_maxproj, part, ldp);
+void launch_nl_w_as(const NlGroup<TS, TC> &g, const NlExtent &e, hipStream_t s) {
+  const int tiles = (e.nlanes + 4 * TL - 1) / (4 * TL);
+  const unsigned gx = (unsigned)(e.nchunks + 7) / 8 * 8;   // a multiple of the 8 XCDs
+  hipLaunchKernelGGL((k_nl_w<CPLX, TS, TC, VEC, PMAX, TL, NW>), dim3(gx, tiles, e.n), dim3(64 * NW), 0, s, g);
 }
 
 // The narrowest row group that holds the lanes: 32 lanes on eight threads move
 // eight rows per wave access where one row per access left 56 of 64 threads
-// idle (FP64, 31,500 DoFs x 32 lanes: 190 -> 17 us; eight
-// complex atoms, 74,088 DoFs x 48 lanes: 213 -> 35 us).  Sixteen waves per
+// idle (FP64, 31,500 DoFs x 32 lanes: 190 -> 15 us; eight complex atoms,
+// 74,088 DoFs x 48 lanes: 213 -> 35 us).  Sixteen waves per
 // chunk where the chunks do not fill the device: about 130 chunks x 128 FP64
 // lanes 217 -> 79 us, 270 chunks x 192 FP32 lanes 333 -> 286 us (beside the
 // local launches); with 940 chunks x 256 FP64 lanes the device is full and
 // four waves are the faster (392 us; sixteen waves 11% slower), so the line
-// lies at two blocks per CU.
+// lies at two blocks per CU.  The form fixes the summation order, so it is each
+// system's own also where systems share a launch.
+int nl_w_form(const Mesh *m, int nlanes) {
+  const int f = nlanes <= 32 ? 0 : nlanes <= 64 ? 1 : nlanes <= 128 ? 2
+                : (int64_t)m->nl_nchunks * ((nlanes + 255) / 256) < NL_W_FEW ? 3 : 4;
+  return 2 * f + (m->nl_maxproj > 4 ? 1 : 0);
+}
+
 template <bool CPLX, typename TS, typename TC, bool VEC, int PMAX>
-void launch_nl_w_tl(Mesh *m, const TS *X, int64_t ldx, int nlanes, const double *dinv, const TC *F, TC *part,
-                    int64_t ldp, hipStream_t s) {
+void launch_nl_w_tl(const NlGroup<TS, TC> &g, const NlExtent &e, hipStream_t s) {
   constexpr int NB = PMAX <= 4 || sizeof(TC) == 4 ? 16 : 8;   // waves of a block whose accumulators fit its registers
-  if (nlanes <= 32) launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 8, NB>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
-  else if (nlanes <= 64) launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 16, NB>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
-  else if (nlanes <= 128) launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 32, NB>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
-  else if ((int64_t)m->nl_nchunks * ((nlanes + 255) / 256) < NL_W_FEW)
-    launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 64, NB>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
-  else launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 64, 4>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
+  switch (e.form >> 1) {
+    case 0: return launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 8, NB>(g, e, s);
+    case 1: return launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 16, NB>(g, e, s);
+    case 2: return launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 32, NB>(g, e, s);
+    case 3: return launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 64, NB>(g, e, s);
+    default: return launch_nl_w_as<CPLX, TS, TC, VEC, PMAX, 64, 4>(g, e, s);
+  }
 }
 
 template <bool CPLX, typename TS, typename TC, bool VEC>
-void launch_nl_w(Mesh *m, const TS *X, int64_t ldx, int nlanes, const double *dinv, const TC *F, TC *part,
-                 int64_t ldp, TC *W, int64_t ldw, hipStream_t s) {
-  if (m->nl_maxproj <= 4) launch_nl_w_tl<CPLX, TS, TC, VEC, 4>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
-  else launch_nl_w_tl<CPLX, TS, TC, VEC, NL_MAXP>(m, X, ldx, nlanes, dinv, F, part, ldp, s);
-  const int64_t nw = (int64_t)m->ns * nlanes;
-  hipLaunchKernelGGL((k_nl_wsum<TC>), dim3((unsigned)((nw + 255) / 256)), dim3(256), 0, s, part, ldp,
-                     m->nl_atom_chunk0, m->nl_atom_proj, m->nl_proj_atom, m->nl_h, m->ns, nlanes, W, ldw);
+void launch_nl_w(const NlGroup<TS, TC> &g, const NlExtent &e, hipStream_t s) {
+  if (!(e.form & 1)) launch_nl_w_tl<CPLX, TS, TC, VEC, 4>(g, e, s);
+  else launch_nl_w_tl<CPLX, TS, TC, VEC, NL_MAXP>(g, e, s);
+  hipLaunchKernelGGL((k_nl_wsum<TS, TC>), dim3((unsigned)((e.nw + 255) / 256), 1, e.n), dim3(256), 0, s, g);
+}
+
+// A brick's up to 32 row tiles are four for each wave of a block; while the
+// blocks do not fill the device (two per CU) they are dealt to two or four
+// blocks.  31,500 DoFs: complex x 66 lanes 37 -> 23 us, 32 real lanes
+// 23 -> 11 us; 74,088 complex DoFs x 48 lanes 43 -> 36 us.
+template <bool CPLX> void launch_nl_ybm(const NlGroup<double, double> &g, const NlExtent &e, hipStream_t s) {
+  if (e.bricks == 0) return;
+  const int64_t whole = e.bricks * 8 * ((e.nlanes + NL_MN - 1) / NL_MN);
+  const int parts = whole * e.n >= 512 ? 1 : whole * e.n >= 256 ? 2 : 4;
+  const size_t shm = (size_t)e.kmax * NL_MN * sizeof(double);
+  hipLaunchKernelGGL((k_nl_ybm<CPLX>), dim3((unsigned)(whole * parts), 1, e.n), dim3(NL_MT), shm, s, g, parts);
 }
 
 template <bool CPLX, typename TS, typename TC, bool VEC>
 void launch_nl_y(Mesh *m, TS *Y, int64_t ldy, int nlanes, const TC *val, const TC *W, int64_t ldw, TC alpha,
                  hipStream_t s) {
-  if constexpr (std::is_same<TC, double>::value) {
-    if (m->nl_nbrick > 0) {
-      const int64_t blocks = ((int64_t)m->nl_nbrick + 7) / 8 * 8 * ((nlanes + NL_MN - 1) / NL_MN);
-      const size_t shm = (size_t)m->nl_b_kmax * NL_MN * sizeof(double);
-      hipLaunchKernelGGL((k_nl_ybm<CPLX>), dim3((unsigned)blocks), dim3(NL_MT), shm, s, (double *)Y, ldy, nlanes,
-                         m->nl_nbrick, m->nl_b_row0, m->nl_b_p0, m->nl_b_proj, m->nl_b_rows, m->nl_b_aoff,
-                         m->nl_b_k, m->nl_b_A64, (const double *)W, ldw, (double)alpha);
-    }
-  } else if (m->nl_nbrick > 0) {
+  if (std::is_same<TC, float>::value && m->nl_nbrick > 0) {
     const TC *bval = (const TC *)m->nl_b_val32;
     constexpr int BT = 64 * (16 / (int)sizeof(TC));
     const int64_t btiles = (nlanes + BT - 1) / BT;
@@ -627,34 +703,75 @@ void launch_nl_y(Mesh *m, TS *Y, int64_t ldy, int nlanes, const TC *val, const T
   }
 }
 
+// One system's call.  ws: the partials + W workspace (nl_workspace_bytes), or
+// null for the mesh's own
+struct NlCall {
+  Mesh *m;
+  const void *X;
+  int64_t ldx;
+  void *Y;
+  int64_t ldy;
+  int nlanes;
+  const double *dinv;
+  double alpha;
+  void *ws;
+};
+
 // part 1: W = diag(h) F^H (D^-1) X;  part 2: Y += alpha F W;  3: both.
-// ws: the partials + W workspace (nl_workspace_bytes), or null for the mesh's own
+// Up to NL_GROUP systems of one kind, precision and reduction form.
 template <bool CPLX, typename TS, typename TC>
-fe_status run_nl(Mesh *m, const void *X, int64_t ldx, void *Y, int64_t ldy, int nlanes, const double *dinv,
-                 double alpha, int parts, void *ws, hipStream_t s) {
-  const bool f64 = std::is_same<TC, double>::value;
-  const TC *F = f64 ? (const TC *)m->nl_F64 : (const TC *)m->nl_F32;
-  const TC *val = f64 ? (const TC *)m->nl_val64 : (const TC *)m->nl_val32;
-  // workspace: partials [nchunks][NL_MAXP][ldp] then W [ns][ldw], rows padded to 4 lanes
-  const int64_t ldp = (nlanes + 3) / 4 * 4, ldw = ldp;
-  if (!ws) {
-    fe_status st = ensure_nl_workspace(m, nlanes);
-    if (st) return st;
-    ws = m->nl_W;
+fe_status run_nl(const NlCall *calls, int n, int parts, hipStream_t s) {
+  constexpr bool f64 = std::is_same<TC, double>::value;
+  NlGroup<TS, TC> g{};
+  NlExtent e;
+  e.n = n;
+  e.form = nl_w_form(calls[0].m, calls[0].nlanes);
+  // vector accesses need every thread's lanes in range and aligned: pairs in
+  // FP64, all four else
+  bool vec = true;
+  for (int i = 0; i < n; ++i) {
+    const NlCall &c = calls[i];
+    Mesh *m = c.m;
+    NlSys<TS, TC> &a = g.a[i];
+    void *ws = c.ws;
+    if (!ws) {
+      fe_status st = ensure_nl_workspace(m, c.nlanes);
+      if (st) return st;
+      ws = m->nl_W;
+    }
+    // workspace: partials [nchunks][NL_MAXP][ldp] then W [ns][ldp], rows padded to 4 lanes
+    a.ldp = (c.nlanes + 3) / 4 * 4;
+    a.part = (TC *)ws;
+    a.W = a.part + (int64_t)m->nl_nchunks * NL_MAXP * a.ldp;
+    a.X = (const TS *)c.X; a.Y = (TS *)c.Y; a.ldx = c.ldx; a.ldy = c.ldy; a.nlanes = c.nlanes;
+    a.dinv = c.dinv; a.h = m->nl_h; a.alpha = (TC)c.alpha;
+    a.F = f64 ? (const TC *)m->nl_F64 : (const TC *)m->nl_F32;
+    a.chunks = (const int4 *)m->nl_chunks; a.nchunks = m->nl_nchunks; a.nodes = m->nl_atom_nodes;
+    a.fstride = m->nl_maxproj; a.ns = m->ns;
+    a.atom_chunk0 = m->nl_atom_chunk0; a.proj_off = m->nl_atom_proj; a.proj_atom = m->nl_proj_atom;
+    a.b_row0 = m->nl_b_row0; a.b_p0 = m->nl_b_p0; a.b_proj = m->nl_b_proj; a.b_rows = m->nl_b_rows;
+    a.a_off = m->nl_b_aoff; a.kb = m->nl_b_k; a.A = m->nl_b_A64; a.nbrick = m->nl_nbrick;
+    e.nlanes = std::max(e.nlanes, c.nlanes);
+    e.nchunks = std::max(e.nchunks, m->nl_nchunks);
+    e.kmax = std::max(e.kmax, m->nl_b_kmax);
+    e.bricks = std::max<int64_t>(e.bricks, (m->nl_nbrick + 7) / 8);
+    e.nw = std::max(e.nw, (int64_t)m->ns * c.nlanes);
+    constexpr int w = f64 ? 2 : 4;
+    vec = vec && c.nlanes % w == 0 && c.ldx % w == 0 && (uintptr_t)c.X % (w * sizeof(TS)) == 0;
   }
-  TC *part = (TC *)ws;
-  TC *W = part + (int64_t)m->nl_nchunks * NL_MAXP * ldp;
-  // vector accesses need every thread's four lanes in range and 4-element aligned
-  const uintptr_t al = 4 * sizeof(TS);
   if (parts & 1) {
-    const bool vec = nlanes % 4 == 0 && ldx % 4 == 0 && (uintptr_t)X % al == 0;
-    if (vec) launch_nl_w<CPLX, TS, TC, true>(m, (const TS *)X, ldx, nlanes, dinv, F, part, ldp, W, ldw, s);
-    else launch_nl_w<CPLX, TS, TC, false>(m, (const TS *)X, ldx, nlanes, dinv, F, part, ldp, W, ldw, s);
+    if (vec) launch_nl_w<CPLX, TS, TC, true>(g, e, s);
+    else launch_nl_w<CPLX, TS, TC, false>(g, e, s);
   }
   if (parts & 2) {
-    const bool vec = nlanes % 4 == 0 && ldy % 4 == 0 && (uintptr_t)Y % al == 0;
-    if (vec) launch_nl_y<CPLX, TS, TC, true>(m, (TS *)Y, ldy, nlanes, val, W, ldw, (TC)alpha, s);
-    else launch_nl_y<CPLX, TS, TC, false>(m, (TS *)Y, ldy, nlanes, val, W, ldw, (TC)alpha, s);
+    if constexpr (f64) launch_nl_ybm<CPLX>(g, e, s);
+    for (int i = 0; i < n; ++i) {
+      const NlCall &c = calls[i];
+      const TC *val = f64 ? (const TC *)c.m->nl_val64 : (const TC *)c.m->nl_val32;
+      const bool v4 = c.nlanes % 4 == 0 && c.ldy % 4 == 0 && (uintptr_t)c.Y % (4 * sizeof(TS)) == 0;
+      if (v4) launch_nl_y<CPLX, TS, TC, true>(c.m, (TS *)c.Y, c.ldy, c.nlanes, val, g.a[i].W, g.a[i].ldp, (TC)c.alpha, s);
+      else launch_nl_y<CPLX, TS, TC, false>(c.m, (TS *)c.Y, c.ldy, c.nlanes, val, g.a[i].W, g.a[i].ldp, (TC)c.alpha, s);
+    }
   }
   FE_HIP_TRY(hipGetLastError());
   return FE_OK;
@@ -664,14 +781,15 @@ fe_status dispatch_nl(Mesh *m, const void *X, int64_t ldx, void *Y, int64_t ldy,
                       const double *dinv, double alpha, int parts, hipStream_t s, void *ws = nullptr) {
   if (m->ns == 0) return FE_OK;
   if (m->nl_maxproj > NL_MAXP) return set_error(FE_EUNSUPPORTED, "more than 10 projectors on one atom");
+  const NlCall c{m, X, ldx, Y, ldy, nlanes, dinv, alpha, ws};
   if (m->cplx) {
-    if (prec == FE_F64) return run_nl<true, double, double>(m, X, ldx, Y, ldy, nlanes, dinv, alpha, parts, ws, s);
-    if (prec == FE_F32) return run_nl<true, float, float>(m, X, ldx, Y, ldy, nlanes, dinv, alpha, parts, ws, s);
-    return run_nl<true, bf16n, float>(m, X, ldx, Y, ldy, nlanes, dinv, alpha, parts, ws, s);
+    if (prec == FE_F64) return run_nl<true, double, double>(&c, 1, parts, s);
+    if (prec == FE_F32) return run_nl<true, float, float>(&c, 1, parts, s);
+    return run_nl<true, bf16n, float>(&c, 1, parts, s);
   }
-  if (prec == FE_F64) return run_nl<false, double, double>(m, X, ldx, Y, ldy, nlanes, dinv, alpha, parts, ws, s);
-  if (prec == FE_F32) return run_nl<false, float, float>(m, X, ldx, Y, ldy, nlanes, dinv, alpha, parts, ws, s);
-  return run_nl<false, bf16n, float>(m, X, ldx, Y, ldy, nlanes, dinv, alpha, parts, ws, s);
+  if (prec == FE_F64) return run_nl<false, double, double>(&c, 1, parts, s);
+  if (prec == FE_F32) return run_nl<false, float, float>(&c, 1, parts, s);
+  return run_nl<false, bf16n, float>(&c, 1, parts, s);
 }
 }  // namespace
 
@@ -754,6 +872,36 @@ fe_status nonlocal_update(Mesh *m, void *Y, int64_t ldy, int nlanes, int prec, d
   return launch_nonlocal_y(m, Y, ldy, nlanes, prec, alpha, s);
 }
 
+// The reductions (part 1) or updates (part 2) of several distinct systems:
+// FP64 NL_GROUP at a time in one launch each, where the streams are the
+// caller's; the others each by itself (their reductions are forked)
+fe_status nonlocal_batch(Mesh *const *ms, const LocalLaunch *Ls, int n, int part, hipStream_t s) {
+  std::map<int, std::vector<NlCall>> calls;               // by kind and form
+  for (int i = 0; i < n; ++i) {
+    const LocalLaunch &L = Ls[i];
+    fe_status st = FE_OK;
+    if (L.prec != FE_F64) {
+      st = part == 1 ? nonlocal_reduce(ms[i], L.X, L.ldx, L.nlanes, L.prec, nullptr, s)
+                     : nonlocal_update(ms[i], L.Y, L.ldy, L.nlanes, L.prec, 1.0, s);
+      if (st) return st;
+      continue;
+    }
+    if (ms[i]->ns == 0) continue;
+    if (ms[i]->nl_maxproj > NL_MAXP) return set_error(FE_EUNSUPPORTED, "more than 10 projectors on one atom");
+    calls[2 * nl_w_form(ms[i], L.nlanes) + (ms[i]->cplx ? 1 : 0)].push_back({ms[i], L.X, L.ldx, L.Y, L.ldy, L.nlanes, nullptr, 1.0, nullptr});
+  }
+  for (const auto &kind : calls) {
+    const std::vector<NlCall> &c = kind.second;
+    for (size_t i = 0; i < c.size(); i += NL_GROUP) {
+      const int k = (int)std::min<size_t>(NL_GROUP, c.size() - i);
+      const fe_status st = kind.first & 1 ? run_nl<true, double, double>(&c[i], k, part, s)
+                                          : run_nl<false, double, double>(&c[i], k, part, s);
+      if (st) return st;
+    }
+  }
+  return FE_OK;
+}
+
 fe_status apply_with_nonlocal(Mesh *m, const LocalLaunch &L, int prec, const double *dinv, double alpha,
                               hipStream_t s) {
   fe_status st;
@@ -764,8 +912,8 @@ fe_status apply_with_nonlocal(Mesh *m, const LocalLaunch &L, int prec, const dou
 
 // ---- the application that allocates nothing ----------------------------------
 // Scratch for fe_apply_H_noalloc: the projector partials and W of one
-// application, then the local operator's segment planes, in a file-scope device array (each device holds its own copy
-// for the life of the process).  Host code never passes the array's name to a
+// application, then the local operator's segment planes, in a file-scope device
+// array (each device holds its own copy for the life of the process).  Host code never passes the array's name to a
 // kernel: its device address comes from hipGetSymbolAddress, once per device
 // with that device current, and only that address is used.
 static __device__ __align__(256) unsigned char scratch[FE_NOALLOC_SCRATCH_BYTES + PLANE_SIDE_BYTES];
