@@ -596,16 +596,26 @@ __device__ __forceinline__ void local_item(const KArgs<TC> &a, int w) {
 }
 
 // Y += the segments' first planes: plane seg of the side block to the plane
-// of Y at that segment's first node; one block per node row
-template <typename TS, typename TC>
-__global__ void k_planes_join(TS *__restrict__ Y, const TS *__restrict__ side, int64_t plane, int nseg, int N2, int p,
-                              int zoff, int64_t ldy, int nlanes) {
-  const int sg = blockIdx.y;
-  const int64_t gz = (int64_t)seg_start(sg, N2, nseg) * p - zoff;
+// of Y at that segment's first node; one block per node row of a segment's
+// plane, systems of a batch along z
+constexpr int JOIN_MAXB = 16;
+template <typename TS> struct JoinArgs {
+  struct {
+    TS *Y;
+    const TS *side;
+    int64_t ldy;
+    int rows, nseg, N2, p, zoff, nlanes;
+  } sys[JOIN_MAXB];
+};
+template <typename TS, typename TC> __global__ void k_planes_join(JoinArgs<TS> J) {
+  const auto &a = J.sys[blockIdx.z];
+  const int row = blockIdx.x, sg = blockIdx.y;
+  if (row >= a.rows || sg >= a.nseg) return;
+  const int64_t gz = (int64_t)seg_start(sg, a.N2, a.nseg) * a.p - a.zoff;
   if (gz < 0) return;                            // a Dirichlet face: no DoFs
-  TS *q = Y + gz * plane + blockIdx.x * ldy;
-  const TS *r = side + sg * plane + blockIdx.x * ldy;
-  for (int l = threadIdx.x; l < nlanes; l += blockDim.x) Cvt<TS, TC>::st(q, l, Cvt<TS, TC>::ld(q, l) + Cvt<TS, TC>::ld(r, l));
+  TS *q = a.Y + (gz * a.rows + row) * a.ldy;
+  const TS *r = a.side + ((int64_t)sg * a.rows + row) * a.ldy;
+  for (int l = threadIdx.x; l < a.nlanes; l += blockDim.x) Cvt<TS, TC>::st(q, l, Cvt<TS, TC>::ld(q, l) + Cvt<TS, TC>::ld(r, l));
 }
 
 // One system, one colour phase: one block per (column, segment, tile).
@@ -691,11 +701,20 @@ inline fe_status segments_begin(const LocalBatch &Bt, int vt, Count count, std::
 }
 template <typename TS, typename TC>
 inline fe_status segments_end(const LocalBatch &Bt, const std::vector<KArgs<TC>> &as, const std::vector<int> &waits, hipStream_t s) {
-  for (const KArgs<TC> &a : as) {
-    if (a.nseg == 1) continue;
-    const int rows = a.M0 * a.M1;
-    hipLaunchKernelGGL((k_planes_join<TS, TC>), dim3(rows, a.nseg), dim3(a.nlanes <= 64 ? 64 : 256), 0, s, (TS *)a.Y,
-                       (const TS *)a.side, rows * a.ldy, a.nseg, a.N2, a.p, a.dmask & 4 ? 1 : 0, a.ldy, a.nlanes);
+  for (size_t i = 0; i < as.size();) {
+    JoinArgs<TS> J{};
+    unsigned n = 0, rows = 0, segs = 0;
+    int lanes = 0;
+    for (; i < as.size() && n < JOIN_MAXB; ++i) {
+      const KArgs<TC> &a = as[i];
+      if (a.nseg == 1) continue;
+      J.sys[n++] = {(TS *)a.Y, (const TS *)a.side, a.ldy, a.M0 * a.M1, a.nseg, a.N2, a.p, a.dmask & 4 ? 1 : 0, a.nlanes};
+      rows = std::max(rows, (unsigned)(a.M0 * a.M1));
+      segs = std::max(segs, (unsigned)a.nseg);
+      lanes = std::max(lanes, a.nlanes);
+    }
+    if (n == 0) continue;
+    hipLaunchKernelGGL((k_planes_join<TS, TC>), dim3(rows, segs, n), dim3(lanes <= 64 ? 64 : 256), 0, s, J);
     FE_HIP_TRY(hipGetLastError());
   }
   for (int i : waits) {

@@ -223,14 +223,13 @@ k_nl_w(NlGroup<TS, TC> grp) {
   constexpr int U = NW == 4 ? 2 : 4;             // nodes in flight per group
   // projectors summed per step: all of them where their sums fit 32 KiB
   constexpr int SB = (int)sizeof(TC) * PMAX * NW * TILE <= 32768 ? PMAX : 1;
-  // Projector values: wave-uniform scalar loads where a wave holds one row;
-  // with several rows a wave TE entries at a time in LDS (the space of the
-  // sums), since per-group loads of them, a chain of four to ten per X row, were
-  // most of the time (31,500 complex DoFs x 66 lanes 47 -> 25 us; eight
-  // k-points of 74,088 DoFs x 48 lanes 250 -> 164 us)
-  constexpr bool STAGE = GW > 1;
-  constexpr int TE = STAGE ? (PMAX <= 4 ? 512 : 256) : NL_CHUNK;
-  constexpr int NRED = SB * NW * TILE, NF = STAGE ? TE * PMAX * C : 0;
+  // Projector values, TE entries at a time in LDS (the space of the sums):
+  // loaded row by row they were a chain of four to ten per X row and most of
+  // the time (31,500 complex DoFs x 66 lanes 47 -> 25 us; eight k-points of
+  // 74,088 DoFs x 48 lanes 250 -> 164 us; as scalar loads of a wave's one row,
+  // 16^3 cells degree 7, nine projectors, 256 lanes 449 -> 320 us)
+  constexpr int TE = PMAX <= 4 ? 512 : 256;
+  constexpr int NRED = SB * NW * TILE, NF = TE * PMAX * C;
   __shared__ int snode[NL_CHUNK];
   __shared__ TC space[NRED > NF ? NRED : NF];
   auto red = reinterpret_cast<TC(*)[NW][TILE]>(space);
@@ -279,7 +278,7 @@ k_nl_w(NlGroup<TS, TC> grp) {
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const TC *f = STAGE ? space + (idx[u] - t0) * fstride * C : F + (int64_t)(n0 + idx[u]) * fstride * C;
+      const TC *f = space + (idx[u] - t0) * fstride * C;
 #pragma unroll
       for (int s = 0; s < PMAX; ++s)
         if (s < ns) nl_conj_fma<CPLX>(f[s * C], CPLX ? f[s * C + 1] : (TC)0, x[u], acc[s]);
@@ -287,17 +286,15 @@ k_nl_w(NlGroup<TS, TC> grp) {
   };
   for (; t0 < nn; t0 = t1) {
     t1 = min(nn, t0 + TE);
-    if constexpr (STAGE) {
-      if (t0 > 0) __syncthreads();
-      const TC *src = F + (int64_t)(n0 + t0) * fstride * C;
-      for (int e = threadIdx.x; e < (t1 - t0) * fstride * C; e += 64 * NW) space[e] = src[e];
-      __syncthreads();
-    }
+    if (t0 > 0) __syncthreads();
+    const TC *src = F + (int64_t)(n0 + t0) * fstride * C;
+    for (int e = threadIdx.x; e < (t1 - t0) * fstride * C; e += 64 * NW) space[e] = src[e];
+    __syncthreads();
     int i0 = t0;
     for (; i0 + U * G <= t1; i0 += U * G) rows(i0, std::false_type{});
     if (i0 < t1) rows(i0, std::true_type{});
   }
-  if constexpr (STAGE) __syncthreads();
+  __syncthreads();
   // fixed-order sums, SB projectors at a time
 #pragma unroll
   for (int s0 = 0; s0 < PMAX; s0 += SB) {
