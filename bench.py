@@ -88,15 +88,17 @@ def parse():
 
 def kernel_source_sha():
     """Hash of the local-operator kernel source (ties counter figures to the code)."""
-    path = os.path.join(ROOT, "paper_2512_08571_amd", "csrc", "k_local_impl.h")
-    return hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in ("k_local_impl.h", "k_local_planes.h"):
+        h.update(open(os.path.join(ROOT, "paper_2512_08571_amd", "csrc", name), "rb").read())
+    return h.hexdigest()[:16]
 
 
 def recorded_traffic(workload, prec, tile):
-    """HBM bytes per k_local launch from the committed counter summary, or None.
+    """HBM bytes per local-operator launch from the committed counter summary, or None.
 
     profiles/k_local_<workload>_<prec>_traffic.txt holds 'key: value' lines
-    (per tile) written from two rocprofv3 --pmc runs of this script
+    ('planes' for the plane kernels, else per tile) written from two rocprofv3 --pmc runs of this script
     (FETCH_SIZE, then WRITE_SIZE), scaled by the counters' reading for a plain
     copy of known size in the same runs.  The figure is used only while the
     kernel source is the one it was measured on.
@@ -112,7 +114,8 @@ def recorded_traffic(workload, prec, tile):
     if kv.get("source_sha256") != kernel_source_sha():
         return None
     try:
-        return int(float(kv[f"tile_{tile}_fetch_bytes_per_launch"]) + float(kv[f"tile_{tile}_write_bytes_per_launch"]))
+        key = "planes" if "planes_fetch_bytes_per_launch" in kv else f"tile_{tile}"
+        return int(float(kv[f"{key}_fetch_bytes_per_launch"]) + float(kv[f"{key}_write_bytes_per_launch"]))
     except (KeyError, ValueError):
         return None
 
@@ -648,7 +651,7 @@ def main():
             "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
             "algorithmic_bytes_per_launch": dofvec * (16 if a.prec == "f64" else 8 if a.prec == "f32" else 4)
                                             * (2 if cplx else 1) // nphase,
-            "kernel": "k_local", "launch_ms": round(ms_launch, 4),
+            "kernel": "k_local" if a.nq_plus else "k_planes", "launch_ms": round(ms_launch, 4),
             "algorithmic_flop_per_launch": fl,
             "hbm_gbs_algorithmic": round(dofvec * (16 if a.prec == "f64" else 8 if a.prec == "f32" else 4)
                                          * (2 if cplx else 1) / nphase / (ms_launch * 1e-3) / 1e9, 1)}
