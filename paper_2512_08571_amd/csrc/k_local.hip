@@ -23,7 +23,11 @@ bool local_mass_ok(const LocalBatch &B);
 // over the colour phases (odd cell counts have five small ones): rounds of the
 // device's units, per_unit items each, times cells per item.  An item's first
 // gather and last plane cost about half a cell; a cell takes about 1 + 2 k with
-// k waves on a SIMD (FP64, 7 points: 20 us alone, 34 us by twos).
+// k waves on a SIMD (FP64, 7 points: 20 us alone, 34 us by twos).  Measured per
+// colour phase, 7 points: FP64 12^3 cells x 256 lanes, 1152 waves in two segments
+// (1.1 rounds) 362 us, in three 285; FP32 16^3 x 256, 1024 waves whole 500 us, in
+// two segments 395; 11 x 13 x 12 cells x 101 lanes (mass, nine phases) five
+// segments 463 us, the model's twelve 408.
 static int segment_count(const Mesh *m, int tiles, int units, int per_unit, int64_t cap, double *cost) {
   auto round = [](int64_t k) { return k ? 1.0 + 2.0 * k : 0.0; };
   int best = 1;
@@ -50,7 +54,9 @@ int plane_segment_count(const Mesh *m, int nq, int nlanes, int64_t ldy, bool f64
                        side_bytes / side_plane(m, ldy, elem_bytes), cost);
 }
 
-// the same for the staged kernels: blocks on CUs
+// the same for the staged kernels: blocks on CUs (distorted 8 x 10 x 8 cells
+// degree 4 x 64 FP64 vectors, whole columns 240 us, segments 117; 9 points
+// 12^3 cells degree 6 x 128 2157 and 1770)
 int block_segment_count(const Mesh *m, int64_t ldy, int tiles, int per_cu, int elem_bytes, int64_t side_bytes) {
   return segment_count(m, tiles, DEVICE_CUS, per_cu, side_bytes / side_plane(m, ldy, elem_bytes), nullptr);
 }
@@ -71,6 +77,8 @@ bool plane_pairs(const LocalBatch &B, size_t elem_bytes) {
 
 // Whether threads of two lanes (a third faster per lane on a full device) beat
 // threads of one (0.55 of the time per cell, twice the waves) for real blocks.
+// FP32, 7 points, a colour phase: 14^3 cells x 8 vectors pairs 38 us, ones 23;
+// 16^3 x 256 pairs 313, ones (255 vectors) 349.
 bool plane_pairs_pay(const LocalBatch &B, int nq, size_t elem_bytes) {
   double one = 0, two = 0;
   for (int i = 0; i < B.n; ++i) {
