@@ -26,8 +26,8 @@ bool local_mass_ok(const LocalBatch &B);
 // k waves on a SIMD (FP64, 7 points: 20 us alone, 34 us by twos).  Measured per
 // colour phase, 7 points: FP64 12^3 cells x 256 lanes, 1152 waves in two segments
 // (1.1 rounds) 362 us, in three 285; FP32 16^3 x 256, 1024 waves whole 500 us, in
-// two segments 395; 11 x 13 x 12 cells x 101 lanes (mass, nine phases) five
-// segments 463 us, the model's twelve 408.
+// two segments 395; the whole mass operator on 11 x 13 x 12 cells x 101 lanes
+// (nine phases) in five segments 463 us, in the model's twelve 408.
 static int segment_count(const Mesh *m, int tiles, int units, int per_unit, int64_t cap, double *cost) {
   auto round = [](int64_t k) { return k ? 1.0 + 2.0 * k : 0.0; };
   int best = 1;
