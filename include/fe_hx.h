@@ -188,7 +188,7 @@ fe_status fe_apply_H(fe_mesh_t mesh, const void *X, int64_t ldx, void *Y,
  * same Y = H X with the same kernels, arguments, layout and errors as
  * fe_apply_H, but it calls no hipMalloc / hipFree / hipStreamCreate and no
  * allocating library routine.  The projector term's per-chunk partials and W
- * live in FE_NOALLOC_SCRATCH_BYTES (followed by 16 MiB for the local operator's
+ * live in FE_NOALLOC_SCRATCH_BYTES (followed by 64 MiB for the local operator's
  * segment planes) of one static device array that the library holds on every device it runs on until the process ends; a call
  * whose projector workspace ((chunks x 10 + projectors) x ceil4(real lanes)
  * x 8 bytes) exceeds it returns FE_EINVAL.  The projector reduction runs on

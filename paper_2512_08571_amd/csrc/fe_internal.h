@@ -128,18 +128,20 @@ constexpr int plane_waves(int nq, bool f64, int lpt) {
   constexpr int w[3][7] = {{5, 3, 3, 2, 2, 1, 1}, {6, 4, 3, 2, 2, 1, 1}, {8, 6, 5, 4, 3, 2, 2}};
   return w[f64 ? 0 : lpt == 2 ? 1 : 2][nq - 3];
 }
-// Segments a column of cells is cut into by the plane kernels, and the block for their first planes (see plane_segments)
-constexpr int64_t PLANE_SIDE_BYTES = 16LL << 20;    // beside the static scratch
-constexpr int64_t PLANE_SIDE_MAX = 64LL << 20;      // of a mesh
-int plane_segment_count(const Mesh *m, int nq, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes, double *cost);
+// Segments a column of cells is cut into (segment_count), and the block for
+// the planes at their cuts
+constexpr int64_t PLANE_SIDE_BYTES = 64LL << 20;    // beside the static scratch
+constexpr int64_t PLANE_SIDE_MAX = 128LL << 20;     // of a mesh
+int64_t side_seg_bytes(const Mesh *m, int64_t side_lanes, int elem_bytes);
+int plane_segment_count(const Mesh *m, int nq, int nlanes, bool f64, int lpt, int64_t side_bytes, double *cost);
 int64_t side_limit(const LocalLaunch &L);
-int block_segment_count(const Mesh *m, int64_t ldy, int tiles, int per_cu, int elem_bytes, int64_t side_bytes);
-int side_segments(Mesh *m, const LocalLaunch &L, int n, int elem_bytes, hipStream_t s, void **side, bool *shared);
+int block_segment_count(const Mesh *m, int tiles, int per_cu, int64_t seg_bytes, int64_t side_bytes);
+int side_segments(Mesh *m, const LocalLaunch &L, int n, int64_t seg_bytes, hipStream_t s, void **side, bool *shared);
 bool plane_mesh(const Mesh *m);
 struct LocalBatch;
 bool plane_pairs(const LocalBatch &B, size_t elem_bytes);
-bool plane_pairs_pay(const LocalBatch &B, int nq, size_t elem_bytes);
-int64_t plane_side_need(const Mesh *m, int nlanes, int64_t ldy, int prec);
+bool plane_pairs_pay(const LocalBatch &B, int nq);
+int64_t plane_side_need(const Mesh *m, int nlanes, int prec);
 fe_status plane_side_enter(Mesh *m, hipStream_t s);
 fe_status plane_side_leave(Mesh *m, hipStream_t s);
 

@@ -17,9 +17,9 @@ bool local_mass_ok(const LocalBatch &B);
 
 // A wave (or block) walks its cells one after another, so a launch with few
 // columns and tiles leaves most of the device idle for the length of a column.
-// Its columns are then cut into segments (each segment's first plane, shared
-// with the one below, goes to a side block of planes laid out as Y's, added to
-// Y after the last colour phase).  The count is the one of least cost, summed
+// Its columns are then cut into segments (the planes at the cuts go to a side
+// block and are formed after the last colour phase, in the order of uncut
+// columns: the count does not show in the result).  The count is the one of least cost, summed
 // over the colour phases (odd cell counts have five small ones): rounds of the
 // device's units, per_unit items each, times cells per item.  An item's first
 // gather and last plane cost about half a cell; a cell takes about 1 + 2 k with
@@ -28,11 +28,14 @@ bool local_mass_ok(const LocalBatch &B);
 // (1.1 rounds) 362 us, in three 285; FP32 16^3 x 256, 1024 waves whole 500 us, in
 // two segments 395; the whole mass operator on 11 x 13 x 12 cells x 101 lanes
 // (nine phases) in five segments 463 us, in the model's twelve 408.
+// (SEG_MAX: past it every unit of the device has a segment of the four or more
+// columns to itself; k_planes_join takes segments x cells below 2^32)
+constexpr int64_t SEG_MAX = 2048;
 static int segment_count(const Mesh *m, int tiles, int units, int per_unit, int64_t cap, double *cost) {
   auto round = [](int64_t k) { return k ? 1.0 + 2.0 * k : 0.0; };
   int best = 1;
   double least = 0;
-  for (int64_t n = 1; n <= std::max<int64_t>(1, std::min<int64_t>(m->N[2], cap)); ++n) {
+  for (int64_t n = 1; n <= std::max<int64_t>(1, std::min<int64_t>({m->N[2], cap, SEG_MAX, (1LL << 31) / m->N[2]})); ++n) {
     double c = 0;
     for (int ph = 0; ph < m->nphase; ++ph) {
       const int64_t k = ((int64_t)(m->phase_off[ph + 1] - m->phase_off[ph]) * tiles * n + units - 1) / units;
@@ -45,20 +48,24 @@ static int segment_count(const Mesh *m, int tiles, int units, int per_unit, int6
   return best;
 }
 
-static int64_t side_plane(const Mesh *m, int64_t ldy, int elem_bytes) { return (int64_t)m->Mn[0] * m->Mn[1] * ldy * elem_bytes; }
+// Bytes of the side block per segment: [cut][half][column][x][y][lane] in the
+// compute type, cut s the first plane of segment s, half 0 what that segment
+// adds to it and half 1 what the one below does (cut 0: the periodic wrap).
+int64_t side_seg_bytes(const Mesh *m, int64_t side_lanes, int elem_bytes) {
+  return 2LL * m->N[0] * m->N[1] * m->np * m->np * side_lanes * elem_bytes;
+}
 
-int plane_segment_count(const Mesh *m, int nq, int nlanes, int64_t ldy, bool f64, int lpt, int elem_bytes, int64_t side_bytes,
-                        double *cost) {
-  const int vt = plane_vt(nq, lpt);
-  return segment_count(m, (nlanes + vt - 1) / vt, 4 * DEVICE_CUS, plane_waves(nq, f64, lpt),
-                       side_bytes / side_plane(m, ldy, elem_bytes), cost);
+int plane_segment_count(const Mesh *m, int nq, int nlanes, bool f64, int lpt, int64_t side_bytes, double *cost) {
+  const int vt = plane_vt(nq, lpt), tiles = (nlanes + vt - 1) / vt;
+  return segment_count(m, tiles, 4 * DEVICE_CUS, plane_waves(nq, f64, lpt),
+                       side_bytes / side_seg_bytes(m, (int64_t)tiles * vt, f64 ? 8 : 4), cost);
 }
 
 // the same for the staged kernels: blocks on CUs (distorted 8 x 10 x 8 cells
 // degree 4 x 64 FP64 vectors, whole columns 240 us, segments 117; 9 points
 // 12^3 cells degree 6 x 128 2157 and 1770)
-int block_segment_count(const Mesh *m, int64_t ldy, int tiles, int per_cu, int elem_bytes, int64_t side_bytes) {
-  return segment_count(m, tiles, DEVICE_CUS, per_cu, side_bytes / side_plane(m, ldy, elem_bytes), nullptr);
+int block_segment_count(const Mesh *m, int tiles, int per_cu, int64_t seg_bytes, int64_t side_bytes) {
+  return segment_count(m, tiles, DEVICE_CUS, per_cu, side_bytes / seg_bytes, nullptr);
 }
 
 int64_t side_limit(const LocalLaunch &L) { return L.side ? L.side_bytes : PLANE_SIDE_MAX; }
@@ -79,33 +86,32 @@ bool plane_pairs(const LocalBatch &B, size_t elem_bytes) {
 // threads of one (0.55 of the time per cell, twice the waves) for real blocks.
 // FP32, 7 points, a colour phase: 14^3 cells x 8 vectors pairs 38 us, ones 23;
 // 16^3 x 256 pairs 313, ones (255 vectors) 349.
-bool plane_pairs_pay(const LocalBatch &B, int nq, size_t elem_bytes) {
+bool plane_pairs_pay(const LocalBatch &B, int nq) {
   double one = 0, two = 0;
   for (int i = 0; i < B.n; ++i) {
     const LocalLaunch &L = B.Ls[i];
     const int64_t side = side_limit(L);
     double c1, c2;
-    plane_segment_count(B.ms[i], nq, L.nlanes, L.ldy, false, 1, (int)elem_bytes, side, &c1);
-    plane_segment_count(B.ms[i], nq, L.nlanes, L.ldy, false, 2, (int)elem_bytes, side, &c2);
+    plane_segment_count(B.ms[i], nq, L.nlanes, false, 1, side, &c1);
+    plane_segment_count(B.ms[i], nq, L.nlanes, false, 2, side, &c2);
     one += 0.55 * c1;
     two += c2;
   }
   return two <= one;
 }
 
-// bytes of the side block of an application to a block of nlanes lanes with
-// leading dimension ldy (lanes): for the plane kernels with either width of a
-// thread and, for FE_BF16, either block type; one segment per cell elsewhere
-int64_t plane_side_need(const Mesh *m, int nlanes, int64_t ldy, int prec) {
+// bytes of the side block of an application to a block of nlanes lanes: for the
+// plane kernels with either width of a thread; one segment per cell elsewhere
+// (the widest tile there holds 32 lanes)
+int64_t plane_side_need(const Mesh *m, int nlanes, int prec) {
   const bool f64 = prec == FE_F64;
   int64_t need = 0;
-  for (int es = prec == FE_BF16 ? 2 : f64 ? 8 : 4; es <= (f64 ? 8 : 4); es *= 2) {
-    const int64_t plane = side_plane(m, ldy, es);
-    for (int lpt = 1; lpt <= (f64 ? 1 : 2); ++lpt) {
-      const int64_t n = plane_mesh(m) ? plane_segment_count(m, m->nq, nlanes, ldy, f64, lpt, es, PLANE_SIDE_MAX, nullptr)
-                                      : std::min<int64_t>(m->N[2], PLANE_SIDE_MAX / plane);
-      if (n > 1) need = std::max(need, n * plane);
-    }
+  for (int lpt = 1; lpt <= (f64 ? 1 : 2); ++lpt) {
+    const int vt = plane_mesh(m) ? plane_vt(m->nq, lpt) : 32;
+    const int64_t seg = side_seg_bytes(m, (int64_t)(nlanes + vt - 1) / vt * vt, f64 ? 8 : 4);
+    const int64_t n = plane_mesh(m) ? plane_segment_count(m, m->nq, nlanes, f64, lpt, PLANE_SIDE_MAX, nullptr)
+                                    : std::min<int64_t>(m->N[2], PLANE_SIDE_MAX / seg);
+    if (n > 1) need = std::max(need, n * seg);
   }
   return need;
 }
@@ -136,13 +142,13 @@ fe_status plane_side_leave(Mesh *m, hipStream_t s) {
 // (then *shared: enter and leave around the use).  A block that cannot be had
 // now (the stream is capturing, a captured graph holds the mesh's smaller one,
 // no memory) means one segment.
-int side_segments(Mesh *m, const LocalLaunch &L, int n, int elem_bytes, hipStream_t s, void **side, bool *shared) {
+int side_segments(Mesh *m, const LocalLaunch &L, int n, int64_t seg_bytes, hipStream_t s, void **side, bool *shared) {
   *side = L.side;
   *shared = false;
   if (n == 1 || L.side) return n;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return 1;
-  const int64_t need = n * side_plane(m, L.ldy, elem_bytes);
+  const int64_t need = n * seg_bytes;
   if (m->ws_bytes[11] < need && (m->graphs > 0 || ensure_workspace(m, 11, need))) return 1;
   *side = m->ws[11];
   *shared = true;

@@ -15,7 +15,10 @@
 //
 // Scatter Y += Q^(e)T Y^(e) without atomics and deterministically:
 //  * along a_2 the shared node plane of consecutive cells is summed in LDS
-//    (and the periodic first/last plane of the column at the end);
+//    (and the periodic first/last plane of the column at the end); where a
+//    column is cut into segments, the two halves of a cut's plane go to a side
+//    block in the compute type and k_planes_join adds them up in the order of
+//    the uncut column, so that the cuts do not show in the result;
 //  * across columns the columns are coloured 2 (or 3 for an odd count) per
 //    axis and launched colour by colour; a node shared by several columns is
 //    stored by the column of the lowest colour phase and read-modify-written
@@ -148,8 +151,8 @@ template <typename TC> struct KArgs {
   const TC *pgather;
   const TC *pcoef;
   TC pkap[3];
-  int nseg;            // plane kernels: segments a column is cut into, and the block of their first planes
-  void *side;
+  int nseg;            // segments a column is cut into, and the planes at their cuts (side_seg_bytes)
+  TC *side;
 };
 
 // ---- even-odd application of a packed centro-(anti)symmetric 1D matrix ----------
@@ -434,10 +437,12 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
     if (!zoff && gz >= a.M2) gz -= a.M2;
     return (int64_t)exy[r] + MM * gz;
   };
-  // where this thread's node row is written: Y, or for the first plane of one
-  // of several segments the side block (planes laid out as Y's)
-  auto row_of = [&](int r, int cz, bool first) -> TS * {
-    return first && ek(r) == 0 ? (TS *)a.side + ((int64_t)exy[r] + MM * seg) * a.ldy : Y + node_of(r, cz) * a.ldy;
+  // this thread's element of half 0 (a segment's first plane) or 1 (the last
+  // plane of the one below) of cut sg (layout at side_seg_bytes)
+  auto side_of = [&](int r, int sg, int half) -> TC * {
+    const int n = (tid + r * NT) / NV, ij = (n % NP) * NP + (n / NP) % NP;
+    const int64_t plane = (int64_t)(2 * sg + half) * (a.N0 * a.N1) + cx + a.N0 * cy;
+    return a.side + (plane * NP2 + ij) * (a.ntiles * VT) + elane(r);
   };
   // plane k of cell cz holds DoFs (always on a periodic a_2)
   auto zin = [&](int k, int cz) { const int gz = cz * p + k - zoff; return !zoff || (gz >= 0 && gz < a.M2); };
@@ -487,7 +492,8 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
     }
     const int kskip0 = (one && cz == 0) ? 0 : -1;      // plane held back for the wrap
     const int kskip1 = (cz < c1 - 1) ? NP - 1 : -1;    // plane carried to the next cell
-    const bool first = !one && cz == c0;               // plane 0 goes to the side block
+    // planes of this cell at a cut, which go to the side block
+    auto at_cut = [&](int k) { return !one && ((k == 0 && cz == c0) || (k == NP - 1 && cz == c1 - 1)); };
     __syncthreads();
     // Y0 = (N x N x N) X^(e): along x and y
     line_pass<NP, NQ, 1, VT, NT>(A, B, tN, NP2, [](int l, int &sb, int &ss, int &db, int &ds) {
@@ -505,8 +511,8 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
       for (int r = 0; r < XPT; ++r) {
 #pragma unroll
         for (int jj = 0; jj < LPE; ++jj) ypre[r][jj] = 0;
-        if (eok(r) && ermw(r) && ek(r) != kskip0 && ek(r) != kskip1 && zin(ek(r), cz))
-          VecIO<TS, TC, LPE>::ld(row_of(r, cz, first) + elane(r), ypre[r]);
+        if (eok(r) && ermw(r) && ek(r) != kskip0 && ek(r) != kskip1 && zin(ek(r), cz) && !at_cut(ek(r)))
+          VecIO<TS, TC, LPE>::ld(Y + node_of(r, cz) * a.ldy + elane(r), ypre[r]);
       }
     };
     // every sweep its own pass; the off-diagonal metric needs all three
@@ -563,9 +569,19 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
       const int e = tid + r * NT;
       TC val[LPE], out[LPE];
       LdsVec<TC, LPE>::ld(B + e * LPE, val);
+      if (at_cut(ek(r))) {
+        TC *q = side_of(r, ek(r) == 0 ? seg : seg + 1 < a.nseg ? seg + 1 : 0, ek(r) == 0 ? 0 : 1);
+        if constexpr (LPE * sizeof(TC) == 16) {
+          VecIO<TC, TC, LPE>::st(q, val);
+        } else {
+#pragma unroll
+          for (int jj = 0; jj < LPE; ++jj) q[jj] = val[jj];
+        }
+        continue;
+      }
 #pragma unroll
       for (int jj = 0; jj < LPE; ++jj) out[jj] = ermw(r) ? ypre[r][jj] + val[jj] : val[jj];
-      VecIO<TS, TC, LPE>::st(row_of(r, cz, first) + elane(r), out);
+      VecIO<TS, TC, LPE>::st(Y + node_of(r, cz) * a.ldy + elane(r), out);
     }
     __syncthreads();
   }
@@ -595,27 +611,89 @@ __device__ __forceinline__ void local_item(const KArgs<TC> &a, int w) {
   local_column<NP, NQ, VT, CPLX, TS, TC, LPE, SH>(a, col, cs - col * a.nseg, tile);
 }
 
-// Y += the segments' first planes: plane seg of the side block to the plane
-// of Y at that segment's first node; one block per node row of a segment's
-// plane, systems of a batch along z
-constexpr int JOIN_MAXB = 16;
-template <typename TS> struct JoinArgs {
+// The planes of Y at the cuts: per node the one to four columns that hold it
+// in the order of their colour phases, each with the sum of its two halves and
+// each sum so far rounded to the block's type, which is what uncut columns do.
+// The plane kernels begin at zero and, where the block has the arithmetic's
+// type, meet the halves of the column's own wrap (cut 0) one after the other.
+// A node of a cut's plane is 2^tl threads of two lanes, as few as hold its
+// lanes up to a wave; its loads are in flight together.
+constexpr int JOIN_MAXB = 16, JOIN_THREADS = 256;
+template <typename TS, typename TC> struct JoinArgs {
   struct {
     TS *Y;
-    const TS *side;
+    const TC *side;
     int64_t ldy;
-    int rows, nseg, N2, p, zoff, nlanes;
+    int M0, M1, N0, N1, N2, p, dmask, nseg, side_lanes, nlanes;
   } sys[JOIN_MAXB];
+  int tl;
+  int planes;
+  int segs;                                      // along the grid's z, per system
+  unsigned rsegs, rp;                            // 2^32 / segs, 2^32 / p, rounded up: quotients by __umulhi
 };
-template <typename TS, typename TC> __global__ void k_planes_join(JoinArgs<TS> J) {
-  const auto &a = J.sys[blockIdx.z];
-  const int row = blockIdx.x, sg = blockIdx.y;
-  if (row >= a.rows || sg >= a.nseg) return;
-  const int64_t gz = (int64_t)seg_start(sg, a.N2, a.nseg) * a.p - a.zoff;
+template <typename TS, typename TC> __global__ void __launch_bounds__(JOIN_THREADS) k_planes_join(JoinArgs<TS, TC> J) {
+  typedef TC Two __attribute__((ext_vector_type(2)));
+  const int zs = __umulhi(blockIdx.z, J.rsegs), sg = blockIdx.z - zs * J.segs;
+  const auto &a = J.sys[zs];
+  const int gx = (blockIdx.x * JOIN_THREADS + threadIdx.x) >> J.tl, gy = blockIdx.y;
+  if (gx >= a.M0 || gy >= a.M1 || sg >= a.nseg) return;
+  const int64_t gz = (int64_t)((unsigned)(sg * a.N2) / (unsigned)a.nseg) * a.p - (a.dmask & 4 ? 1 : 0);
   if (gz < 0) return;                            // a Dirichlet face: no DoFs
-  TS *q = a.Y + (gz * a.rows + row) * a.ldy;
-  const TS *r = a.side + ((int64_t)sg * a.rows + row) * a.ldy;
-  for (int l = threadIdx.x; l < a.nlanes; l += blockDim.x) Cvt<TS, TC>::st(q, l, Cvt<TS, TC>::ld(q, l) + Cvt<TS, TC>::ld(r, l));
+  // the cells of a node along an axis, the lower colour first, and its index in each
+  auto cells = [&](int g, int n, int (&c)[2], int (&i)[2]) {
+    c[0] = c[1] = __umulhi((unsigned)g, J.rp);
+    i[0] = i[1] = g - c[0] * a.p;
+    if (i[0]) return 1;
+    const int left = c[0] == 0 ? n - 1 : c[0] - 1;
+    const bool swap = colour_of(left, n) < colour_of(c[0], n);
+    c[0] = swap ? left : c[1];
+    i[0] = swap ? a.p : 0;
+    c[1] = swap ? c[1] : left;
+    i[1] = swap ? 0 : a.p;
+    return 2;
+  };
+  int cx[2], ix[2], cy[2], iy[2];
+  const int nx = cells(gx + (a.dmask & 1), a.N0, cx, ix);
+  const int ny = cells(gy + ((a.dmask >> 1) & 1), a.N1, cy, iy);
+  const int NP = a.p + 1, n = nx * ny;
+  const int64_t half = (int64_t)a.N0 * a.N1 * NP * NP * a.side_lanes;
+  auto at = [&](int x, int y) {
+    return a.side + 2 * sg * half + ((int64_t)((cx[x] + a.N0 * cy[y]) * NP + ix[x]) * NP + iy[y]) * a.side_lanes;
+  };
+  // in phase order: x within y
+  const TC *const s[4] = {at(0, 0), nx == 2 ? at(1, 0) : at(0, ny - 1), at(0, ny - 1), at(nx - 1, ny - 1)};
+  const bool apart = J.planes && sizeof(TS) == sizeof(TC) && sg == 0;
+  TS *q = a.Y + (gz * ((int64_t)a.M0 * a.M1) + gx + (int64_t)a.M0 * gy) * a.ldy;
+  const int step = 2 << J.tl;
+  for (int l = 2 * (threadIdx.x & ((1 << J.tl) - 1)); l < a.nlanes; l += step) {
+    Two up[4], lo[4];
+    auto load = [&](int k) {
+      up[k] = *(const Two *)(s[k] + l);
+      lo[k] = *(const Two *)(s[k] + half + l);
+    };
+    load(0);
+    if (n > 1) load(1);
+    if (n > 2) {
+      load(2);
+      load(3);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      TS sum;
+      auto add = [&](int k) {
+        const TC u = j ? up[k].y : up[k].x, v = j ? lo[k].y : lo[k].x;
+        const TC old = k == 0 ? (TC)0 : Cvt<TS, TC>::ld(&sum, 0);
+        Cvt<TS, TC>::st(&sum, 0, apart ? (old + u) + v : k == 0 && !J.planes ? u + v : old + (u + v));
+      };
+      add(0);
+      if (n > 1) add(1);
+      if (n > 2) {
+        add(2);
+        add(3);
+      }
+      if (l + j < a.nlanes) q[l + j] = sum;
+    }
+  }
 }
 
 // One system, one colour phase: one block per (column, segment, tile).
@@ -681,8 +759,8 @@ template <typename TC> KArgs<TC> make_args(Mesh *m, const LocalLaunch &L, int vt
 }
 
 // Arguments of every system with its segments (count(mesh, launch, tiles)) and
-// side block; segments_end adds the segments' first planes to Y.
-template <typename TS, typename TC, typename Count>
+// side block; segments_end forms the planes at the cuts.
+template <typename TC, typename Count>
 inline fe_status segments_begin(const LocalBatch &Bt, int vt, Count count, std::vector<KArgs<TC>> &as,
                                 std::vector<int> &waits, hipStream_t s) {
   for (int i = 0; i < Bt.n; ++i) {
@@ -690,7 +768,9 @@ inline fe_status segments_begin(const LocalBatch &Bt, int vt, Count count, std::
     as.push_back(make_args<TC>(m, Bt.Ls[i], vt));
     const int n = count(m, Bt.Ls[i], as.back().ntiles);
     bool shared = false;
-    as.back().nseg = side_segments(m, Bt.Ls[i], n, sizeof(TS), s, &as.back().side, &shared);
+    void *side = nullptr;
+    as.back().nseg = side_segments(m, Bt.Ls[i], n, side_seg_bytes(m, as.back().ntiles * vt, sizeof(TC)), s, &side, &shared);
+    as.back().side = (TC *)side;
     if (shared) {
       const fe_status st = plane_side_enter(m, s);
       if (st) return st;
@@ -700,21 +780,28 @@ inline fe_status segments_begin(const LocalBatch &Bt, int vt, Count count, std::
   return FE_OK;
 }
 template <typename TS, typename TC>
-inline fe_status segments_end(const LocalBatch &Bt, const std::vector<KArgs<TC>> &as, const std::vector<int> &waits, hipStream_t s) {
+inline fe_status segments_end(const LocalBatch &Bt, int vt, const std::vector<KArgs<TC>> &as, const std::vector<int> &waits,
+                              bool planes, hipStream_t s) {
   for (size_t i = 0; i < as.size();) {
-    JoinArgs<TS> J{};
-    unsigned n = 0, rows = 0, segs = 0;
+    JoinArgs<TS, TC> J{};
+    J.planes = planes;
+    unsigned n = 0, mx = 0, my = 0;
     int lanes = 0;
     for (; i < as.size() && n < JOIN_MAXB; ++i) {
       const KArgs<TC> &a = as[i];
       if (a.nseg == 1) continue;
-      J.sys[n++] = {(TS *)a.Y, (const TS *)a.side, a.ldy, a.M0 * a.M1, a.nseg, a.N2, a.p, a.dmask & 4 ? 1 : 0, a.nlanes};
-      rows = std::max(rows, (unsigned)(a.M0 * a.M1));
-      segs = std::max(segs, (unsigned)a.nseg);
+      J.sys[n++] = {(TS *)a.Y, a.side, a.ldy, a.M0, a.M1, a.N0, a.N1, a.N2, a.p, a.dmask, a.nseg, a.ntiles * vt, a.nlanes};
+      mx = std::max(mx, (unsigned)a.M0);
+      my = std::max(my, (unsigned)a.M1);
+      J.segs = std::max(J.segs, a.nseg);
       lanes = std::max(lanes, a.nlanes);
+      J.rp = (unsigned)((1ULL << 32) / a.p + 1);   // one degree per launch
     }
     if (n == 0) continue;
-    hipLaunchKernelGGL((k_planes_join<TS, TC>), dim3(rows, segs, n), dim3(lanes <= 64 ? 64 : 256), 0, s, J);
+    J.rsegs = (unsigned)((1ULL << 32) / J.segs + 1);
+    while (J.tl < 6 && 2 << J.tl < lanes) ++J.tl;
+    const unsigned nodes = JOIN_THREADS >> J.tl;
+    hipLaunchKernelGGL((k_planes_join<TS, TC>), dim3((mx + nodes - 1) / nodes, my, n * J.segs), dim3(JOIN_THREADS), 0, s, J);
     FE_HIP_TRY(hipGetLastError());
   }
   for (int i : waits) {
@@ -759,7 +846,7 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
   std::vector<int> waits;
   auto count = [](int per_cu) {      // blocks of this kernel on a CU
     return [per_cu](Mesh *m, const LocalLaunch &L, int tiles) {
-      return block_segment_count(m, L.ldy, tiles, per_cu, sizeof(TS), side_limit(L));
+      return block_segment_count(m, tiles, per_cu, side_seg_bytes(m, tiles * VT, sizeof(TC)), side_limit(L));
     };
   };
   if (Bt.n == 1 && !Bt.persistent) {
@@ -772,7 +859,7 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
       attr_set = shm;
     }
     if (!per_cu[offd]) FE_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu[offd], (const void *)kern, NTB, shm));
-    const fe_status st = segments_begin<TS, TC>(Bt, VT, count(per_cu[offd]), as, waits, s);
+    const fe_status st = segments_begin<TC>(Bt, VT, count(per_cu[offd]), as, waits, s);
     if (st) return st;
     KArgs<TC> &a = as[0];
     for (int ph = 0; ph < m->nphase; ++ph) {
@@ -784,7 +871,7 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
       hipLaunchKernelGGL(kern, dim3(nb), dim3(NTB), shm, s, a);
       FE_HIP_TRY(hipGetLastError());
     }
-    return segments_end<TS, TC>(Bt, as, waits, s);
+    return segments_end<TS, TC>(Bt, VT, as, waits, false, s);
   }
   auto kern = k_local_batch<NP, NQ, VT, CPLX, TS, TC, LPE, SH>;
   static size_t battr_set = 65536;
@@ -799,7 +886,7 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
     resident[offd] = (per_cu > 0 ? per_cu : 1) * device_cus(Bt.ms[0]->device);
   }
   {
-    const fe_status st = segments_begin<TS, TC>(Bt, VT, count(std::max(1, resident[offd] / device_cus(Bt.ms[0]->device))), as, waits, s);
+    const fe_status st = segments_begin<TC>(Bt, VT, count(std::max(1, resident[offd] / device_cus(Bt.ms[0]->device))), as, waits, s);
     if (st) return st;
   }
   const int cap = Bt.blocks_per_cu > 0 ? Bt.blocks_per_cu * device_cus(Bt.ms[0]->device) : resident[offd];
@@ -830,7 +917,7 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
       FE_HIP_TRY(hipGetLastError());
     }
   }
-  return segments_end<TS, TC>(Bt, as, waits, s);
+  return segments_end<TS, TC>(Bt, VT, as, waits, false, s);
 }
 
 // The wide (16-byte) element form when every block of every system allows it.

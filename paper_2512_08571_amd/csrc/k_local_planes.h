@@ -34,7 +34,8 @@
 //
 // Scatter: as in k_local_impl.h (columns coloured, one launch per colour
 // phase, nodes of several columns stored by the lowest phase and
-// read-modify-written by later ones; fixed summation order, no atomics).
+// read-modify-written by later ones; fixed summation order, no atomics; the
+// planes at the cuts of a segmented column in the same order, by k_planes_join).
 //
 // What bounds it: with every wave slot filled, FP64 issue and the load/store
 // path in about equal parts (real, 7 points, 16^3 cells x 256 vectors, one of
@@ -601,6 +602,13 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
   const unsigned or0 = ins && (fy || fx0) && x0 ? yo : BUF_OFF, or1 = ins && (fy || fx1) && x1 ? yo : BUF_OFF,
                  orm = ins && fy ? yo : BUF_OFF;
   const unsigned ow0 = x0 ? ow : BUF_OFF, ow1 = x1 ? ow : BUF_OFF;
+  // the planes at the cuts (layout at side_seg_bytes)
+  typedef LaneIO<TC, V> SideIO;
+  const int side_lanes = a.ntiles * S::VT, side_x = NP * side_lanes;
+  const unsigned so = t0 < NT && pl < NP ? (unsigned)(pl * side_lanes + lane) * (unsigned)sizeof(TC) : BUF_OFF;
+  auto side_at = [&](int sg, int half) {
+    return a.side + ((int64_t)(2 * sg + half) * (a.N0 * a.N1) + cx + a.N0 * cy) * (NP * NP) * side_lanes;
+  };
   TC ksgn = 0;                                           // sign of the Bloch term in this lane
   if constexpr (CPLX && LPT == 1) ksgn = (lane & 1) ? (TC)-1 : (TC)1;
 
@@ -647,6 +655,14 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
   V carry[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) carry[i] = 0;
+  // Blocks narrower than the arithmetic (BF16): an uncut periodic column's
+  // first plane, held for the last cell's, so that their sum rounds once as at
+  // every other plane.  (Elsewhere it waits in Y, exactly.)
+  constexpr bool HOLD = sizeof(TS) != sizeof(TC);
+  const bool wrap = a.nseg == 1 && !zoff;
+  V held[HOLD ? NP : 1];
+#pragma unroll
+  for (int i = 0; i < (HOLD ? NP : 1); ++i) held[i] = 0;
 
   V w[NQ][NQ];                                           // the plane [x][y]
   typename IO::R wr[NP][NP];                             // the next cell's, as stored
@@ -828,14 +844,17 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
     const int64_t sy = opaque(a.ldy), sz = opaque(MM * a.ldy);
     const bool z0 = cz * p >= zoff;                      // the first plane holds DoFs
     TS *const Yz = (TS *)a.Y + (cz * p - zoff) * sz;
-    // a segment's first plane, which the segment below stores, goes to the
-    // side block (same layout as a plane of Y)
-    TS *const Y0 = a.nseg > 1 && cz == c0 ? (TS *)a.side + seg * sz : z0 ? Yz : Yz + sz;
+    TS *const Y0 = z0 ? Yz : Yz + sz;
+    // a cut segment's first plane goes to the side block instead
+    const bool cut0 = a.nseg > 1 && cz == c0;
+    const bool hold0 = HOLD && wrap && cz == 0;
+    TC *const side0 = side_at(seg, 0);
+    const unsigned rd0 = cut0 ? BUF_OFF : or0, rd1 = cut0 ? BUF_OFF : or1, rdm = cut0 ? BUF_OFF : orm;
     typename IO::R old[NP][NP - 1];                      // [x][z]
     auto xnode = [&](int i) { return (i == 0 ? gxf : i == NP - 1 ? gxl : gx0 + i) * sy; };
     auto read_back = [&](int i) {
       const unsigned o = i == 0 ? or0 : i == NP - 1 ? or1 : orm;
-      old[i][0] = IO::ldb(buf_at(opaque(Y0) + xnode(i)), (int)o);
+      old[i][0] = IO::ldb(buf_at(opaque(Y0) + xnode(i)), (int)(i == 0 ? rd0 : i == NP - 1 ? rd1 : rdm));
       TS *q = opaque(Yz) + xnode(i);
 #pragma unroll
       for (int k = 1; k < NP - 1; ++k) old[i][k] = IO::ldb(buf_at(q += sz), (int)o);
@@ -901,7 +920,14 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
       y[0] += carry[i];
       carry[i] = y[NP - 1];
       const unsigned oi = i == 0 ? ow0 : i == NP - 1 ? ow1 : ow;
-      IO::stb(buf_at(opaque(Y0) + xnode(i)), (int)(z0 ? oi : BUF_OFF), IO::up(old[i][0]) + y[0]);
+      if constexpr (HOLD) {
+        held[i] = hold0 ? y[0] : held[i];
+        IO::stb(buf_at(opaque(Y0) + xnode(i)), (int)(z0 && !cut0 && !hold0 ? oi : BUF_OFF), IO::up(old[i][0]) + y[0]);
+        SideIO::stb(buf_at(opaque(side0) + i * side_x), (int)(cut0 ? so : BUF_OFF), y[0]);
+      } else {
+        TS *const q0 = cut0 ? opaque(side0) + i * side_x : opaque(Y0) + xnode(i);
+        IO::stb(buf_at(q0), (int)(cut0 ? so : z0 ? oi : BUF_OFF), IO::up(old[i][0]) + y[0]);
+      }
       TS *q = opaque(Yz) + xnode(i);
 #pragma unroll
       for (int k = 1; k < NP - 1; ++k) IO::stb(buf_at(q += sz), (int)oi, IO::up(old[i][k]) + y[k]);
@@ -909,19 +935,23 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
     }
     wave_order();
   }
-  // The segment's last plane: the next segment's first one, which that leaves
-  // to this one.  Past the column's end it is the column's first plane on a
-  // periodic axis (with one segment this thread has stored it already: read
-  // back by all), and has no DoF on a Dirichlet axis.
-  int gz = c1 * p - zoff;
-  if (gz >= a.M2) gz = 0;
-  if (c1 < a.N2 || !zoff) {
+  // The last plane: of a segment, the cut it shares with the next one's first;
+  // of a whole column on a periodic axis the column's first plane (stored by
+  // this thread already and read back by all, or held).  A Dirichlet axis has
+  // no DoFs there.
+  if (a.nseg > 1) {
+    TC *const side1 = side_at(seg + 1 < a.nseg ? seg + 1 : 0, 1);
+#pragma unroll
+    for (int i = 0; i < NP; ++i) SideIO::stb(buf_at(side1 + i * side_x), (int)so, carry[i]);
+  } else if (wrap) {
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-      const BufRsrc r = buf_at((TS *)a.Y + gz * MM * a.ldy + (int64_t)(i == 0 ? gxf : i == NP - 1 ? gxl : gx0 + i) * a.ldy);
+      const BufRsrc r = buf_at((TS *)a.Y + (int64_t)(i == 0 ? gxf : i == NP - 1 ? gxl : gx0 + i) * a.ldy);
       const unsigned oi = i == 0 ? ow0 : i == NP - 1 ? ow1 : ow;
-      const unsigned o = a.nseg == 1 ? oi : i == 0 ? or0 : i == NP - 1 ? or1 : orm;
-      IO::stb(r, (int)oi, IO::up(IO::ldb(r, (int)o)) + carry[i]);
+      const unsigned o = !HOLD ? oi : i == 0 ? or0 : i == NP - 1 ? or1 : orm;
+      V z = carry[i];
+      if constexpr (HOLD) z += held[i];
+      IO::stb(r, (int)oi, IO::up(IO::ldb(r, (int)o)) + z);
     }
   }
 }
@@ -982,8 +1012,8 @@ inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
   FE_HIP_TRY(plane_lds(kern, shm));
   std::vector<KArgs<TC>> as;
   std::vector<int> waits;
-  fe_status st = segments_begin<TS, TC>(Bt, S::VT, [&](Mesh *m, const LocalLaunch &L, int) {
-    return plane_segment_count(m, NQ, L.nlanes, L.ldy, sizeof(TC) == 8, LPT, sizeof(TS), side_limit(L), nullptr);
+  fe_status st = segments_begin<TC>(Bt, S::VT, [&](Mesh *m, const LocalLaunch &L, int) {
+    return plane_segment_count(m, NQ, L.nlanes, sizeof(TC) == 8, LPT, side_limit(L), nullptr);
   }, as, waits, s);
   if (st) return st;
   int nphase = 0;
@@ -1016,14 +1046,13 @@ inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
       FE_HIP_TRY(hipGetLastError());
     }
   }
-  return segments_end<TS, TC>(Bt, as, waits, s);
+  return segments_end<TS, TC>(Bt, S::VT, as, waits, true, s);
 }
 
 // The plane kernel where it applies (affine cells with a diagonal metric, the
 // operator H), at every number of lanes; the staged kernel for the general
-// metric (its mixed second-derivative terms need two directions at once), the
-// mass operator, and blocks whose z plane of nodes exceeds the span that a
-// buffer offset reaches.
+// metric (its mixed second-derivative terms need two directions at once) and
+// blocks whose z plane of nodes exceeds the span that a buffer offset reaches.
 inline bool planes_ok(const LocalBatch &B, size_t es) {
   for (int i = 0; i < B.n; ++i) {
     const Mesh *m = B.ms[i];
@@ -1055,7 +1084,7 @@ template <int NP, int NQ> fe_status pick_planes_f64(const LocalBatch &B, hipStre
 template <int NP, int NQ, typename TS> bool run_planes_f32(const LocalBatch &B, hipStream_t s, fe_status *st) {
   if (!planes_ok(B, sizeof(TS))) return false;
   const bool cplx = B.ms[0]->cplx;
-  const bool pairs = plane_pairs(B, sizeof(TS)) && (cplx || plane_pairs_pay(B, NQ, sizeof(TS)));
+  const bool pairs = plane_pairs(B, sizeof(TS)) && (cplx || plane_pairs_pay(B, NQ));
   if (cplx && !pairs) return false;
   *st = cplx ? run_planes<NP, NQ, true, TS, float, 2>(B, s)
              : pairs ? run_planes<NP, NQ, false, TS, float, 2>(B, s) : run_planes<NP, NQ, false, TS, float, 1>(B, s);

@@ -80,9 +80,9 @@ void request_needs(const fe_request &q, int64_t need[fehx::Mesh::NWS], int64_t &
     need[3] = q.prec != FE_F64 ? n * eb : 0;
     need[4] = (int64_t)(q.degree + 1) * q.nvec * 8;
     if (m->mass_kind == FE_MASS_CONSISTENT) need[9] = n * 8;
-    need[11] = std::max(fehx::plane_side_need(m, (int)lanes, lanes, FE_F64), fehx::plane_side_need(m, (int)lanes, lanes, q.prec));
+    need[11] = std::max(fehx::plane_side_need(m, (int)lanes, FE_F64), fehx::plane_side_need(m, (int)lanes, q.prec));
   } else {
-    need[11] = fehx::plane_side_need(m, (int)lanes, q.ldy * C, q.prec);
+    need[11] = fehx::plane_side_need(m, (int)lanes, q.prec);
   }
   nl_need = m->ns > 0 ? fehx::nl_workspace_bytes(m, (int)lanes) : 0;
 }

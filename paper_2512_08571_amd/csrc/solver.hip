@@ -293,7 +293,7 @@ fe_status filter_setup(FilterPlan &P, Mesh *m, double *X, int64_t ldx_l, const d
     return st;                                                                  // M X (FP64)
   if ((st = ensure_nl_workspace(m, P.lanes))) return st;
   // the segment planes of the FP64 prologue and of the steps
-  P.side_need = std::max(plane_side_need(m, P.lanes, P.lanes, FE_F64), plane_side_need(m, P.lanes, P.lanes, prec));
+  P.side_need = std::max(plane_side_need(m, P.lanes, FE_F64), plane_side_need(m, P.lanes, prec));
   if (m->graphs == 0 && (st = ensure_workspace(m, 11, P.side_need))) return st;
   P.Y = (double *)m->ws[share ? 2 : 0];
   P.RY = m->ws[1];
