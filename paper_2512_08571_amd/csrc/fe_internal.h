@@ -139,7 +139,12 @@ int block_segment_count(const Mesh *m, int tiles, int per_cu, int64_t seg_bytes,
 int side_segments(Mesh *m, const LocalLaunch &L, int n, int64_t seg_bytes, hipStream_t s, void **side, bool *shared);
 bool plane_mesh(const Mesh *m);
 struct LocalBatch;
-bool plane_pairs(const LocalBatch &B, size_t elem_bytes);
+// The kernel of one application: the staged one with a diagonal or a general
+// metric, or the plane kernels (the mass operator's sweeps) in threads of one
+// lane or, where the block's rows start on pairs of lanes, of one or two.
+enum LocalKind { LOCAL_STAGED, LOCAL_GENERAL, LOCAL_PLANES, LOCAL_PLANES_PAIRS, LOCAL_MASS, LOCAL_MASS_PAIRS };
+LocalKind local_kind(const Mesh *m, const LocalLaunch &L);
+constexpr int64_t PLANE_SPAN = 0x7fffffff;   // bytes of a z plane that the plane kernels' buffer offsets reach
 bool plane_pairs_pay(const LocalBatch &B, int nq);
 int64_t plane_side_need(const Mesh *m, int nlanes, int prec);
 fe_status plane_side_enter(Mesh *m, hipStream_t s);
@@ -151,6 +156,7 @@ struct LocalBatch {
   Mesh *const *ms = nullptr;
   const LocalLaunch *Ls = nullptr;
   int n = 0;
+  LocalKind kind = LOCAL_STAGED;   // of every system (set by launch_local_batch)
   bool persistent = false;   // use the persistent batched kernel even for n = 1
   int blocks_per_cu = 0;     // persistent grid per CU (0: occupancy limit)
 };

@@ -13,7 +13,6 @@ fe_status launch_local_f64(const LocalBatch &B, hipStream_t s);
 fe_status launch_local_f32(const LocalBatch &B, hipStream_t s);
 fe_status launch_local_bf16(const LocalBatch &B, hipStream_t s);
 fe_status launch_local_mass(const LocalBatch &B, hipStream_t s);
-bool local_mass_ok(const LocalBatch &B);
 
 // A wave (or block) walks its cells one after another, so a launch with few
 // columns and tiles leaves most of the device idle for the length of a column.
@@ -72,18 +71,24 @@ int64_t side_limit(const LocalLaunch &L) { return L.side ? L.side_bytes : PLANE_
 
 bool plane_mesh(const Mesh *m) { return !m->offd && m->nq == m->np; }
 
-// Whether every block of the launch can be read in pairs of lanes.
-bool plane_pairs(const LocalBatch &B, size_t elem_bytes) {
-  for (int i = 0; i < B.n; ++i) {
-    const LocalLaunch &L = B.Ls[i];
-    if ((L.ldx | L.ldy | L.nlanes) & 1) return false;
-    if (((uintptr_t)L.X | (uintptr_t)L.Y) % (2 * elem_bytes)) return false;
-  }
-  return true;
+// The choice depends on the system and its blocks alone, never on those it
+// shares a launch with.  The plane kernels take affine cells with a diagonal
+// metric (the mass operator: affine cells) and, in FP32 and BF16, complex
+// vectors as pairs of lanes; a z plane past their span goes to the staged kernel.
+LocalKind local_kind(const Mesh *m, const LocalLaunch &L) {
+  const size_t es = L.prec == FE_F64 ? 8 : L.prec == FE_F32 || L.store32 ? 4 : 2;
+  const bool reach = (int64_t)m->Mn[0] * m->Mn[1] * L.ldy * (int64_t)es < PLANE_SPAN;
+  const bool pairs = L.prec != FE_F64 && !((L.ldx | L.ldy | L.nlanes) & 1) &&
+                     ((uintptr_t)L.X | (uintptr_t)L.Y) % (2 * es) == 0;
+  if (L.mass) return m->distorted || !reach ? LOCAL_STAGED : pairs ? LOCAL_MASS_PAIRS : LOCAL_MASS;
+  if (m->offd) return LOCAL_GENERAL;
+  if (m->nq != m->np || !reach || (m->cplx && L.prec != FE_F64 && !pairs)) return LOCAL_STAGED;
+  return pairs ? LOCAL_PLANES_PAIRS : LOCAL_PLANES;
 }
 
 // Whether threads of two lanes (a third faster per lane on a full device) beat
-// threads of one (0.55 of the time per cell, twice the waves) for real blocks.
+// threads of one (0.55 of the time per cell, twice the waves) for real blocks;
+// both form the same sums.
 // FP32, 7 points, a colour phase: 14^3 cells x 8 vectors pairs 38 us, ones 23;
 // 16^3 x 256 pairs 313, ones (255 vectors) 349.
 bool plane_pairs_pay(const LocalBatch &B, int nq) {
@@ -155,6 +160,14 @@ int side_segments(Mesh *m, const LocalLaunch &L, int n, int64_t seg_bytes, hipSt
   return n;
 }
 
+static fe_status launch_local_kind(const LocalBatch &B, hipStream_t s) {
+  if (B.kind >= LOCAL_MASS) return launch_local_mass(B, s);
+  if (B.Ls[0].prec == FE_F64) return launch_local_f64(B, s);
+  if (B.Ls[0].prec == FE_F32) return launch_local_f32(B, s);
+  if (B.Ls[0].prec == FE_BF16) return launch_local_bf16(B, s);
+  return set_error(FE_EINVAL, "unknown precision");
+}
+
 fe_status launch_local_batch(const LocalBatch &B, hipStream_t s) {
   if (B.n < 1) return FE_OK;
   Mesh *m0 = B.ms[0];
@@ -167,28 +180,25 @@ fe_status launch_local_batch(const LocalBatch &B, hipStream_t s) {
     if (B.Ls[i].prec != B.Ls[0].prec || B.Ls[i].vt != B.Ls[0].vt || B.Ls[i].store32 != B.Ls[0].store32)
       return set_error(FE_EINVAL, "a batched launch needs one precision, block type and vector tile");
   }
-  if (local_mass_ok(B)) return launch_local_mass(B, s);
-  // general-metric systems and the rest run different kernels: one launch set each
-  auto general = [&](int i) { return B.ms[i]->offd && !B.Ls[i].mass; };
-  int ngen = 0;
-  for (int i = 0; i < B.n; ++i) ngen += general(i) ? 1 : 0;
-  if (ngen > 0 && ngen < B.n) {
-    for (int kind = 0; kind < 2; ++kind) {
-      std::vector<Mesh *> ms;
-      std::vector<LocalLaunch> Ls;
-      for (int i = 0; i < B.n; ++i)
-        if (general(i) == (kind == 1)) { ms.push_back(B.ms[i]); Ls.push_back(B.Ls[i]); }
-      LocalBatch P = B;
-      P.ms = ms.data(); P.Ls = Ls.data(); P.n = (int)ms.size();
-      const fe_status st = launch_local_batch(P, s);
-      if (st) return st;
-    }
-    return FE_OK;
+  // systems that run different kernels: one launch set each
+  LocalBatch P = B;
+  P.kind = local_kind(B.ms[0], B.Ls[0]);
+  int same = 1;
+  while (same < B.n && local_kind(B.ms[same], B.Ls[same]) == P.kind) ++same;
+  if (same == B.n) return launch_local_kind(P, s);
+  std::vector<Mesh *> ms;
+  std::vector<LocalLaunch> Ls;
+  for (int kind = LOCAL_STAGED; kind <= LOCAL_MASS_PAIRS; ++kind) {
+    ms.clear();
+    Ls.clear();
+    for (int i = 0; i < B.n; ++i)
+      if (local_kind(B.ms[i], B.Ls[i]) == kind) { ms.push_back(B.ms[i]); Ls.push_back(B.Ls[i]); }
+    P.ms = ms.data(); P.Ls = Ls.data(); P.n = (int)ms.size();
+    P.kind = (LocalKind)kind;
+    const fe_status st = P.n ? launch_local_kind(P, s) : (fe_status)FE_OK;
+    if (st) return st;
   }
-  if (B.Ls[0].prec == FE_F64) return launch_local_f64(B, s);
-  if (B.Ls[0].prec == FE_F32) return launch_local_f32(B, s);
-  if (B.Ls[0].prec == FE_BF16) return launch_local_bf16(B, s);
-  return set_error(FE_EINVAL, "unknown precision");
+  return FE_OK;
 }
 
 fe_status launch_local(Mesh *m, const LocalLaunch &L, hipStream_t s) {

@@ -11,17 +11,11 @@ template <int NP> fe_status run_mass(const LocalBatch &B, hipStream_t s) {
   const LocalLaunch &L = B.Ls[0];
   if (L.prec == FE_F64) return run_planes<NP, NP, false, double, double, 1, true>(B, s);
   const bool f32 = L.prec == FE_F32 || L.store32;
-  const size_t es = f32 ? sizeof(float) : sizeof(bf16s);
-  const bool pairs = plane_pairs(B, es) && plane_pairs_pay(B, NP);
+  const bool pairs = B.kind == LOCAL_MASS_PAIRS && plane_pairs_pay(B, NP);
   if (f32) return pairs ? run_planes<NP, NP, false, float, float, 2, true>(B, s) : run_planes<NP, NP, false, float, float, 1, true>(B, s);
   return pairs ? run_planes<NP, NP, false, bf16s, float, 2, true>(B, s) : run_planes<NP, NP, false, bf16s, float, 1, true>(B, s);
 }
 }  // namespace
-
-bool local_mass_ok(const LocalBatch &B) {
-  const LocalLaunch &L = B.Ls[0];
-  return plane_mass_ok(B, L.prec == FE_F64 ? 8 : L.prec == FE_F32 || L.store32 ? 4 : 2);
-}
 
 fe_status launch_local_mass(const LocalBatch &B, hipStream_t s) {
   switch (B.ms[0]->np) {

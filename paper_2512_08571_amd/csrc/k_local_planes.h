@@ -481,7 +481,7 @@ template <typename T> __device__ __forceinline__ const T *scalar_ptr(const T *p)
 // waited for the whole next gather at the first store).
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef __amdgpu_buffer_rsrc_t BufRsrc;
-constexpr unsigned BUF_SPAN = 0x7fffffffu, BUF_OFF = 0x80000000u;
+constexpr unsigned BUF_SPAN = (unsigned)PLANE_SPAN, BUF_OFF = 0x80000000u;
 __device__ __forceinline__ BufRsrc buf_at(void *p) {
   return __builtin_amdgcn_make_buffer_rsrc(p, (short)0, (int)BUF_SPAN, 0x00027000);
 }
@@ -1049,43 +1049,17 @@ inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
   return segments_end<TS, TC>(Bt, S::VT, as, waits, true, s);
 }
 
-// The plane kernel where it applies (affine cells with a diagonal metric, the
-// operator H), at every number of lanes; the staged kernel for the general
-// metric (its mixed second-derivative terms need two directions at once) and
-// blocks whose z plane of nodes exceeds the span that a buffer offset reaches.
-inline bool planes_ok(const LocalBatch &B, size_t es) {
-  for (int i = 0; i < B.n; ++i) {
-    const Mesh *m = B.ms[i];
-    if (m->offd || B.Ls[i].mass) return false;
-    // one z plane of the block within a buffer descriptor's span
-    if ((int64_t)m->Mn[0] * m->Mn[1] * B.Ls[i].ldy * (int64_t)es >= (int64_t)BUF_SPAN) return false;
-  }
-  return true;
-}
-
-// The mass operator of affine cells, any rule; complex blocks as their lanes.
-inline bool plane_mass_ok(const LocalBatch &B, size_t es) {
-  for (int i = 0; i < B.n; ++i) {
-    const Mesh *m = B.ms[i];
-    if (!B.Ls[i].mass || m->distorted) return false;
-    if ((int64_t)m->Mn[0] * m->Mn[1] * B.Ls[i].ldy * (int64_t)es >= (int64_t)BUF_SPAN) return false;
-  }
-  return true;
-}
-
 template <int NP, int NQ> fe_status pick_planes_f64(const LocalBatch &B, hipStream_t s) {
-  if (!planes_ok(B, sizeof(double))) return pick_cplx_f64<NP, NQ>(B, s);
+  if (B.kind != LOCAL_PLANES) return pick_cplx_f64<NP, NQ>(B, s);
   return B.ms[0]->cplx ? run_planes<NP, NQ, true, double, double, 1>(B, s)
                        : run_planes<NP, NQ, false, double, double, 1>(B, s);
 }
 
-// FP32 and BF16: threads of two adjacent lanes (a complex vector) where every
-// block's rows start on such a pair, else, real, of one.
+// FP32 and BF16: threads of two adjacent lanes (a complex vector) or, real, of one
 template <int NP, int NQ, typename TS> bool run_planes_f32(const LocalBatch &B, hipStream_t s, fe_status *st) {
-  if (!planes_ok(B, sizeof(TS))) return false;
+  if (B.kind != LOCAL_PLANES && B.kind != LOCAL_PLANES_PAIRS) return false;
   const bool cplx = B.ms[0]->cplx;
-  const bool pairs = plane_pairs(B, sizeof(TS)) && (cplx || plane_pairs_pay(B, NQ));
-  if (cplx && !pairs) return false;
+  const bool pairs = B.kind == LOCAL_PLANES_PAIRS && (cplx || plane_pairs_pay(B, NQ));
   *st = cplx ? run_planes<NP, NQ, true, TS, float, 2>(B, s)
              : pairs ? run_planes<NP, NQ, false, TS, float, 2>(B, s) : run_planes<NP, NQ, false, TS, float, 1>(B, s);
   return true;

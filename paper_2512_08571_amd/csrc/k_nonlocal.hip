@@ -714,6 +714,12 @@ struct NlCall {
   void *ws;
 };
 
+// vector accesses of the reduction need every thread's lanes in range and
+// aligned: pairs in FP64, all four else
+template <typename TS> bool nl_w_vec(const void *X, int64_t ldx, int nlanes, int w) {
+  return nlanes % w == 0 && ldx % w == 0 && (uintptr_t)X % (w * sizeof(TS)) == 0;
+}
+
 // part 1: W = diag(h) F^H (D^-1) X;  part 2: Y += alpha F W;  3: both.
 // Up to NL_GROUP systems of one kind, precision and reduction form.
 template <bool CPLX, typename TS, typename TC>
@@ -723,8 +729,6 @@ fe_status run_nl(const NlCall *calls, int n, int parts, hipStream_t s) {
   NlExtent e;
   e.n = n;
   e.form = nl_w_form(calls[0].m, calls[0].nlanes);
-  // vector accesses need every thread's lanes in range and aligned: pairs in
-  // FP64, all four else
   bool vec = true;
   for (int i = 0; i < n; ++i) {
     const NlCall &c = calls[i];
@@ -753,8 +757,7 @@ fe_status run_nl(const NlCall *calls, int n, int parts, hipStream_t s) {
     e.kmax = std::max(e.kmax, m->nl_b_kmax);
     e.bricks = std::max<int64_t>(e.bricks, (m->nl_nbrick + 7) / 8);
     e.nw = std::max(e.nw, (int64_t)m->ns * c.nlanes);
-    constexpr int w = f64 ? 2 : 4;
-    vec = vec && c.nlanes % w == 0 && c.ldx % w == 0 && (uintptr_t)c.X % (w * sizeof(TS)) == 0;
+    vec = vec && nl_w_vec<TS>(c.X, c.ldx, c.nlanes, f64 ? 2 : 4);
   }
   if (parts & 1) {
     if (vec) launch_nl_w<CPLX, TS, TC, true>(g, e, s);
@@ -873,7 +876,7 @@ fe_status nonlocal_update(Mesh *m, void *Y, int64_t ldy, int nlanes, int prec, d
 // FP64 NL_GROUP at a time in one launch each, where the streams are the
 // caller's; the others each by itself (their reductions are forked)
 fe_status nonlocal_batch(Mesh *const *ms, const LocalLaunch *Ls, int n, int part, hipStream_t s) {
-  std::map<int, std::vector<NlCall>> calls;               // by kind and form
+  std::map<int, std::vector<NlCall>> calls;               // by kind, access width and form
   for (int i = 0; i < n; ++i) {
     const LocalLaunch &L = Ls[i];
     fe_status st = FE_OK;
@@ -885,7 +888,8 @@ fe_status nonlocal_batch(Mesh *const *ms, const LocalLaunch *Ls, int n, int part
     }
     if (ms[i]->ns == 0) continue;
     if (ms[i]->nl_maxproj > NL_MAXP) return set_error(FE_EUNSUPPORTED, "more than 10 projectors on one atom");
-    calls[2 * nl_w_form(ms[i], L.nlanes) + (ms[i]->cplx ? 1 : 0)].push_back({ms[i], L.X, L.ldx, L.Y, L.ldy, L.nlanes, nullptr, 1.0, nullptr});
+    const int vec = nl_w_vec<double>(L.X, L.ldx, L.nlanes, 2) ? 2 : 0;
+    calls[4 * nl_w_form(ms[i], L.nlanes) + vec + (ms[i]->cplx ? 1 : 0)].push_back({ms[i], L.X, L.ldx, L.Y, L.ldy, L.nlanes, nullptr, 1.0, nullptr});
   }
   for (const auto &kind : calls) {
     const std::vector<NlCall> &c = kind.second;
