@@ -53,6 +53,10 @@
  *  - Host arrays passed in are copied before return; the caller keeps
  *    ownership.  Device buffers the mesh allocates are freed by
  *    fe_mesh_destroy.
+ *  - While meshes exist, the library holds one scratch block of 128 MiB per mesh,
+ *    at most four, on their device (outside the meshes' footprint): an
+ *    application of few columns cuts them into segments and keeps the planes at
+ *    the cuts there.  Results do not depend on it.
  */
 #ifndef FE_HX_H
 #define FE_HX_H

@@ -44,7 +44,7 @@ void Mesh::dev_free_all() {
 
 fe_status ensure_workspace(Mesh *m, int slot, int64_t bytes) {
   if (m->ws_bytes[slot] >= bytes) return FE_OK;
-  const bool filter_slot = slot <= 4 || slot == 8 || slot == 9 || slot == 11;   // the slots a filter pass uses
+  const bool filter_slot = slot <= 4 || slot == 8 || slot == 9;   // the slots a filter pass uses
   if (m->ws[slot] && filter_slot && m->graphs > 0)
     return set_error(FE_ESTATE, "a captured filter graph holds this mesh's workspace; destroy it before a call that "
                                 "needs a larger one");
@@ -547,6 +547,7 @@ fe_status fe_mesh_create(const fe_mesh_desc *desc, fe_mesh_t *out) {
     if (st == FE_OK) st = set_error(FE_EINVAL, e.what());
     return st;
   }
+  if (!host_only) side_pool_enter(m->device);
   *out = m;
   return FE_OK;
 }
@@ -559,9 +560,9 @@ fe_status fe_mesh_destroy(fe_mesh_t mesh) {
     hipDeviceSynchronize();
     if (mesh->ev_fork) hipEventDestroy(mesh->ev_fork);
     if (mesh->ev_join) hipEventDestroy(mesh->ev_join);
-    if (mesh->side_ev) hipEventDestroy(mesh->side_ev);
     if (mesh->side) hipStreamDestroy(mesh->side);
     mesh->dev_free_all();
+    side_pool_leave(mesh->device);
   }
   delete mesh;
   return FE_OK;

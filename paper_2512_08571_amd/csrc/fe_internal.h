@@ -111,7 +111,7 @@ struct LocalLaunch {
   const double *dinv_gather = nullptr;  // scale gathered X by D^-1 (filter)
   bool mass = false;          // the consistent mass operator M instead of H
   int vt = 0, nt = 0;         // vector tile / threads (0: tuned default)
-  void *side = nullptr;       // segment planes the caller provides (null: the mesh's own)
+  void *side = nullptr;       // a side block of the caller's own (null: one of the device's, SideUse)
   int64_t side_bytes = 0;
   bool store32 = false;       // FE_BF16 arithmetic on FP32 blocks (the filter's recurrence state)
 };
@@ -130,13 +130,28 @@ constexpr int plane_waves(int nq, bool f64, int lpt) {
 }
 // Segments a column of cells is cut into (segment_count), and the block for
 // the planes at their cuts
-constexpr int64_t PLANE_SIDE_BYTES = 64LL << 20;    // beside the static scratch
-constexpr int64_t PLANE_SIDE_MAX = 128LL << 20;     // of a mesh
+constexpr int64_t NOALLOC_SIDE_BYTES = 64LL << 20;   // beside the static scratch
+constexpr int64_t SIDE_BYTES = 128LL << 20;          // of the device's blocks
 int64_t side_seg_bytes(const Mesh *m, int64_t side_lanes, int elem_bytes);
 int plane_segment_count(const Mesh *m, int nq, int nlanes, bool f64, int lpt, int64_t side_bytes, double *cost);
-int64_t side_limit(const LocalLaunch &L);
+inline int64_t side_limit(const LocalLaunch &L) { return L.side ? L.side_bytes : SIDE_BYTES; }
 int block_segment_count(const Mesh *m, int tiles, int per_cu, int64_t seg_bytes, int64_t side_bytes);
-int side_segments(Mesh *m, const LocalLaunch &L, int n, int64_t seg_bytes, hipStream_t s, void **side, bool *shared);
+void side_pool_enter(int device);
+void side_pool_leave(int device);
+// One application's hold on a side block of the device (k_local.hip), given
+// back, with an event behind the work enqueued so far, when it goes.
+struct SideBlock;
+class SideUse {
+ public:
+  SideUse() = default;
+  SideUse(const SideUse &) = delete;
+  ~SideUse();
+  void *take(int device, hipStream_t s);   // SIDE_BYTES, or null: none is free, or s is capturing
+ private:
+  SideBlock *block_ = nullptr;
+  int device_ = 0;
+  hipStream_t s_ = nullptr;
+};
 bool plane_mesh(const Mesh *m);
 struct LocalBatch;
 // The kernel of one application: the staged one with a diagonal or a general
@@ -147,8 +162,6 @@ LocalKind local_kind(const Mesh *m, const LocalLaunch &L);
 constexpr int64_t PLANE_SPAN = 0x7fffffff;   // bytes of a z plane that the plane kernels' buffer offsets reach
 bool plane_pairs_pay(const LocalBatch &B, int nq);
 int64_t plane_side_need(const Mesh *m, int nlanes, int prec);
-fe_status plane_side_enter(Mesh *m, hipStream_t s);
-fe_status plane_side_leave(Mesh *m, hipStream_t s);
 
 // Several local-operator applications of one class (degree, quadrature,
 // real/complex, precision, vector tile) launched together.
@@ -195,8 +208,8 @@ struct FilterPlan {
   std::vector<double> alpha, s2;   // per step k = 2..degree: 2 sigma2 / e, sigma sigma2
   double *Y = nullptr, *tab = nullptr;
   void *RY = nullptr, *RX = nullptr, *Ylp = nullptr, *T = nullptr;
-  void *side = nullptr;            // captured passes: the mesh's segment planes (LocalLaunch::side)
-  int64_t side_need = 0;           // their bytes
+  void *side = nullptr;            // captured passes: the graph's own side block (LocalLaunch::side)
+  int64_t side_bytes = 0;
   int k = 2;                       // next recurrence step
 };
 fe_status filter_setup(FilterPlan &P, Mesh *m, double *X, int64_t ldx_lanes, const double *lam, int64_t nvec,
@@ -314,13 +327,9 @@ struct Mesh {
   // FP32 / BF16 filter: no slots 0 and 8; slot 2 holds R_X and, at
   // filter_t_offset, H D^-1 R_Y, and the FP64 Y (read only by the prologue)
   // spans both (slot 2 padded to 8 bytes per element where they are smaller).
-  // 11 the plane kernels' segment planes.
-  static constexpr int NWS = 12;
+  static constexpr int NWS = 11;
   void *ws[NWS] = {};
   int64_t ws_bytes[NWS] = {};
-  hipStream_t side_stream = nullptr;   // slot 11: the stream of its last use, and the event after it once a
-  hipEvent_t side_ev = nullptr;        // second stream has used it (plane_side_enter)
-  bool side_used = false;
 
   int64_t footprint = 0;
   std::vector<std::pair<void *, size_t>> owned;

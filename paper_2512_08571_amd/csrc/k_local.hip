@@ -1,6 +1,7 @@
 // Matrix-free local operator: dispatch by precision (kernels in k_local_impl.h,
 // instantiated in k_local_f64.hip, k_local_f32.hip, k_local_bf16.hip).
 #include <algorithm>
+#include <mutex>
 #include <vector>
 
 #include "fe_internal.h"
@@ -67,8 +68,6 @@ int block_segment_count(const Mesh *m, int tiles, int per_cu, int64_t seg_bytes,
   return segment_count(m, tiles, DEVICE_CUS, per_cu, side_bytes / seg_bytes, nullptr);
 }
 
-int64_t side_limit(const LocalLaunch &L) { return L.side ? L.side_bytes : PLANE_SIDE_MAX; }
-
 bool plane_mesh(const Mesh *m) { return !m->offd && m->nq == m->np; }
 
 // The choice depends on the system and its blocks alone, never on those it
@@ -114,50 +113,119 @@ int64_t plane_side_need(const Mesh *m, int nlanes, int prec) {
   for (int lpt = 1; lpt <= (f64 ? 1 : 2); ++lpt) {
     const int vt = plane_mesh(m) ? plane_vt(m->nq, lpt) : 32;
     const int64_t seg = side_seg_bytes(m, (int64_t)(nlanes + vt - 1) / vt * vt, f64 ? 8 : 4);
-    const int64_t n = plane_mesh(m) ? plane_segment_count(m, m->nq, nlanes, f64, lpt, PLANE_SIDE_MAX, nullptr)
-                                    : std::min<int64_t>(m->N[2], PLANE_SIDE_MAX / seg);
+    const int64_t n = plane_mesh(m) ? plane_segment_count(m, m->nq, nlanes, f64, lpt, SIDE_BYTES, nullptr)
+                                    : std::min<int64_t>(m->N[2], SIDE_BYTES / seg);
     if (n > 1) need = std::max(need, n * seg);
   }
   return need;
 }
 
-// The mesh's side block is shared by every application of the mesh, which may
-// come on any stream: applications on one stream are in order by themselves;
-// the first one on another stream waits for the device, and from then on each
-// records an event that one on another stream waits for.
-fe_status plane_side_enter(Mesh *m, hipStream_t s) {
-  if (m->side_used && m->side_stream != s) {
-    if (!m->side_ev) {
-      FE_HIP_TRY(hipEventCreateWithFlags(&m->side_ev, hipEventDisableTiming));
-      FE_HIP_TRY(hipDeviceSynchronize());
-    } else {
-      FE_HIP_TRY(hipStreamWaitEvent(s, m->side_ev, 0));
-    }
-  }
-  m->side_used = true;
-  m->side_stream = s;
-  return FE_OK;
+// ---- side blocks ------------------------------------------------------------
+// They belong to the device: as many as it has meshes, up to SIDE_BLOCKS,
+// allocated when a mesh is made and freed with the last one, so that an
+// application allocates nothing, whichever mesh it is on.  An application that
+// cuts its columns holds one while it enqueues and leaves an event behind; the
+// next on that stream follows in stream order, one on another stream takes a
+// block whose event has passed.  Without a block (all in use by other streams, no
+// memory for one, or a stream that is capturing, whose graph may be replayed
+// beside anything) columns stay whole, with the same result.
+// (The event orders work on the device only: without the fence to the host it
+// costs 0.7 us of an application, with it 2.5.)
+constexpr int SIDE_BLOCKS = 4, SIDE_DEVICES = 64;
+struct SideBlock {
+  void *p = nullptr;
+  hipEvent_t done = nullptr;
+  hipStream_t s = nullptr;   // of the last use
+  bool used = false, held = false;
+};
+namespace {
+struct SidePool {
+  std::mutex mu;
+  int meshes = 0;
+  SideBlock blocks[SIDE_BLOCKS];
+};
+SidePool g_side[SIDE_DEVICES];
+
+// the event has passed; asked without upsetting a capture on another stream
+bool event_passed(hipEvent_t e) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  const hipError_t r = hipEventQuery(e);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (r != hipSuccess) (void)hipGetLastError();
+  return r == hipSuccess;
 }
-fe_status plane_side_leave(Mesh *m, hipStream_t s) {
-  if (m->side_ev) FE_HIP_TRY(hipEventRecord(m->side_ev, s));
-  return FE_OK;
+}  // namespace
+
+void side_pool_enter(int device) {
+  if (device < 0 || device >= SIDE_DEVICES) return;
+  SidePool &P = g_side[device];
+  std::lock_guard<std::mutex> g(P.mu);
+  const int i = P.meshes++;
+  if (i >= SIDE_BLOCKS || P.blocks[i].p) return;
+  SideBlock b;
+  if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess) {
+    if (hipMalloc(&b.p, (size_t)SIDE_BYTES) == hipSuccess) {
+      P.blocks[i] = b;
+      return;
+    }
+    hipEventDestroy(b.done);
+  }
+  (void)hipGetLastError();                       // columns stay whole
 }
 
-// The side block of a launch with n segments, and their count: the launch's own block, or the mesh's
-// (then *shared: enter and leave around the use).  A block that cannot be had
-// now (the stream is capturing, a captured graph holds the mesh's smaller one,
-// no memory) means one segment.
-int side_segments(Mesh *m, const LocalLaunch &L, int n, int64_t seg_bytes, hipStream_t s, void **side, bool *shared) {
-  *side = L.side;
-  *shared = false;
-  if (n == 1 || L.side) return n;
+// (the device has been synchronised)
+void side_pool_leave(int device) {
+  if (device < 0 || device >= SIDE_DEVICES) return;
+  SidePool &P = g_side[device];
+  std::lock_guard<std::mutex> g(P.mu);
+  if (--P.meshes > 0) return;
+  for (SideBlock &b : P.blocks) {
+    if (b.p) {
+      hipFree(b.p);
+      hipEventDestroy(b.done);
+    }
+    b = SideBlock();
+  }
+}
+
+void *SideUse::take(int device, hipStream_t s) {
+  if (block_) return block_->p;
+  if (device < 0 || device >= SIDE_DEVICES) return nullptr;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return 1;
-  const int64_t need = n * seg_bytes;
-  if (m->ws_bytes[11] < need && (m->graphs > 0 || ensure_workspace(m, 11, need))) return 1;
-  *side = m->ws[11];
-  *shared = true;
-  return n;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (cs != hipStreamCaptureStatusNone) return nullptr;
+  SidePool &P = g_side[device];
+  std::lock_guard<std::mutex> g(P.mu);
+  SideBlock *found = nullptr;
+  for (SideBlock &b : P.blocks)
+    if (b.p && !b.held && b.used && b.s == s) { found = &b; break; }
+  // (a handle may be a new stream's: for one and the same stream the wait is nothing)
+  if (found && hipStreamWaitEvent(s, found->done, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    found = nullptr;
+  }
+  if (!found)
+    for (SideBlock &b : P.blocks)
+      if (b.p && !b.held && (!b.used || event_passed(b.done))) { found = &b; break; }
+  if (!found) return nullptr;
+  found->held = true;
+  block_ = found;
+  device_ = device;
+  s_ = s;
+  return found->p;
+}
+
+SideUse::~SideUse() {
+  if (!block_) return;
+  std::lock_guard<std::mutex> g(g_side[device_].mu);
+  block_->used = true;
+  block_->s = s_;
+  // without an event behind the work the block is not given out again
+  block_->held = hipEventRecord(block_->done, s_) != hipSuccess;
 }
 
 static fe_status launch_local_kind(const LocalBatch &B, hipStream_t s) {

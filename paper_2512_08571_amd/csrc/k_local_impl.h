@@ -758,30 +758,34 @@ template <typename TC> KArgs<TC> make_args(Mesh *m, const LocalLaunch &L, int vt
   return a;
 }
 
-// Arguments of every system with its segments (count(mesh, launch, tiles)) and
-// side block; segments_end forms the planes at the cuts.
+// Arguments of every system with its segments, count(mesh, launch, tiles, bytes
+// of side block), and its part of the side block: where the systems of a batch
+// want more than one holds, each in proportion.  segments_end forms the planes
+// at the cuts.
 template <typename TC, typename Count>
-inline fe_status segments_begin(const LocalBatch &Bt, int vt, Count count, std::vector<KArgs<TC>> &as,
-                                std::vector<int> &waits, hipStream_t s) {
+inline void segments_begin(const LocalBatch &Bt, int vt, Count count, std::vector<KArgs<TC>> &as, SideUse &use, hipStream_t s) {
+  auto seg_bytes = [&](int i) { return side_seg_bytes(Bt.ms[i], (int64_t)as[i].ntiles * vt, sizeof(TC)); };
+  int64_t want = 0;
   for (int i = 0; i < Bt.n; ++i) {
-    Mesh *m = Bt.ms[i];
-    as.push_back(make_args<TC>(m, Bt.Ls[i], vt));
-    const int n = count(m, Bt.Ls[i], as.back().ntiles);
-    bool shared = false;
-    void *side = nullptr;
-    as.back().nseg = side_segments(m, Bt.Ls[i], n, side_seg_bytes(m, as.back().ntiles * vt, sizeof(TC)), s, &side, &shared);
-    as.back().side = (TC *)side;
-    if (shared) {
-      const fe_status st = plane_side_enter(m, s);
-      if (st) return st;
-      waits.push_back(i);
-    }
+    as.push_back(make_args<TC>(Bt.ms[i], Bt.Ls[i], vt));
+    as[i].nseg = count(Bt.ms[i], Bt.Ls[i], as[i].ntiles, side_limit(Bt.Ls[i]));
+    as[i].side = (TC *)Bt.Ls[i].side;
+    if (as[i].nseg > 1 && !as[i].side) want += as[i].nseg * seg_bytes(i);
   }
-  return FE_OK;
+  if (want == 0) return;
+  char *next = (char *)use.take(Bt.ms[0]->device, s);
+  for (int i = 0; i < Bt.n; ++i) {
+    if (as[i].nseg == 1 || as[i].side) continue;
+    if (next && want > SIDE_BYTES)
+      as[i].nseg = count(Bt.ms[i], Bt.Ls[i], as[i].ntiles, (int64_t)((double)as[i].nseg * seg_bytes(i) / want * SIDE_BYTES));
+    if (!next) as[i].nseg = 1;
+    if (as[i].nseg == 1) continue;
+    as[i].side = (TC *)next;
+    next += as[i].nseg * seg_bytes(i);
+  }
 }
 template <typename TS, typename TC>
-inline fe_status segments_end(const LocalBatch &Bt, int vt, const std::vector<KArgs<TC>> &as, const std::vector<int> &waits,
-                              bool planes, hipStream_t s) {
+inline fe_status segments_end(int vt, const std::vector<KArgs<TC>> &as, bool planes, hipStream_t s) {
   for (size_t i = 0; i < as.size();) {
     JoinArgs<TS, TC> J{};
     J.planes = planes;
@@ -803,10 +807,6 @@ inline fe_status segments_end(const LocalBatch &Bt, int vt, const std::vector<KA
     const unsigned nodes = JOIN_THREADS >> J.tl;
     hipLaunchKernelGGL((k_planes_join<TS, TC>), dim3((mx + nodes - 1) / nodes, my, n * J.segs), dim3(JOIN_THREADS), 0, s, J);
     FE_HIP_TRY(hipGetLastError());
-  }
-  for (int i : waits) {
-    const fe_status st = plane_side_leave(Bt.ms[i], s);
-    if (st) return st;
   }
   return FE_OK;
 }
@@ -843,10 +843,10 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
   const size_t shm = lds_need<NP, NQ>(VT, sizeof(TC), offd);
   constexpr int NTB = BlockSize<NQ, VT, TC>::value;
   std::vector<KArgs<TC>> as;
-  std::vector<int> waits;
+  SideUse use;
   auto count = [](int per_cu) {      // blocks of this kernel on a CU
-    return [per_cu](Mesh *m, const LocalLaunch &L, int tiles) {
-      return block_segment_count(m, tiles, per_cu, side_seg_bytes(m, tiles * VT, sizeof(TC)), side_limit(L));
+    return [per_cu](Mesh *m, const LocalLaunch &, int tiles, int64_t side_bytes) {
+      return block_segment_count(m, tiles, per_cu, side_seg_bytes(m, (int64_t)tiles * VT, sizeof(TC)), side_bytes);
     };
   };
   if (Bt.n == 1 && !Bt.persistent) {
@@ -859,8 +859,7 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
       attr_set = shm;
     }
     if (!per_cu[offd]) FE_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu[offd], (const void *)kern, NTB, shm));
-    const fe_status st = segments_begin<TC>(Bt, VT, count(per_cu[offd]), as, waits, s);
-    if (st) return st;
+    segments_begin<TC>(Bt, VT, count(per_cu[offd]), as, use, s);
     KArgs<TC> &a = as[0];
     for (int ph = 0; ph < m->nphase; ++ph) {
       a.cols = m->cols + 2 * m->phase_off[ph];
@@ -871,7 +870,7 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
       hipLaunchKernelGGL(kern, dim3(nb), dim3(NTB), shm, s, a);
       FE_HIP_TRY(hipGetLastError());
     }
-    return segments_end<TS, TC>(Bt, VT, as, waits, false, s);
+    return segments_end<TS, TC>(VT, as, false, s);
   }
   auto kern = k_local_batch<NP, NQ, VT, CPLX, TS, TC, LPE, SH>;
   static size_t battr_set = 65536;
@@ -885,10 +884,7 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
     FE_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, NTB, shm));
     resident[offd] = (per_cu > 0 ? per_cu : 1) * device_cus(Bt.ms[0]->device);
   }
-  {
-    const fe_status st = segments_begin<TC>(Bt, VT, count(std::max(1, resident[offd] / device_cus(Bt.ms[0]->device))), as, waits, s);
-    if (st) return st;
-  }
+  segments_begin<TC>(Bt, VT, count(std::max(1, resident[offd] / device_cus(Bt.ms[0]->device))), as, use, s);
   const int cap = Bt.blocks_per_cu > 0 ? Bt.blocks_per_cu * device_cus(Bt.ms[0]->device) : resident[offd];
   int nphase = 0;
   for (int i = 0; i < Bt.n; ++i) nphase = nphase > Bt.ms[i]->nphase ? nphase : Bt.ms[i]->nphase;
@@ -917,7 +913,7 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
       FE_HIP_TRY(hipGetLastError());
     }
   }
-  return segments_end<TS, TC>(Bt, VT, as, waits, false, s);
+  return segments_end<TS, TC>(VT, as, false, s);
 }
 
 // The wide (16-byte) element form when every block of every system allows it.

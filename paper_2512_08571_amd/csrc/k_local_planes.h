@@ -1011,11 +1011,10 @@ inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
   const void *kern = single ? (const void *)k_planes<NP, NQ, CPLX, TS, TC, LPT, MASS> : (const void *)k_planes_batch<NP, NQ, CPLX, TS, TC, LPT, MASS>;
   FE_HIP_TRY(plane_lds(kern, shm));
   std::vector<KArgs<TC>> as;
-  std::vector<int> waits;
-  fe_status st = segments_begin<TC>(Bt, S::VT, [&](Mesh *m, const LocalLaunch &L, int) {
-    return plane_segment_count(m, NQ, L.nlanes, sizeof(TC) == 8, LPT, side_limit(L), nullptr);
-  }, as, waits, s);
-  if (st) return st;
+  SideUse use;
+  segments_begin<TC>(Bt, S::VT, [](Mesh *m, const LocalLaunch &L, int, int64_t side_bytes) {
+    return plane_segment_count(m, NQ, L.nlanes, sizeof(TC) == 8, LPT, side_bytes, nullptr);
+  }, as, use, s);
   int nphase = 0;
   for (int i = 0; i < Bt.n; ++i) {
     if constexpr (MASS) as[i].pgather = as[i].ptab + plane_tab(Bt.ms[i]->np, Bt.ms[i]->nq).m;
@@ -1046,7 +1045,7 @@ inline fe_status run_planes(const LocalBatch &Bt, hipStream_t s) {
       FE_HIP_TRY(hipGetLastError());
     }
   }
-  return segments_end<TS, TC>(Bt, S::VT, as, waits, true, s);
+  return segments_end<TS, TC>(S::VT, as, true, s);
 }
 
 template <int NP, int NQ> fe_status pick_planes_f64(const LocalBatch &B, hipStream_t s) {

@@ -917,7 +917,7 @@ fe_status apply_with_nonlocal(Mesh *m, const LocalLaunch &L, int prec, const dou
 // array (each device holds its own copy for the life of the process).  Host code never passes the array's name to a
 // kernel: its device address comes from hipGetSymbolAddress, once per device
 // with that device current, and only that address is used.
-static __device__ __align__(256) unsigned char scratch[FE_NOALLOC_SCRATCH_BYTES + PLANE_SIDE_BYTES];
+static __device__ __align__(256) unsigned char scratch[FE_NOALLOC_SCRATCH_BYTES + NOALLOC_SIDE_BYTES];
 
 namespace {
 constexpr int SCRATCH_MAXDEV = 64;
@@ -970,7 +970,7 @@ extern "C" fe_status fe_apply_H_noalloc(fe_mesh_t m, const void *X, int64_t ldx,
   L.X = X; L.Y = Y; L.ldx = ldx * C; L.ldy = ldy * C; L.nlanes = nlanes; L.prec = prec;
   L.vt = m->vt_pref[prec][0];
   L.side = (unsigned char *)ws + FE_NOALLOC_SCRATCH_BYTES;
-  L.side_bytes = PLANE_SIDE_BYTES;
+  L.side_bytes = NOALLOC_SIDE_BYTES;
   // projector reduction, local operator, projector update on the caller's
   // stream, as in fe_apply_H
   if ((st = dispatch_nl(m, X, L.ldx, nullptr, 0, nlanes, prec, nullptr, 0.0, 1, s, ws))) return st;

@@ -59,7 +59,7 @@ size_t elem_bytes(int prec) { return prec == FE_F64 ? 8 : (prec == FE_F32 ? 4 : 
 size_t filter_elem_bytes(int prec) { return prec == FE_F64 ? 8 : 4; }
 
 // request workspace slots: the filter blocks (see the mesh's workspace list)
-constexpr int REQ_SLOTS[] = {0, 1, 2, 3, 4, 8, 9, 11};
+constexpr int REQ_SLOTS[] = {0, 1, 2, 3, 4, 8, 9};
 
 // the workspace bytes a request needs on its mesh, per slot, and its
 // projector reduction block
@@ -80,9 +80,6 @@ void request_needs(const fe_request &q, int64_t need[fehx::Mesh::NWS], int64_t &
     need[3] = q.prec != FE_F64 ? n * eb : 0;
     need[4] = (int64_t)(q.degree + 1) * q.nvec * 8;
     if (m->mass_kind == FE_MASS_CONSISTENT) need[9] = n * 8;
-    need[11] = std::max(fehx::plane_side_need(m, (int)lanes, FE_F64), fehx::plane_side_need(m, (int)lanes, q.prec));
-  } else {
-    need[11] = fehx::plane_side_need(m, (int)lanes, q.prec);
   }
   nl_need = m->ns > 0 ? fehx::nl_workspace_bytes(m, (int)lanes) : 0;
 }

@@ -292,9 +292,6 @@ fe_status filter_setup(FilterPlan &P, Mesh *m, double *X, int64_t ldx_l, const d
   if (m->mass_kind == FE_MASS_CONSISTENT && (st = ensure_workspace(m, 9, n * (int64_t)sizeof(double))))
     return st;                                                                  // M X (FP64)
   if ((st = ensure_nl_workspace(m, P.lanes))) return st;
-  // the segment planes of the FP64 prologue and of the steps
-  P.side_need = std::max(plane_side_need(m, P.lanes, FE_F64), plane_side_need(m, P.lanes, prec));
-  if (m->graphs == 0 && (st = ensure_workspace(m, 11, P.side_need))) return st;
   P.Y = (double *)m->ws[share ? 2 : 0];
   P.RY = m->ws[1];
   P.RX = m->ws[2];
@@ -314,7 +311,7 @@ fe_status filter_prologue(FilterPlan &P, hipStream_t s) {
   LocalLaunch L0;
   L0.X = P.X; L0.Y = P.Y; L0.ldx = P.ldx; L0.ldy = P.lanes; L0.nlanes = P.lanes; L0.prec = FE_F64;
   L0.vt = m->vt_pref[FE_F64][0];
-  L0.side = P.side; L0.side_bytes = P.side_need;
+  L0.side = P.side; L0.side_bytes = P.side_bytes;
   fe_status st;
   if ((st = apply_with_nonlocal(m, L0, FE_F64, nullptr, 1.0, s))) return st;
   const double *MX = nullptr;
@@ -348,7 +345,7 @@ LocalLaunch filter_step_local(const FilterPlan &P) {
   L.X = P.RY; L.Y = P.T; L.ldx = P.lanes; L.ldy = P.lanes; L.nlanes = P.lanes; L.prec = P.prec;
   L.store32 = P.prec == FE_BF16;
   L.dinv_gather = P.m->dinv;
-  L.side = P.side; L.side_bytes = P.side_need;
+  L.side = P.side; L.side_bytes = P.side_bytes;
   L.vt = P.m->vt_pref[P.prec][1];
   return L;
 }
@@ -698,6 +695,14 @@ struct fe_filter_graph_s {
   fehx::FilterPlan P;
   hipGraph_t g = nullptr;
   hipGraphExec_t ex = nullptr;
+  ~fe_filter_graph_s() {
+    if (ex) hipGraphExecDestroy(ex);
+    if (g) hipGraphDestroy(g);
+    if (P.side) {
+      hipFree(P.side);
+      P.m->footprint -= P.side_bytes;
+    }
+  }
 };
 
 fe_status fe_filter_graph_create(fe_mesh_t m, void *X, int64_t ldx, const double *lam, int64_t nvec, int32_t degree,
@@ -716,6 +721,18 @@ fe_status fe_filter_graph_create(fe_mesh_t m, void *X, int64_t ldx, const double
   fe_filter_graph_s *G = new fe_filter_graph_s();
   fe_status st = filter_setup(G->P, m, (double *)X, ldx * C, lam, nvec, degree, lam_min, lam_T, lam_max, inner_prec);
   if (st) { delete G; return st; }
+  // the planes at the cuts of the FP64 prologue and of the steps: a block of the
+  // graph's own (without it columns stay whole)
+  const int64_t side = std::max(plane_side_need(m, G->P.lanes, FE_F64), plane_side_need(m, G->P.lanes, inner_prec));
+  if (side > 0) {
+    if (hipMalloc(&G->P.side, (size_t)side) == hipSuccess) {
+      G->P.side_bytes = side;
+      m->footprint += side;
+    } else {
+      G->P.side = nullptr;
+      (void)hipGetLastError();
+    }
+  }
   hipStream_t cs = nullptr;
   if (hipStreamCreate(&cs) != hipSuccess) { delete G; return set_error(FE_EDEVICE, "hipStreamCreate failed"); }
   if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) {
@@ -723,7 +740,6 @@ fe_status fe_filter_graph_create(fe_mesh_t m, void *X, int64_t ldx, const double
     delete G;
     return set_error(FE_EDEVICE, "hipStreamBeginCapture failed");
   }
-  if (m->ws_bytes[11] >= G->P.side_need) G->P.side = m->ws[11];   // else one segment
   FilterPlan P = G->P;   // enqueueing advances the step and swaps the blocks
   st = filter_enqueue(P, cs);
   hipGraph_t g = nullptr;
@@ -734,8 +750,6 @@ fe_status fe_filter_graph_create(fe_mesh_t m, void *X, int64_t ldx, const double
     st = set_error(FE_EDEVICE, "hipGraphInstantiate failed");
   G->g = g;
   if (st) {
-    if (G->ex) hipGraphExecDestroy(G->ex);
-    if (G->g) hipGraphDestroy(G->g);
     delete G;
     return st;
   }
@@ -747,21 +761,13 @@ fe_status fe_filter_graph_create(fe_mesh_t m, void *X, int64_t ldx, const double
 fe_status fe_filter_graph_launch(fe_filter_graph_t G, void *stream) {
   if (!G || !G->ex) return set_error(FE_EINVAL, "NULL graph");
   if (hipSetDevice(G->P.m->device) != hipSuccess) return set_error(FE_EDEVICE, "hipSetDevice failed");
-  fe_status st;
-  // (a caller that captures the launch orders its replays itself)
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  const bool shared = G->P.side && hipStreamIsCapturing((hipStream_t)stream, &cs) == hipSuccess &&
-                      cs == hipStreamCaptureStatusNone;
-  if (shared && (st = plane_side_enter(G->P.m, (hipStream_t)stream))) return st;
   FE_HIP_TRY(hipGraphLaunch(G->ex, (hipStream_t)stream));
-  return shared ? plane_side_leave(G->P.m, (hipStream_t)stream) : (fe_status)FE_OK;
+  return FE_OK;
 }
 
 fe_status fe_filter_graph_destroy(fe_filter_graph_t G) {
   if (!G) return FE_OK;
   --G->P.m->graphs;
-  if (G->ex) hipGraphExecDestroy(G->ex);
-  if (G->g) hipGraphDestroy(G->g);
   delete G;
   return FE_OK;
 }
