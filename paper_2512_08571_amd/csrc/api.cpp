@@ -447,6 +447,9 @@ fe_status fe_mesh_create(const fe_mesh_desc *desc, fe_mesh_t *out) {
   m->device = d.device;
   m->host_only = host_only;
   if (!host_only && hipSetDevice(m->device) != hipSuccess) { delete m; return set_error(FE_EDEVICE, "hipSetDevice failed"); }
+  int cus = 0;
+  if (!host_only && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device) == hipSuccess && cus > 0)
+    m->cus = cus;
   m->p = d.degree;
   m->np = d.degree + 1;
   m->nq = d.nq;
@@ -1190,9 +1193,6 @@ fe_status fe_batch_apply(int32_t n, const fe_mesh_t *meshes, const void *const *
     // fills the device on its own; when all of a class do, separate launches
     // (same per-item arithmetic) beat the persistent batch, whose blocks
     // stride over all systems' work lists.
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ms[0]->device) != hipSuccess || cus <= 0)
-      cus = 256;
     bool all_large = true;
     for (size_t j = 0; j < ms.size(); ++j) {
       const int vt = Ls[j].vt ? Ls[j].vt : (prec == FE_F64 ? 8 : 16);
@@ -1200,7 +1200,7 @@ fe_status fe_batch_apply(int32_t n, const fe_mesh_t *meshes, const void *const *
       int minc = INT32_MAX;
       for (int ph = 0; ph < ms[j]->nphase; ++ph)
         minc = std::min(minc, ms[j]->phase_off[ph + 1] - ms[j]->phase_off[ph]);
-      if ((int64_t)minc * tiles < 2LL * cus) all_large = false;
+      if ((int64_t)minc * tiles < 2LL * ms[j]->cus) all_large = false;
     }
     if (all_large && ms.size() > 1) {
       for (size_t j = 0; j < ms.size(); ++j) {

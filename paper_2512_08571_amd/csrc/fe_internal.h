@@ -133,6 +133,8 @@ constexpr int plane_waves(int nq, bool f64, int lpt) {
 constexpr int64_t NOALLOC_SIDE_BYTES = 64LL << 20;   // beside the static scratch
 constexpr int64_t SIDE_BYTES = 128LL << 20;          // of the device's blocks
 int64_t side_seg_bytes(const Mesh *m, int64_t side_lanes, int elem_bytes);
+int segment_count(const int *phase_off, int nphase, int64_t cells, int64_t tiles, int units, int per_unit, int64_t cap,
+                  double *cost);
 int plane_segment_count(const Mesh *m, int nq, int nlanes, bool f64, int lpt, int64_t side_bytes, double *cost);
 inline int64_t side_limit(const LocalLaunch &L) { return L.side ? L.side_bytes : SIDE_BYTES; }
 int block_segment_count(const Mesh *m, int tiles, int per_cu, int64_t seg_bytes, int64_t side_bytes);
@@ -230,6 +232,7 @@ struct Mesh {
   int64_t E = 0, m = 0;
   bool cplx = false;
   int device = 0;
+  int cus = 256;            // compute units of the device
   bool host_only = false;   // device < 0: host tables and maps only
   double J[3][3]{}, Jinv[3][3]{}, detJ = 0;
   double gdiag[3]{}, kap[3]{}, k2half = 0;

@@ -8,8 +8,6 @@
 
 namespace fehx {
 
-constexpr int DEVICE_CUS = 256;
-
 fe_status launch_local_f64(const LocalBatch &B, hipStream_t s);
 fe_status launch_local_f32(const LocalBatch &B, hipStream_t s);
 fe_status launch_local_bf16(const LocalBatch &B, hipStream_t s);
@@ -31,17 +29,19 @@ fe_status launch_local_mass(const LocalBatch &B, hipStream_t s);
 // (SEG_MAX: past it every unit of the device has a segment of the four or more
 // columns to itself; k_planes_join takes segments x cells below 2^32)
 constexpr int64_t SEG_MAX = 2048;
-static int segment_count(const Mesh *m, int tiles, int units, int per_unit, int64_t cap, double *cost) {
+int segment_count(const int *phase_off, int nphase, int64_t cells, int64_t tiles, int units, int per_unit, int64_t cap,
+                  double *cost) {
+  per_unit = std::max(per_unit, 1);              // (an occupancy query may answer none)
   auto round = [](int64_t k) { return k ? 1.0 + 2.0 * k : 0.0; };
   int best = 1;
   double least = 0;
-  for (int64_t n = 1; n <= std::max<int64_t>(1, std::min<int64_t>({m->N[2], cap, SEG_MAX, (1LL << 31) / m->N[2]})); ++n) {
+  for (int64_t n = 1; n <= std::max<int64_t>(1, std::min<int64_t>({cells, cap, SEG_MAX, (1LL << 31) / cells})); ++n) {
     double c = 0;
-    for (int ph = 0; ph < m->nphase; ++ph) {
-      const int64_t k = ((int64_t)(m->phase_off[ph + 1] - m->phase_off[ph]) * tiles * n + units - 1) / units;
+    for (int ph = 0; ph < nphase; ++ph) {
+      const int64_t k = ((int64_t)(phase_off[ph + 1] - phase_off[ph]) * tiles * n + units - 1) / units;
       c += (double)(k / per_unit) * round(per_unit) + round(k % per_unit);
     }
-    c *= (m->N[2] + n - 1) / n + 0.5;
+    c *= (cells + n - 1) / n + 0.5;
     if (n == 1 || c < least) { best = (int)n; least = c; }
   }
   if (cost) *cost = least;
@@ -57,7 +57,7 @@ int64_t side_seg_bytes(const Mesh *m, int64_t side_lanes, int elem_bytes) {
 
 int plane_segment_count(const Mesh *m, int nq, int nlanes, bool f64, int lpt, int64_t side_bytes, double *cost) {
   const int vt = plane_vt(nq, lpt), tiles = (nlanes + vt - 1) / vt;
-  return segment_count(m, tiles, 4 * DEVICE_CUS, plane_waves(nq, f64, lpt),
+  return segment_count(m->phase_off.data(), m->nphase, m->N[2], tiles, 4 * m->cus, plane_waves(nq, f64, lpt),
                        side_bytes / side_seg_bytes(m, (int64_t)tiles * vt, f64 ? 8 : 4), cost);
 }
 
@@ -65,7 +65,7 @@ int plane_segment_count(const Mesh *m, int nq, int nlanes, bool f64, int lpt, in
 // degree 4 x 64 FP64 vectors, whole columns 240 us, segments 117; 9 points
 // 12^3 cells degree 6 x 128 2157 and 1770)
 int block_segment_count(const Mesh *m, int tiles, int per_cu, int64_t seg_bytes, int64_t side_bytes) {
-  return segment_count(m, tiles, DEVICE_CUS, per_cu, side_bytes / seg_bytes, nullptr);
+  return segment_count(m->phase_off.data(), m->nphase, m->N[2], tiles, m->cus, per_cu, side_bytes / seg_bytes, nullptr);
 }
 
 bool plane_mesh(const Mesh *m) { return !m->offd && m->nq == m->np; }

@@ -818,12 +818,6 @@ template <int NP, int NQ> constexpr size_t lds_need(int vt, int bytes, bool offd
           (offd ? (size_t)3 * NQ * NQ * NQ * vt : 0)) * bytes;
 }
 
-inline int device_cus(int dev) {
-  int n = 0;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-  return n;
-}
-
 // Single system: one launch per colour phase, one block per (column, tile).
 // Batch (several systems of one class, or persistent=true): one persistent
 // launch per colour phase over the concatenated work lists of up to
@@ -882,10 +876,10 @@ inline fe_status run_local_lpe(const LocalBatch &Bt, hipStream_t s) {
   if (!resident[offd]) {
     int per_cu = 0;
     FE_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, NTB, shm));
-    resident[offd] = (per_cu > 0 ? per_cu : 1) * device_cus(Bt.ms[0]->device);
+    resident[offd] = (per_cu > 0 ? per_cu : 1) * Bt.ms[0]->cus;
   }
-  segments_begin<TC>(Bt, VT, count(std::max(1, resident[offd] / device_cus(Bt.ms[0]->device))), as, use, s);
-  const int cap = Bt.blocks_per_cu > 0 ? Bt.blocks_per_cu * device_cus(Bt.ms[0]->device) : resident[offd];
+  segments_begin<TC>(Bt, VT, count(std::max(1, resident[offd] / Bt.ms[0]->cus)), as, use, s);
+  const int cap = Bt.blocks_per_cu > 0 ? Bt.blocks_per_cu * Bt.ms[0]->cus : resident[offd];
   int nphase = 0;
   for (int i = 0; i < Bt.n; ++i) nphase = nphase > Bt.ms[i]->nphase ? nphase : Bt.ms[i]->nphase;
   for (int ph = 0; ph < nphase; ++ph) {
