@@ -161,6 +161,8 @@ struct LocalBatch;
 // lane or, where the block's rows start on pairs of lanes, of one or two.
 enum LocalKind { LOCAL_STAGED, LOCAL_GENERAL, LOCAL_PLANES, LOCAL_PLANES_PAIRS, LOCAL_MASS, LOCAL_MASS_PAIRS };
 LocalKind local_kind(const Mesh *m, const LocalLaunch &L);
+// the vector tile an application depends on (the plane kernels take none: 0)
+inline int local_tile(const Mesh *m, const LocalLaunch &L) { return local_kind(m, L) <= LOCAL_GENERAL ? L.vt : 0; }
 constexpr int64_t PLANE_SPAN = 0x7fffffff;   // bytes of a z plane that the plane kernels' buffer offsets reach
 bool plane_pairs_pay(const LocalBatch &B, int nq);
 int64_t plane_side_need(const Mesh *m, int nlanes, int prec);

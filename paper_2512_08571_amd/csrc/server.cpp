@@ -377,7 +377,7 @@ struct fe_server_s {
         const fehx::Mesh *b = items[j].q->r.mesh;
         const LocalLaunch &Lb = items[j].L;
         if (done[j] || b->np != a->np || b->nq != a->nq || b->cplx != a->cplx || Lb.prec != La.prec ||
-            Lb.vt != La.vt || Lb.store32 != La.store32)
+            Lb.store32 != La.store32 || fehx::local_tile(b, Lb) != fehx::local_tile(a, La))
           continue;
         ms.push_back(items[j].q->r.mesh);
         Ls.push_back(Lb);

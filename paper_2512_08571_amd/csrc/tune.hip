@@ -61,7 +61,7 @@ void fill(void *x, int64_t n, uint64_t seed, hipStream_t s) {
   hipLaunchKernelGGL(k_fill<TS>, dim3((unsigned)b), dim3(256), 0, s, (TS *)x, n, seed);
 }
 
-// FP64 offers ten lanes on the line-gather path (n_q = n_p)
+// FP64 offers ten lanes where n_q = n_p
 constexpr int MAX_CAND = FE_TILE_CANDIDATES;
 int candidates(int prec, bool nq_eq_np, int *out) {
   if (prec == FE_F64) {
@@ -156,7 +156,7 @@ fe_status fe_autotune(fe_mesh_t m, int32_t prec, int32_t kind, int64_t nvec, int
   } eg{e0, e1};
   int cand[MAX_CAND];
   const int nc = candidates(prec, m->nq == m->np, cand);
-  float best = INFINITY;
+  float best = INFINITY, planes = INFINITY;
   int bestv = 0;
   for (int i = 0; i < nc; ++i) {
     LocalLaunch L;
@@ -164,9 +164,14 @@ fe_status fe_autotune(fe_mesh_t m, int32_t prec, int32_t kind, int64_t nvec, int
     L.store32 = store32;
     if (kind == 1) L.dinv_gather = m->dinv;   // a filter step: D^-1 applied at the gather
     float ms = INFINITY;
-    // warm-up; a tile that fe_set_tile refuses on this mesh is skipped
-    fe_status st = tile_fits(m, prec, cand[i]) ? launch_local(m, L, s) : (fe_status)FE_EUNSUPPORTED;
-    if (st == FE_OK) {
+    // warm-up; a tile that fe_set_tile refuses on this mesh is skipped, and the
+    // plane kernels, which take no tile, run once for all of them
+    const bool fits = tile_fits(m, prec, cand[i]);
+    const bool timed = fits && std::isfinite(planes);
+    fe_status st = !fits ? (fe_status)FE_EUNSUPPORTED : timed ? (fe_status)FE_OK : launch_local(m, L, s);
+    if (timed) {
+      ms = planes;
+    } else if (st == FE_OK) {
       FE_HIP_TRY(hipEventRecord(e0, s));
       for (int r = 0; r < reps && st == FE_OK; ++r) st = launch_local(m, L, s);
       FE_HIP_TRY(hipEventRecord(e1, s));
@@ -174,6 +179,7 @@ fe_status fe_autotune(fe_mesh_t m, int32_t prec, int32_t kind, int64_t nvec, int
       if (st == FE_OK) {
         FE_HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
         ms /= (float)reps;
+        if (local_kind(m, L) > LOCAL_GENERAL) planes = ms;
       }
     } else if (st != FE_EUNSUPPORTED) {
       return st;
