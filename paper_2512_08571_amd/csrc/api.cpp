@@ -282,10 +282,12 @@ void plane_coefficients(const Mesh *m, const double *vloc, const double *vgga, d
 std::vector<double> plane_tables(const Mesh *m) {
   const int np = m->np, nq = m->nq;
   const PlaneTab L = plane_tab(np, nq);
-  std::vector<double> tab(L.total), A;
-  const std::vector<double> &N = m->t1.N, &Dt = m->t1.Dt, &w = m->t1.wq;
-  const double dj = std::cbrt(m->detJ);
-  auto put = [&](int off, const std::vector<double> &A, int nout, int nin, int sym) {
+  typedef long double real;
+  std::vector<double> tab(L.total);
+  std::vector<real> A;
+  const std::vector<real> &N = m->t1.Nx, &Dt = m->t1.Dtx, &w = m->t1.wqx;
+  const real dj = std::cbrt((real)m->detJ);
+  auto put = [&](int off, const std::vector<real> &A, int nout, int nin, int sym) {
     const std::vector<double> v = eo_pack(A, nout, nin, sym);
     std::copy(v.begin(), v.end(), tab.begin() + off);
     int e = off + (int)v.size();
@@ -293,21 +295,21 @@ std::vector<double> plane_tables(const Mesh *m) {
       for (int c = 0; c < nin; ++c)
         if (c != 0 && c != (nin + 1) / 2) tab[e++] = v[q * nin + c];
   };
-  std::vector<double> Nh((size_t)nq * np);
+  std::vector<real> Nh((size_t)nq * np);
   for (int q = 0; q < nq; ++q)
     for (int i = 0; i < np; ++i) Nh[q * np + i] = N[q * np + i] * std::sqrt(w[q] * dj);
   put(L.n, Nh, nq, np, +1);
-  A.assign((size_t)nq * np, 0.0);
+  A.assign((size_t)nq * np, 0.0L);
   for (int q = 0; q < nq; ++q)
-    for (int i = 0; i < np; ++i) A[q * np + i] = Nh[q * np + i] / (m->t1.gllw[i] * (i == 0 || i == np - 1 ? 2.0 : 1.0) * dj);
+    for (int i = 0; i < np; ++i) A[q * np + i] = Nh[q * np + i] / (m->t1.gllwx[i] * (i == 0 || i == np - 1 ? 2.0L : 1.0L) * dj);
   put(L.nd, A, nq, np, +1);
-  A.assign((size_t)np * nq, 0.0);
+  A.assign((size_t)np * nq, 0.0L);
   for (int i = 0; i < np; ++i)
     for (int q = 0; q < nq; ++q) A[i * nq + q] = Nh[q * np + i];
   put(L.nt, A, np, nq, +1);
   for (int d = 0; d < 3; ++d) {
-    const double g = std::sqrt(m->gdiag[d]);
-    std::vector<double> D((size_t)nq * nq), H((size_t)nq * nq), K((size_t)nq * nq, 0.0);
+    const real g = std::sqrt((real)m->gdiag[d]);
+    std::vector<real> D((size_t)nq * nq), H((size_t)nq * nq), K((size_t)nq * nq, 0.0L);
     for (int q = 0; q < nq; ++q)
       for (int r = 0; r < nq; ++r) {
         D[q * nq + r] = g * Dt[q * nq + r] * std::sqrt(w[q] / w[r]);
@@ -320,7 +322,7 @@ std::vector<double> plane_tables(const Mesh *m) {
     put(L.dh + d * L.dsz, H, nq, nq, -1);
     put(L.k + d * L.dsz, K, nq, nq, +1);
   }
-  A.assign((size_t)np * np, 0.0);
+  A.assign((size_t)np * np, 0.0L);
   for (int i = 0; i < np; ++i)
     for (int j = 0; j < np; ++j)
       for (int q = 0; q < nq; ++q) A[i * np + j] += Nh[q * np + i] * Nh[q * np + j];
@@ -481,17 +483,17 @@ fe_status fe_mesh_create(const fe_mesh_desc *desc, fe_mesh_t *out) {
     m->t1 = make_tables(m->p, m->nq);
     const int np = m->np, nq = m->nq;
     // the four 1D matrices of Alg. 2 in even-odd packed form
-    std::vector<double> NT((size_t)np * nq), DT((size_t)nq * nq);
+    std::vector<long double> NT((size_t)np * nq), DT((size_t)nq * nq);
     for (int q = 0; q < nq; ++q)
-      for (int i = 0; i < np; ++i) NT[i * nq + q] = m->t1.N[q * np + i];
+      for (int i = 0; i < np; ++i) NT[i * nq + q] = m->t1.Nx[q * np + i];
     for (int q = 0; q < nq; ++q)
-      for (int r = 0; r < nq; ++r) DT[r * nq + q] = m->t1.Dt[q * nq + r];
+      for (int r = 0; r < nq; ++r) DT[r * nq + q] = m->t1.Dtx[q * nq + r];
     TabLayout L = tab_layout(np, nq);
     std::vector<double> tab(L.total);
     auto put = [&](int off, const std::vector<double> &v) { std::copy(v.begin(), v.end(), tab.begin() + off); };
-    put(L.n_off, eo_pack(m->t1.N, nq, np, +1));
+    put(L.n_off, eo_pack(m->t1.Nx, nq, np, +1));
     put(L.nt_off, eo_pack(NT, np, nq, +1));
-    put(L.d_off, eo_pack(m->t1.Dt, nq, nq, -1));
+    put(L.d_off, eo_pack(m->t1.Dtx, nq, nq, -1));
     put(L.dt_off, eo_pack(DT, nq, nq, -1));
     // w_Q det J = (w_a w_b)(w_i det J) for a line along direction D through
     // (a, b): the pair product per line, the per-point factor with g and kappa

@@ -50,12 +50,13 @@ struct Tables1D {
   std::vector<double> N;           // N[q*np + i]  = l_i(xq_q)
   std::vector<double> Dt;          // Dt[q*nq + r] = d/dxi of the Gauss-point
                                    // Lagrange polynomial r at xq_q (collocation)
+  std::vector<long double> gllwx, wqx, Nx, Dtx;   // the same before rounding
 };
 Tables1D make_tables(int p, int nq);
 
 // Even-odd packing of a centro-(anti)symmetric matrix A[nout][nin]: rows
 // q < ceil(nout/2): E[q][0..ceil(nin/2)) then O[q][0..floor(nin/2)).
-std::vector<double> eo_pack(const std::vector<double> &A, int nout, int nin, int sym);
+std::vector<double> eo_pack(const std::vector<long double> &A, int nout, int nin, int sym);
 
 // offsets (in elements) inside one table buffer: the four packed matrices,
 // then per direction D the point factors g_DD w_i det J and kappa_D w_i det J
