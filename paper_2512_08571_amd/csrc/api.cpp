@@ -1,6 +1,7 @@
 // C-ABI entry points of libfehx: mesh set-up, coefficient fields, nonlocal
 // projectors and the operator application (include/fe_hx.h documents each).
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -330,6 +331,143 @@ std::vector<double> plane_tables(const Mesh *m) {
   return tab;
 }
 
+// The FP32 tables: the FP64 ones with N' times s, which leaves the operator as it
+// is with D_d and c_d divided by s^3 and V by s^6.
+double plane_factor(const PlaneTab &L, int off, double s) {
+  return off < L.d ? s : off < L.k ? 1.0 / (s * s * s) : off < L.m ? 1.0 / std::pow(s, 6) : 1.0;
+}
+std::vector<float> plane_tables32(const Mesh *m, const std::vector<double> &tab) {
+  const PlaneTab L = plane_tab(m->np, m->nq);
+  std::vector<float> out(tab.size());
+  for (size_t i = 0; i < tab.size(); ++i) out[i] = (float)(tab[i] * plane_factor(L, (int)i, m->pscale32));
+  return out;
+}
+
+// The factor s with which the FP32 tables round least.  Rounding the tables
+// is much of the FP32 operator's error, as each entry's error is met at every
+// cell (7 points: 1.0e-7 of 2.0e-7, and 0.4e-7 of 1.7e-7 with the best factor,
+// where the unfolded tables' operator has 1.8e-7).  The measure is the kinetic
+// operator's, A x M x M + M x A x M + M x M x A with M = N'^T N'' and
+// A = N'^T D^T D N'' (or K for D^T D, which real cells without a GGA field
+// take), N'' the gather's table in applications and filter steps: its first-order
+// error relative to it, in the Frobenius norm.
+double plane_scale32(const Mesh *m, const std::vector<double> &tab) {
+  const int nq = m->nq, nn = nq * nq;
+  if (m->np != nq) return 1.0;
+  const PlaneTab L = plane_tab(nq, nq);
+  typedef std::array<double, 81> Mat;            // [nq][nq], nq <= 9
+  // a table, with s != 0 rounded as the FP32 one and scaled back
+  auto table = [&](int off, int sym, double s) {
+    Mat A;
+    const double f = s != 0.0 ? plane_factor(L, off, s) : 1.0, back = 1.0 / f;
+    const int CI = (nq + 1) / 2, HI = nq / 2;
+    auto at = [&](int e) { return s != 0.0 ? (double)(float)(tab[off + e] * f) * back : tab[off + e]; };
+    for (int q = 0; q < CI; ++q)
+      for (int i = 0; i < CI; ++i) {
+        const bool mid = (nq & 1) && q == HI;
+        const double e = mid && sym < 0 ? 0.0 : at(q * nq + i);
+        const double o = i == HI || (mid && sym > 0) ? 0.0 : at(q * nq + CI + i);
+        A[q * nq + i] = e + o;
+        A[(nq - 1 - q) * nq + nq - 1 - i] = sym * (e + o);
+        if (i < HI) {
+          A[q * nq + nq - 1 - i] = e - o;
+          A[(nq - 1 - q) * nq + i] = sym * (e - o);
+        }
+      }
+    return A;
+  };
+  auto mul = [&](const Mat &A, bool tr, const Mat &B) {            // A B or A^T B
+    Mat R;
+    std::fill_n(R.begin(), nn, 0.0);
+    for (int i = 0; i < nq; ++i)
+      for (int k = 0; k < nq; ++k) {
+        const double x = tr ? A[k * nq + i] : A[i * nq + k];
+        for (int j = 0; j < nq; ++j) R[i * nq + j] += x * B[k * nq + j];
+      }
+    return R;
+  };
+  // per gather table: M, then per axis A by D and, where the mesh may run it, A by K
+  const int nvar = m->cplx ? 1 : 2, per = 1 + 3 * nvar;
+  auto factors = [&](double s, Mat *out) {
+    const Mat N = table(L.n, +1, s);
+    for (int off : {L.n, L.nd}) {
+      const Mat G = table(off, +1, s);
+      *out++ = mul(N, true, G);
+      for (int d = 0; d < 3; ++d, out += nvar) {
+        if (d > 0 && m->gdiag[d] == m->gdiag[d - 1]) {   // the axis before's
+          std::copy(out - nvar, out, out);
+          continue;
+        }
+        const Mat D = table(L.d + d * L.dsz, -1, s);
+        out[0] = mul(mul(D, false, N), true, mul(D, false, G));
+        if (nvar == 2) out[1] = mul(N, true, mul(table(L.k + d * L.dsz, +1, s), false, G));
+      }
+    }
+  };
+  Mat exact[14], err[14];
+  factors(0.0, exact);
+  double best = 1.0, least = INFINITY;
+  constexpr int TRIES = 24;
+  for (int k = 0; k < TRIES; ++k) {
+    const double s = std::exp2((double)k / TRIES);
+    factors(s, err);
+    for (int f = 0; f < 2 * per; ++f)
+      for (int i = 0; i < nn; ++i) err[f][i] -= exact[f][i];
+    double sum = 0.0;
+    for (int g = 0; g < 2; ++g)
+      for (int v = 0; v < nvar; ++v) {
+        // Gram matrices of {A, dA, M, dM} along each axis
+        double gram[3][4][4];
+        for (int d = 0; d < 3; ++d) {
+          const int a = g * per + 1 + d * nvar + v, o = g * per;
+          const Mat *f[4] = {&exact[a], &err[a], &exact[o], &err[o]};
+          for (int i = 0; i < 4; ++i)
+            for (int j = 0; j <= i; ++j) {
+              double x = 0.0;
+              for (int e = 0; e < nn; ++e) x += (*f[i])[e] * (*f[j])[e];
+              gram[d][i][j] = gram[d][j][i] = x;
+            }
+        }
+        // term t has A along axis t; its c-th error term the error along axis c
+        auto which = [](int t, int axis, int c) { return (axis == t ? 0 : 2) + (axis == c ? 1 : 0); };
+        double num = 0.0, den = 0.0;
+        for (int t = 0; t < 3; ++t)
+          for (int u = 0; u < 3; ++u) {
+            double x = 1.0;
+            for (int d = 0; d < 3; ++d) x *= gram[d][which(t, d, -1)][which(u, d, -1)];
+            den += x;
+            for (int c = 0; c < 3; ++c)
+              for (int b = 0; b < 3; ++b) {
+                x = 1.0;
+                for (int d = 0; d < 3; ++d) x *= gram[d][which(t, d, c)][which(u, d, b)];
+                num += x;
+              }
+          }
+        sum += num / den;
+      }
+    if (sum < least) {
+      least = sum;
+      best = s;
+    }
+  }
+  return best;
+}
+
+// FP32 plane coefficients from the FP64 ones (layout at Mesh::pcoef64)
+std::vector<float> plane_coefficients32(const Mesh *m, const std::vector<double> &pc) {
+  const size_t nq3 = (size_t)m->nq * m->nq * m->nq;
+  const double c = 1.0 / (m->pscale32 * m->pscale32 * m->pscale32), v = c * c;
+  std::vector<float> out(pc.size());
+  for (size_t o = 0; o < pc.size(); o += 4 * nq3) {
+    for (size_t e = 0; e < 2 * nq3; e += 2) {
+      out[o + e] = (float)(pc[o + e] * v);
+      out[o + e + 1] = (float)(pc[o + e + 1] * c);
+    }
+    for (size_t e = 2 * nq3; e < 4 * nq3; ++e) out[o + e] = (float)(pc[o + e] * c);
+  }
+  return out;
+}
+
 // Every device array that depends on the cell geometry: the mass-operator
 // coefficients (one shared block, or one per cell on the general-metric
 // path), the lumped mass D and its inverse, and the operator coefficients of
@@ -389,7 +527,8 @@ fe_status build_geometry(Mesh *m) {
   if (!m->distorted) {
     const std::vector<double> ptab = plane_tables(m);
     if ((st = upload(m, &m->ptab64, ptab))) return st;
-    if ((st = upload(m, &m->ptab32, to_f32(ptab)))) return st;
+    if (!m->host_only) m->pscale32 = plane_scale32(m, ptab);
+    if ((st = upload(m, &m->ptab32, plane_tables32(m, ptab)))) return st;
     for (int d = 0; d < 3; ++d) m->pkap[d] = m->kap[d] / std::sqrt(m->gdiag[d]);
   }
   if (plane_mesh(m)) {
@@ -397,7 +536,7 @@ fe_status build_geometry(Mesh *m) {
     plane_coefficients(m, nullptr, nullptr, pc.data());
     for (int64_t c = 1; c < m->E; ++c) std::copy_n(pc.begin(), 4 * nq3, pc.begin() + c * 4 * nq3);
     if ((st = upload(m, &m->pcoef64, pc))) return st;
-    if ((st = upload(m, &m->pcoef32, to_f32(pc)))) return st;
+    if ((st = upload(m, &m->pcoef32, plane_coefficients32(m, pc)))) return st;
   }
   m->has_gga = false;
   return FE_OK;
@@ -678,7 +817,7 @@ fe_status fe_set_potential(fe_mesh_t m, const double *vloc, const double *vgga) 
     for (int64_t c = 0; c < m->E; ++c)
       plane_coefficients(m, vloc + c * nq3, vgga ? vgga + 3 * c * nq3 : nullptr, &pc[(size_t)c * 4 * nq3]);
     FE_HIP_TRY(hipMemcpy(m->pcoef64, pc.data(), pc.size() * sizeof(double), hipMemcpyHostToDevice));
-    c32 = to_f32(pc);
+    c32 = plane_coefficients32(m, pc);
     FE_HIP_TRY(hipMemcpy(m->pcoef32, c32.data(), c32.size() * sizeof(float), hipMemcpyHostToDevice));
   }
   m->has_gga = vgga != nullptr;

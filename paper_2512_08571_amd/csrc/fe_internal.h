@@ -267,6 +267,7 @@ struct Mesh {
   double *ptab64 = nullptr, *pcoef64 = nullptr;
   float *ptab32 = nullptr, *pcoef32 = nullptr;
   double pkap[3]{};
+  double pscale32 = 1.0;                // the FP32 tables' factor on N' (plane_scale32)
   bool has_gga = false;
   double *dmass = nullptr, *dinv = nullptr;   // lumped mass and its inverse [m]
   std::vector<double> h_dmass;

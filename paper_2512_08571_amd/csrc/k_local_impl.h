@@ -751,7 +751,8 @@ template <typename TC> KArgs<TC> make_args(Mesh *m, const LocalLaunch &L, int vt
   const PlaneTab pt = plane_tab(m->np, m->nq);
   a.pgather = a.ptab + (L.dinv_gather ? pt.nd : pt.n);
   a.pcoef = f64 ? (const TC *)m->pcoef64 : (const TC *)m->pcoef32;
-  for (int d = 0; d < 3; ++d) a.pkap[d] = (TC)m->pkap[d];
+  const double ps = f64 ? 1.0 : m->pscale32;
+  for (int d = 0; d < 3; ++d) a.pkap[d] = (TC)(m->pkap[d] / (ps * ps * ps));
   a.nseg = 1;
   a.dinv = L.dinv_gather;
   a.ntiles = (L.nlanes + vt - 1) / vt;
