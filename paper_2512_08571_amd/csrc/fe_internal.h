@@ -113,7 +113,7 @@ struct LocalLaunch {
   bool mass = false;          // the consistent mass operator M instead of H
   int vt = 0, nt = 0;         // vector tile / threads (0: tuned default)
   void *side = nullptr;       // a side block of the caller's own (null: one of the device's, SideUse)
-  int64_t side_bytes = 0;
+  int64_t side_bytes = 0;     // its two halves, one after the other
   bool store32 = false;       // FE_BF16 arithmetic on FP32 blocks (the filter's recurrence state)
 };
 
@@ -132,7 +132,7 @@ constexpr int plane_waves(int nq, bool f64, int lpt) {
 // Segments a column of cells is cut into (segment_count), and the block for
 // the planes at their cuts
 constexpr int64_t NOALLOC_SIDE_BYTES = 64LL << 20;   // beside the static scratch
-constexpr int64_t SIDE_BYTES = 128LL << 20;          // of the device's blocks
+constexpr int64_t SIDE_BYTES = 128LL << 20;          // of the device's blocks, in two halves
 int64_t side_seg_bytes(const Mesh *m, int64_t side_lanes, int elem_bytes);
 int segment_count(const int *phase_off, int nphase, int64_t cells, int64_t tiles, int units, int per_unit, int64_t cap,
                   double *cost);
@@ -149,7 +149,9 @@ class SideUse {
   SideUse() = default;
   SideUse(const SideUse &) = delete;
   ~SideUse();
-  void *take(int device, hipStream_t s);   // SIDE_BYTES, or null: none is free, or s is capturing
+  // the first half of a block and its distance from the second in bytes, or
+  // null: none is free, or s is capturing
+  void *take(int device, hipStream_t s, int64_t *half);
  private:
   SideBlock *block_ = nullptr;
   int device_ = 0;

@@ -48,8 +48,8 @@ int segment_count(const int *phase_off, int nphase, int64_t cells, int64_t tiles
   return best;
 }
 
-// Bytes of the side block per segment: [cut][half][column][x][y][lane] in the
-// compute type, cut s the first plane of segment s, half 0 what that segment
+// Bytes of the side block per segment: two halves of [cut][column][x][y][lane] in
+// the compute type, cut s the first plane of segment s, half 0 what that segment
 // adds to it and half 1 what the one below does (cut 0: the periodic wrap).
 int64_t side_seg_bytes(const Mesh *m, int64_t side_lanes, int elem_bytes) {
   return 2LL * m->N[0] * m->N[1] * m->np * m->np * side_lanes * elem_bytes;
@@ -131,9 +131,11 @@ int64_t plane_side_need(const Mesh *m, int nlanes, int prec) {
 // beside anything) columns stay whole, with the same result.
 // (The event orders work on the device only: without the fence to the host it
 // costs 0.7 us of an application, with it 2.5.)
+// The halves are allocations of their own: past 64 MiB one takes 140 us and its
+// release 350, below 12 each.
 constexpr int SIDE_BLOCKS = 4, SIDE_DEVICES = 64;
 struct SideBlock {
-  void *p = nullptr;
+  void *p = nullptr, *q = nullptr;
   hipEvent_t done = nullptr;
   hipStream_t s = nullptr;   // of the last use
   bool used = false, held = false;
@@ -165,9 +167,12 @@ void side_pool_enter(int device) {
   if (i >= SIDE_BLOCKS || P.blocks[i].p) return;
   SideBlock b;
   if (hipEventCreateWithFlags(&b.done, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess) {
-    if (hipMalloc(&b.p, (size_t)SIDE_BYTES) == hipSuccess) {
-      P.blocks[i] = b;
-      return;
+    if (hipMalloc(&b.p, (size_t)SIDE_BYTES / 2) == hipSuccess) {
+      if (hipMalloc(&b.q, (size_t)SIDE_BYTES / 2) == hipSuccess) {
+        P.blocks[i] = b;
+        return;
+      }
+      hipFree(b.p);
     }
     hipEventDestroy(b.done);
   }
@@ -183,14 +188,14 @@ void side_pool_leave(int device) {
   for (SideBlock &b : P.blocks) {
     if (b.p) {
       hipFree(b.p);
+      hipFree(b.q);
       hipEventDestroy(b.done);
     }
     b = SideBlock();
   }
 }
 
-void *SideUse::take(int device, hipStream_t s) {
-  if (block_) return block_->p;
+void *SideUse::take(int device, hipStream_t s, int64_t *half) {
   if (device < 0 || device >= SIDE_DEVICES) return nullptr;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
@@ -216,6 +221,7 @@ void *SideUse::take(int device, hipStream_t s) {
   block_ = found;
   device_ = device;
   s_ = s;
+  *half = (char *)found->q - (char *)found->p;
   return found->p;
 }
 

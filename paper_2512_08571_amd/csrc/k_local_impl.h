@@ -153,6 +153,7 @@ template <typename TC> struct KArgs {
   TC pkap[3];
   int nseg;            // segments a column is cut into, and the planes at their cuts (side_seg_bytes)
   TC *side;
+  int64_t side_half;   // elements from its first half to the second
 };
 
 // ---- even-odd application of a packed centro-(anti)symmetric 1D matrix ----------
@@ -441,8 +442,8 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
   // plane of the one below) of cut sg (layout at side_seg_bytes)
   auto side_of = [&](int r, int sg, int half) -> TC * {
     const int n = (tid + r * NT) / NV, ij = (n % NP) * NP + (n / NP) % NP;
-    const int64_t plane = (int64_t)(2 * sg + half) * (a.N0 * a.N1) + cx + a.N0 * cy;
-    return a.side + (plane * NP2 + ij) * (a.ntiles * VT) + elane(r);
+    const int64_t plane = (int64_t)sg * (a.N0 * a.N1) + cx + a.N0 * cy;
+    return a.side + half * a.side_half + (plane * NP2 + ij) * (a.ntiles * VT) + elane(r);
   };
   // plane k of cell cz holds DoFs (always on a periodic a_2)
   auto zin = [&](int k, int cz) { const int gz = cz * p + k - zoff; return !zoff || (gz >= 0 && gz < a.M2); };
@@ -623,7 +624,7 @@ template <typename TS, typename TC> struct JoinArgs {
   struct {
     TS *Y;
     const TC *side;
-    int64_t ldy;
+    int64_t side_half, ldy;
     int M0, M1, N0, N1, N2, p, dmask, nseg, side_lanes, nlanes;
   } sys[JOIN_MAXB];
   int tl;
@@ -656,9 +657,9 @@ template <typename TS, typename TC> __global__ void __launch_bounds__(JOIN_THREA
   const int nx = cells(gx + (a.dmask & 1), a.N0, cx, ix);
   const int ny = cells(gy + ((a.dmask >> 1) & 1), a.N1, cy, iy);
   const int NP = a.p + 1, n = nx * ny;
-  const int64_t half = (int64_t)a.N0 * a.N1 * NP * NP * a.side_lanes;
+  const int64_t cut = (int64_t)a.N0 * a.N1 * NP * NP * a.side_lanes;
   auto at = [&](int x, int y) {
-    return a.side + 2 * sg * half + ((int64_t)((cx[x] + a.N0 * cy[y]) * NP + ix[x]) * NP + iy[y]) * a.side_lanes;
+    return a.side + sg * cut + ((int64_t)((cx[x] + a.N0 * cy[y]) * NP + ix[x]) * NP + iy[y]) * a.side_lanes;
   };
   // in phase order: x within y
   const TC *const s[4] = {at(0, 0), nx == 2 ? at(1, 0) : at(0, ny - 1), at(0, ny - 1), at(nx - 1, ny - 1)};
@@ -669,7 +670,7 @@ template <typename TS, typename TC> __global__ void __launch_bounds__(JOIN_THREA
     Two up[4], lo[4];
     auto load = [&](int k) {
       up[k] = *(const Two *)(s[k] + l);
-      lo[k] = *(const Two *)(s[k] + half + l);
+      lo[k] = *(const Two *)(s[k] + a.side_half + l);
     };
     load(0);
     if (n > 1) load(1);
@@ -771,10 +772,12 @@ inline void segments_begin(const LocalBatch &Bt, int vt, Count count, std::vecto
     as.push_back(make_args<TC>(Bt.ms[i], Bt.Ls[i], vt));
     as[i].nseg = count(Bt.ms[i], Bt.Ls[i], as[i].ntiles, side_limit(Bt.Ls[i]));
     as[i].side = (TC *)Bt.Ls[i].side;
+    as[i].side_half = Bt.Ls[i].side_bytes / 2 / (int64_t)sizeof(TC);
     if (as[i].nseg > 1 && !as[i].side) want += as[i].nseg * seg_bytes(i);
   }
   if (want == 0) return;
-  char *next = (char *)use.take(Bt.ms[0]->device, s);
+  int64_t half = 0;
+  char *next = (char *)use.take(Bt.ms[0]->device, s, &half);
   for (int i = 0; i < Bt.n; ++i) {
     if (as[i].nseg == 1 || as[i].side) continue;
     if (next && want > SIDE_BYTES)
@@ -782,7 +785,8 @@ inline void segments_begin(const LocalBatch &Bt, int vt, Count count, std::vecto
     if (!next) as[i].nseg = 1;
     if (as[i].nseg == 1) continue;
     as[i].side = (TC *)next;
-    next += as[i].nseg * seg_bytes(i);
+    as[i].side_half = half / (int64_t)sizeof(TC);
+    next += as[i].nseg * seg_bytes(i) / 2;
   }
 }
 template <typename TS, typename TC>
@@ -795,7 +799,7 @@ inline fe_status segments_end(int vt, const std::vector<KArgs<TC>> &as, bool pla
     for (; i < as.size() && n < JOIN_MAXB; ++i) {
       const KArgs<TC> &a = as[i];
       if (a.nseg == 1) continue;
-      J.sys[n++] = {(TS *)a.Y, a.side, a.ldy, a.M0, a.M1, a.N0, a.N1, a.N2, a.p, a.dmask, a.nseg, a.ntiles * vt, a.nlanes};
+      J.sys[n++] = {(TS *)a.Y, a.side, a.side_half, a.ldy, a.M0, a.M1, a.N0, a.N1, a.N2, a.p, a.dmask, a.nseg, a.ntiles * vt, a.nlanes};
       mx = std::max(mx, (unsigned)a.M0);
       my = std::max(my, (unsigned)a.M1);
       J.segs = std::max(J.segs, a.nseg);

@@ -607,7 +607,7 @@ __device__ __forceinline__ void plane_column(const KArgs<TC> &a, const int col, 
   const int side_lanes = a.ntiles * S::VT, side_x = NP * side_lanes;
   const unsigned so = t0 < NT && pl < NP ? (unsigned)(pl * side_lanes + lane) * (unsigned)sizeof(TC) : BUF_OFF;
   auto side_at = [&](int sg, int half) {
-    return a.side + ((int64_t)(2 * sg + half) * (a.N0 * a.N1) + cx + a.N0 * cy) * (NP * NP) * side_lanes;
+    return a.side + half * a.side_half + ((int64_t)sg * (a.N0 * a.N1) + cx + a.N0 * cy) * (NP * NP) * side_lanes;
   };
   TC ksgn = 0;                                           // sign of the Bloch term in this lane
   if constexpr (CPLX && LPT == 1) ksgn = (lane & 1) ? (TC)-1 : (TC)1;
