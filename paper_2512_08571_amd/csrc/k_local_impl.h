@@ -152,7 +152,7 @@ template <typename TC> struct KArgs {
   const TC *pcoef;
   TC pkap[3];
   int nseg;            // segments a column is cut into, and the planes at their cuts (side_seg_bytes)
-  TC *side;
+  TC *side;            // (the first half)
   int64_t side_half;   // elements from its first half to the second
 };
 
@@ -406,7 +406,8 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
   const int byr = colour_of(cy == a.N1 - 1 ? 0 : cy + 1, a.N1);
 
   // this thread's block elements e = tid + r NT: the x/y part of the node
-  // index, and packed {plane k, lane offset v, in range, read-modify-write}
+  // index, and packed {plane k, lane offset v, in range, read-modify-write,
+  // place (i, j) in a side block's plane}
   int exy[XPT], emeta[XPT];
 #pragma unroll
   for (int r = 0; r < XPT; ++r) {
@@ -425,7 +426,7 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
     const int axo = (i == 0) ? axl : axr, byo = (j == 0) ? byl : byr;
     const bool rmw = !((!xs || ax < axo) && (!ys || by < byo));
     const bool ok = e < NP3 * NV && lane0 + v < a.nlanes && inb;
-    emeta[r] = (n / NP2) | (v << 4) | (ok ? 1 << 12 : 0) | (rmw ? 1 << 13 : 0);
+    emeta[r] = (n / NP2) | (v << 4) | (ok ? 1 << 12 : 0) | (rmw ? 1 << 13 : 0) | ((i * NP + j) << 14);
   }
   auto ek = [&](int r) { return emeta[r] & 15; };
   auto elane = [&](int r) { return lane0 + ((emeta[r] >> 4) & 255); };
@@ -438,12 +439,11 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
     if (!zoff && gz >= a.M2) gz -= a.M2;
     return (int64_t)exy[r] + MM * gz;
   };
-  // this thread's element of half 0 (a segment's first plane) or 1 (the last
-  // plane of the one below) of cut sg (layout at side_seg_bytes)
-  auto side_of = [&](int r, int sg, int half) -> TC * {
-    const int n = (tid + r * NT) / NV, ij = (n % NP) * NP + (n / NP) % NP;
-    const int64_t plane = (int64_t)sg * (a.N0 * a.N1) + cx + a.N0 * cy;
-    return a.side + half * a.side_half + (plane * NP2 + ij) * (a.ntiles * VT) + elane(r);
+  // this column's plane of half 0 (a segment's first plane) or 1 (the last plane
+  // of the one below) of cut sg (layout at side_seg_bytes)
+  const int side_lanes = a.ntiles * VT;
+  auto side_at = [&](int sg, int half) {
+    return a.side + half * a.side_half + ((int64_t)sg * (a.N0 * a.N1) + cx + a.N0 * cy) * NP2 * side_lanes;
   };
   // plane k of cell cz holds DoFs (always on a periodic a_2)
   auto zin = [&](int k, int cz) { const int gz = cz * p + k - zoff; return !zoff || (gz >= 0 && gz < a.M2); };
@@ -473,6 +473,7 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
     }
   };
   const bool one = a.nseg == 1;
+  TC *const side0 = side_at(seg, 0), *const side1 = side_at(seg + 1 < a.nseg ? seg + 1 : 0, 1);
   prefetch(c0);
 
   for (int cz = c0; cz < c1; ++cz) {
@@ -571,7 +572,7 @@ __device__ __forceinline__ void local_column(const KArgs<TC> &a, const int col, 
       TC val[LPE], out[LPE];
       LdsVec<TC, LPE>::ld(B + e * LPE, val);
       if (at_cut(ek(r))) {
-        TC *q = side_of(r, ek(r) == 0 ? seg : seg + 1 < a.nseg ? seg + 1 : 0, ek(r) == 0 ? 0 : 1);
+        TC *q = (ek(r) == 0 ? side0 : side1) + (emeta[r] >> 14) * side_lanes + elane(r);
         if constexpr (LPE * sizeof(TC) == 16) {
           VecIO<TC, TC, LPE>::st(q, val);
         } else {
@@ -618,7 +619,10 @@ __device__ __forceinline__ void local_item(const KArgs<TC> &a, int w) {
 // The plane kernels begin at zero and, where the block has the arithmetic's
 // type, meet the halves of the column's own wrap (cut 0) one after the other.
 // A node of a cut's plane is 2^tl threads of two lanes, as few as hold its
-// lanes up to a wave; its loads are in flight together.
+// lanes up to a wave; its loads are in flight together.  Bound by reading the
+// two halves, much of it from the caches: eleven cuts of 11 x 13 columns of 7
+// points x 101 FP64 lanes, 175 MB, 19 us; eight systems of 7^3 cells x 48 lanes
+// 28 us (a wave per node took 24.5 and 68).
 constexpr int JOIN_MAXB = 16, JOIN_THREADS = 256;
 template <typename TS, typename TC> struct JoinArgs {
   struct {
