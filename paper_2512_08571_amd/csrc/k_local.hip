@@ -17,15 +17,16 @@ fe_status launch_local_mass(const LocalBatch &B, hipStream_t s);
 // columns and tiles leaves most of the device idle for the length of a column.
 // Its columns are then cut into segments (the planes at the cuts go to a side
 // block and are formed after the last colour phase, in the order of uncut
-// columns: the count does not show in the result).  The count is the one of least cost, summed
-// over the colour phases (odd cell counts have five small ones): rounds of the
-// device's units, per_unit items each, times cells per item.  An item's first
-// gather and last plane cost about half a cell; a cell takes about 1 + 2 k with
-// k waves on a SIMD (FP64, 7 points: 20 us alone, 34 us by twos).  Measured per
+// columns: the count does not show in the result).  The count is the one of
+// least cost, summed over the colour phases (odd cell counts have five small
+// ones): rounds of the device's units, per_unit items each, times cells per
+// item.  An item's first gather and last plane cost about half a cell; a cell
+// takes about 1 + 2 k with k waves on a SIMD (FP64, 7 points: 20 us alone, 34 us
+// by twos).  Measured per
 // colour phase, 7 points: FP64 12^3 cells x 256 lanes, 1152 waves in two segments
 // (1.1 rounds) 362 us, in three 285; FP32 16^3 x 256, 1024 waves whole 500 us, in
 // two segments 395; the whole mass operator on 11 x 13 x 12 cells x 101 lanes
-// (nine phases) in five segments 463 us, in the model's twelve 408.
+// (nine phases) in five segments 463 us, in the model's eleven 417.
 // (SEG_MAX: past it every unit of the device has a segment of the four or more
 // columns to itself; k_planes_join takes segments x cells below 2^32)
 constexpr int64_t SEG_MAX = 2048;

@@ -44,8 +44,8 @@
 // column with the cell in LDS and a barrier at each change of direction (one
 // phase there / here): real 16^3 x 256 vectors at 6 points 583 / 386 us, at 7
 // points 648 / 545, complex 8 points 1288 / 890, real 9 points 12^3 952 / 870;
-// the whole operator on 31,500 DoFs complex x 30 vectors 190 / 40 us, on 4,096
-// DoFs x 16 vectors 75 / 42.
+// with columns cut into segments, 27,000 complex DoFs x 33 vectors 43 / 17,
+// 4,096 DoFs x 8 vectors 19 / 10.
 #pragma once
 #include <algorithm>
 #include <vector>

@@ -225,7 +225,7 @@ k_nl_w(NlGroup<TS, TC> grp) {
   constexpr int SB = (int)sizeof(TC) * PMAX * NW * TILE <= 32768 ? PMAX : 1;
   // Projector values, TE entries at a time in LDS (the space of the sums):
   // loaded row by row they were a chain of four to ten per X row and most of
-  // the time (31,500 complex DoFs x 66 lanes 47 -> 25 us; eight k-points of
+  // the time (27,000 complex DoFs x 66 lanes 47 -> 25 us; eight k-points of
   // 74,088 DoFs x 48 lanes 250 -> 164 us; as scalar loads of a wave's one row,
   // 16^3 cells degree 7, nine projectors, 256 lanes 449 -> 320 us)
   constexpr int TE = PMAX <= 4 ? 512 : 256;
@@ -668,8 +668,8 @@ void launch_nl_w(const NlGroup<TS, TC> &g, const NlExtent &e, hipStream_t s) {
 
 // A brick's up to 32 row tiles are four for each wave of a block; while the
 // blocks do not fill the device (two per CU) they are dealt to two or four
-// blocks.  31,500 DoFs: complex x 66 lanes 37 -> 23 us, 32 real lanes
-// 23 -> 11 us; 74,088 complex DoFs x 48 lanes 43 -> 36 us.
+// blocks.  27,000 complex DoFs x 66 lanes 37 -> 23 us, 31,500 real x 32 lanes
+// 23 -> 12 us; 74,088 complex DoFs x 48 lanes 43 -> 36 us.
 template <bool CPLX> void launch_nl_ybm(const NlGroup<double, double> &g, const NlExtent &e, hipStream_t s) {
   if (e.bricks == 0) return;
   const int64_t whole = e.bricks * 8 * ((e.nlanes + NL_MN - 1) / NL_MN);
@@ -845,11 +845,11 @@ fe_status ensure_side_stream(Mesh *m) {
 // launches and the projector update Y += alpha F W after them.  FP64: all on
 // the caller's stream.  FP32 / BF16: the reduction is forked to the mesh's
 // second stream, beside the local launches (both only read X), and joined
-// back before the update.  The choice is measured: the FP64 line-gather
-// local kernel fills the CUs' registers and loses more to a co-running
-// reduction than the reduction takes on its own (Mid: step 3.57 ms forked,
-// 3.53 ms in order), while the FP32 staged kernel loses less (filter pass at
-// 512 vectors: 258 ms forked, 264 ms in order).
+// back before the update.  The choice is measured on the plane kernels, forked
+// / in order: a filter pass in FP32 on 14^3 cells of 7 points x 192 vectors
+// 12.84 / 13.01 ms, one BF16 application on 12^3 x 200 538 / 573 us, one FP32
+// application on 16^3 x 256 1697 / 1682.  FP64 fills the CUs' registers and
+// loses more to a co-running reduction than that takes on its own.
 static bool nl_forked(int prec) { return prec != FE_F64; }
 
 fe_status nonlocal_reduce(Mesh *m, const void *X, int64_t ldx, int nlanes, int prec, const double *dinv,
