@@ -278,9 +278,10 @@ fe_status fe_rayleigh_ritz(fe_mesh_t mesh, void *X, int64_t ldx, int64_t nvec,
 
 /* Y_i = H_i X_i for n systems (meshes on one device) in as few launches as
  * possible: the local operator of all systems of one class (degree,
- * quadrature, real/complex, vector tile) runs as one persistent launch per
- * colour phase over the concatenated (column, vector tile) work lists of up
- * to 8 systems at a time; the nonlocal terms follow per system.  Arrays of n
+ * quadrature, real/complex, kernel, vector tile where it has one) runs as one
+ * launch per colour phase over the concatenated (column, vector tile) work
+ * lists of up to 8 systems at a time; FP64 projector terms share launches
+ * likewise.  Arrays of n
  * entries (host): meshes, X[i] / Y[i] device blocks as in fe_apply_H with
  * ldx[i], ldy[i], nvec[i]; each mesh at most once per call.  Results equal n
  * separate fe_apply_H calls bit for bit.  Enqueued on 'stream'. */
@@ -300,7 +301,9 @@ fe_status fe_batch_apply(int32_t n, const fe_mesh_t *meshes, const void *const *
  * mesh (16 FP64 lanes at n_p = 8, two lanes wherever four fit, ...).
  * fe_autotune runs every
  * candidate tile 'reps' times on scratch blocks of nvec vectors (allocated and
- * freed inside; synchronous), keeps the fastest on the mesh and returns it;
+ * freed inside; synchronous), keeps the fastest on the mesh and returns it
+ * (where a tile has no effect they are timed once, and the first that fits is
+ * kept);
  * cand_vt / cand_ms (host, FE_TILE_CANDIDATES entries, may be NULL) receive
  * each candidate's time per application in ms (-1: does not fit), *ncand
  * their count. */

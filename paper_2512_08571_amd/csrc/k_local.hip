@@ -56,17 +56,23 @@ int64_t side_seg_bytes(const Mesh *m, int64_t side_lanes, int elem_bytes) {
   return 2LL * m->N[0] * m->N[1] * m->np * m->np * side_lanes * elem_bytes;
 }
 
+// (k_planes_join's grid has the nodes along a_1 as its y)
+static int64_t side_room(const Mesh *m, int64_t side_bytes, int64_t seg_bytes) {
+  return m->Mn[1] > 65535 ? 0 : side_bytes / seg_bytes;
+}
+
 int plane_segment_count(const Mesh *m, int nq, int nlanes, bool f64, int lpt, int64_t side_bytes, double *cost) {
   const int vt = plane_vt(nq, lpt), tiles = (nlanes + vt - 1) / vt;
   return segment_count(m->phase_off.data(), m->nphase, m->N[2], tiles, 4 * m->cus, plane_waves(nq, f64, lpt),
-                       side_bytes / side_seg_bytes(m, (int64_t)tiles * vt, f64 ? 8 : 4), cost);
+                       side_room(m, side_bytes, side_seg_bytes(m, (int64_t)tiles * vt, f64 ? 8 : 4)), cost);
 }
 
 // the same for the staged kernels: blocks on CUs (distorted 8 x 10 x 8 cells
 // degree 4 x 64 FP64 vectors, whole columns 240 us, segments 117; 9 points
 // 12^3 cells degree 6 x 128 2157 and 1770)
 int block_segment_count(const Mesh *m, int tiles, int per_cu, int64_t seg_bytes, int64_t side_bytes) {
-  return segment_count(m->phase_off.data(), m->nphase, m->N[2], tiles, m->cus, per_cu, side_bytes / seg_bytes, nullptr);
+  return segment_count(m->phase_off.data(), m->nphase, m->N[2], tiles, m->cus, per_cu, side_room(m, side_bytes, seg_bytes),
+                       nullptr);
 }
 
 bool plane_mesh(const Mesh *m) { return !m->offd && m->nq == m->np; }

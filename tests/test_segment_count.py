@@ -42,3 +42,16 @@ def test_range_and_no_resident_block(count, cols, tiles, per_unit):
 def test_small_launches_are_cut_and_full_ones_whole(count):
     assert count([4] * 4, 16, 1, 1024, 2, 1 << 40) == 16
     assert count([64] * 4, 16, 32, 1024, 2, 1 << 40) == 1
+
+
+def test_nodes_past_the_grid_stay_whole():
+    """The planes at the cuts are formed by a grid with the nodes along a_1 as its y, at most 65535."""
+    if not os.path.exists(fehx.LIB_PATH):
+        pytest.skip("library not built")
+    f = getattr(fehx.lib(), "_ZN4fehx19plane_segment_countEPKNS_4MeshEiibilPd")
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_bool, ctypes.c_int, ctypes.c_int64, ctypes.c_void_p]
+    for n1, whole in ((1024, False), (32768, True)):
+        m = fehx.Mesh([[2, 0, 0], [0, n1, 0], [0, 0, 4]], (2, n1, 4), 2, 3, (0, 0, 0), device=-1)
+        assert (f(m._h, 3, 1, True, 1, 1 << 30, None) == 1) == whole
+        m.close()
