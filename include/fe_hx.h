@@ -53,10 +53,11 @@
  *  - Host arrays passed in are copied before return; the caller keeps
  *    ownership.  Device buffers the mesh allocates are freed by
  *    fe_mesh_destroy.
- *  - While meshes exist, the library holds one scratch block of 128 MiB per mesh,
- *    at most four, on their device (outside the meshes' footprint): an
- *    application of few columns cuts them into segments and keeps the planes at
- *    the cuts there.  Results do not depend on it.
+ *  - The library holds one scratch block of 192 MiB per mesh, at most four, on
+ *    their device (outside the meshes' footprint; the last mesh gives all but
+ *    one back, which stays until the process ends): an application of few
+ *    columns cuts them into segments and keeps the planes at the cuts there.
+ *    Results do not depend on it.
  */
 #ifndef FE_HX_H
 #define FE_HX_H

@@ -132,7 +132,7 @@ constexpr int plane_waves(int nq, bool f64, int lpt) {
 // Segments a column of cells is cut into (segment_count), and the block for
 // the planes at their cuts
 constexpr int64_t NOALLOC_SIDE_BYTES = 64LL << 20;   // beside the static scratch
-constexpr int64_t SIDE_BYTES = 128LL << 20;          // of the device's blocks, in two halves
+constexpr int64_t SIDE_BYTES = 192LL << 20;          // of the device's blocks, in two halves
 int64_t side_seg_bytes(const Mesh *m, int64_t side_lanes, int elem_bytes);
 int segment_count(const int *phase_off, int nphase, int64_t cells, int64_t tiles, int units, int per_unit, int64_t cap,
                   double *cost);

@@ -26,7 +26,7 @@ fe_status launch_local_mass(const LocalBatch &B, hipStream_t s);
 // colour phase, 7 points: FP64 12^3 cells x 256 lanes, 1152 waves in two segments
 // (1.1 rounds) 362 us, in three 285; FP32 16^3 x 256, 1024 waves whole 500 us, in
 // two segments 395; the whole mass operator on 11 x 13 x 12 cells x 101 lanes
-// (nine phases) in five segments 463 us, in the model's eleven 417.
+// (nine phases) in five segments 463 us, in the model's twelve 380.
 // (SEG_MAX: past it every unit of the device has a segment of the four or more
 // columns to itself; k_planes_join takes segments x cells below 2^32)
 constexpr int64_t SEG_MAX = 2048;
@@ -129,17 +129,20 @@ int64_t plane_side_need(const Mesh *m, int nlanes, int prec) {
 
 // ---- side blocks ------------------------------------------------------------
 // They belong to the device: as many as it has meshes, up to SIDE_BLOCKS,
-// allocated when a mesh is made and freed with the last one, so that an
-// application allocates nothing, whichever mesh it is on.  An application that
-// cuts its columns holds one while it enqueues and leaves an event behind; the
-// next on that stream follows in stream order, one on another stream takes a
-// block whose event has passed.  Without a block (all in use by other streams, no
-// memory for one, or a stream that is capturing, whose graph may be replayed
-// beside anything) columns stay whole, with the same result.
-// (The event orders work on the device only: without the fence to the host it
-// costs 0.7 us of an application, with it 2.5.)
-// The halves are allocations of their own: past 64 MiB one takes 140 us and its
-// release 350, below 12 each.
+// allocated when a mesh is made, so that an application allocates nothing,
+// whichever mesh it is on.  The last mesh frees all but the first block, which
+// the next mesh of the process finds (a program that makes and destroys one
+// mesh at a time paid 0.2 ms for making and 0.6 for destroying each).
+// An application that cuts its columns holds one while it enqueues and leaves
+// an event behind; the next on that stream follows in stream order, one on
+// another stream takes a block whose event has passed.  Without a block (all in
+// use by other streams, no memory for one, or a stream that is capturing, whose
+// graph may be replayed beside anything) columns stay whole, with the same
+// result.  The event orders work on the device only: without the fence to the
+// host it costs 0.7 us of an application, with it 2.5.
+// 192 MiB hold the segments that the device's fill asks for: 12^3 cells of 9
+// points x 256 FP64 lanes, three of 48 MiB, 3026 us an application, whole
+// columns 3490.
 constexpr int SIDE_BLOCKS = 4, SIDE_DEVICES = 64;
 struct SideBlock {
   void *p = nullptr, *q = nullptr;
@@ -192,7 +195,8 @@ void side_pool_leave(int device) {
   SidePool &P = g_side[device];
   std::lock_guard<std::mutex> g(P.mu);
   if (--P.meshes > 0) return;
-  for (SideBlock &b : P.blocks) {
+  for (int i = 1; i < SIDE_BLOCKS; ++i) {
+    SideBlock &b = P.blocks[i];
     if (b.p) {
       hipFree(b.p);
       hipFree(b.q);

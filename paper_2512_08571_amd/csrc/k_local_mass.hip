@@ -1,7 +1,7 @@
 // The consistent mass operator of affine cells on the plane kernels
 // (k_local_planes.h), all precisions.  Bound by the gather and scatter of each
 // colour phase; 11 x 13 x 12 cells degree 6 x 101 FP64 vectors: 953 us as the
-// staged operator with zero derivative tables, 417 here (nine phases).
+// staged operator with zero derivative tables, 380 here (nine phases).
 #include "k_local_planes.h"
 
 namespace fehx {

@@ -125,3 +125,51 @@ def test_filter_graph_beside_applications():
         assert torch.equal(G, want) and torch.equal(Y, alone)
     graph.close()
     assert m.footprint == held
+
+
+def test_application_beside_a_capture():
+    """An application on one stream while another captures: neither disturbs the other."""
+    m = _mesh()
+    X = _block(m, 24)
+    alone, Y, Z = torch.empty_like(X), torch.empty_like(X), torch.zeros_like(X)
+    m.apply(X, alone)
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        Z.add_(1.0)
+        for _ in range(2):
+            m.apply(X, Y, stream=s)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, alone) and not Z.any()
+    for i in range(3):
+        g.replay()
+        m.apply(X, Y)
+        torch.cuda.synchronize()
+        assert torch.equal(Y, alone) and bool((Z == i + 1).all())
+
+
+def test_threads_with_meshes_of_their_own():
+    """Two host threads, each with its mesh and stream, share the device's blocks."""
+    import threading
+    ms = [_mesh(seed=i) for i in range(2)]
+    X = [_block(m, 24, i) for i, m in enumerate(ms)]
+    alone = [torch.empty_like(x) for x in X]
+    for m, x, y in zip(ms, X, alone):
+        m.apply(x, y)
+    st = [torch.cuda.Stream() for _ in ms]
+    Y = [[torch.empty_like(x) for _ in range(60)] for x in X]
+    torch.cuda.synchronize()
+
+    def work(i):
+        for y in Y[i]:
+            ms[i].apply(X[i], y, stream=st[i])
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert all(torch.equal(y, alone[i]) for y in Y[i])
